@@ -215,7 +215,7 @@ bd_status bd_prefill(bd_model* model, const int32_t* prompt_dev, int32_t b, int3
  *   conf_dev [b][G] float32: confidence of every position masked this step,
  *   tok_dev [b][G] int32: its argmax;
  *   logits_dev [b][G][vocab] float32: scaled, mask-suppressed logits (-inf in
- *   the mask column) of those positions, from a separate debug kernel.
+ *   the mask column) of those positions, written by the LM head itself.
  *  Positions not masked this step are left untouched.
  *  Errors: BD_ESTATE when the previous step was not committed.
  */

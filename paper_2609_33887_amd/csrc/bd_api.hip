@@ -139,7 +139,6 @@ struct bd_state {
   int32_t* parg;
   float* conf;
   int32_t* tok;
-  float* logits_tmp;
   // bf16 models: plane offsets (elements) of the lo halves of A, Ob, Hact, Alm
   size_t pl_A, pl_O, pl_H, pl_lm;
   int attn_splits;
@@ -479,7 +478,7 @@ static bd_status run_moe(bd_model* m, bd_state* s, const LayerW& L, const PlanVi
 }
 
 static bd_status run_forward(bd_model* m, bd_state* s, const PlanView& plan, int rows_cap,
-                             int win_cap, bool lm) {
+                             int win_cap, bool lm, const StepOut& so = StepOut{}) {
   const bd_model_cfg& c = m->cfg;
   const bool bf = m->bf16;
   const hipStream_t st = m->stream;
@@ -552,7 +551,7 @@ static bd_status run_forward(bd_model* m, bd_state* s, const PlanView& plan, int
                                         plan.lm_row, s->lm_cap, s->Alm, s->pl_lm, pend, st));
     LAUNCH(BD_PROF_LM_HEAD, launch_lm_head(bf, s->Alm, d, s->pl_lm, m->lm_head, c.vocab, c.mask_id,
                                            c.logit_scale, plan.hdr + 1, s->lm_cap, s->pmax, s->psum,
-                                           s->parg, s->conf, s->tok, st));
+                                           s->parg, s->conf, s->tok, so, st));
   }
   return BD_OK;
 }
@@ -862,21 +861,17 @@ extern "C" bd_status bd_denoise_step(bd_model* m, bd_state* s, float* conf_dev, 
   if (!m || !s) return fail(BD_EINVAL, "NULL argument");
   if (s->pending) return fail(BD_ESTATE, "previous step not committed");
   const PlanView& plan = s->plan[s->cur];
-  bd_status r = run_forward(m, s, plan, s->rows_step, s->win_step, true);
+  StepOut so;
+  so.conf = conf_dev;
+  so.tok = tok_dev;
+  so.logits = logits_dev;
+  so.lm_row = plan.lm_row;
+  so.row_seq = plan.row_seq;
+  so.row_pos = plan.row_pos;
+  so.P = s->P;
+  so.G = s->G;
+  bd_status r = run_forward(m, s, plan, s->rows_step, s->win_step, true, so);
   if (r != BD_OK) return r;
-  const bd_model_cfg& c = m->cfg;
-  if (conf_dev || tok_dev)
-    HIPCHK(launch_scatter_stats(s->conf, s->tok, plan, s->P, s->G, conf_dev, tok_dev, s->lm_cap,
-                                m->stream));
-  if (logits_dev) {
-    if (!s->logits_tmp) {
-      if ((r = dev_alloc(s, (void**)&s->logits_tmp, (size_t)s->lm_cap * c.vocab * 4)) != BD_OK) return r;
-    }
-    HIPCHK(launch_lm_logits(m->bf16, s->Alm, c.d_model, s->pl_lm, m->lm_head, c.vocab, c.mask_id, c.logit_scale,
-                            plan.hdr + 1, s->lm_cap, s->logits_tmp, m->stream));
-    HIPCHK(launch_scatter_logits(s->logits_tmp, plan, c.vocab, s->P, s->G, logits_dev, s->lm_cap,
-                                 m->stream));
-  }
   s->pending = true;
   return BD_OK;
 }

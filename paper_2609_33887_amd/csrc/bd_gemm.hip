@@ -443,8 +443,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const bf16_t* __restrict_
           const int n = n0 + wn * WCOL + j * 16 + (lane & 15);
           const float v = t.acc[i][j][r];
           if (EPI == EPI_ADD_F32 && S > 1) wz[(size_t)m * N + n] = v;
-          else if (EPI == EPI_ADD_F32) ((float*)out)[(size_t)m * ldo + n] += v;
-          else ((float*)out)[(size_t)m * ldo + n] = v;
+          else ((float*)out)[(size_t)m * ldo + n] += v;
         }
       }
     }
@@ -649,14 +648,19 @@ hipError_t launch_gemm_grouped(int epi, const void* A, int lda, size_t a_plane, 
 // with 8 waves of 64 x 64 (the gate/up tile) where the LM rows reach 2048,
 // else 128 x 128 with 4 waves of 64 x 64: on the multi-block decode's
 // 3072-row capacity the LM head went from 1065 to 772 us per launch.
-template <int TBN, int NW>
+// LOGITS: the tile's logits also go to the caller's [seq][position][V] buffer
+// straight from the accumulators (64-byte runs per row).  They used to come
+// from a second product of the same size, a scaling pass and a scatter pass
+// over [rows][V]: 199 us for 3072 rows x 4096 columns (d 2048) on top of the
+// head's 118, and 246 on top of 242 for 96 x 152064.
+template <int TBN, int NW, bool LOGITS>
 __global__ __launch_bounds__(64 * NW) void k_lm_head_bf16(const bf16_t* __restrict__ A, int d,
                                                       size_t a_plane,
                                                       const bf16_t* __restrict__ W, int V, int mask_id,
                                                       float scale, const int32_t* __restrict__ Mp,
                                                       int rows_cap, float* __restrict__ pmax,
                                                       float* __restrict__ psum,
-                                                      int32_t* __restrict__ parg) {
+                                                      int32_t* __restrict__ parg, StepOut so) {
   constexpr int TBM = 128, FN = TBN / (8 * NW), WCOL = 2 * TBN / NW, NP = NW / 2;
   const int M = *Mp;
   // items in bands of row tiles (band_tile): an XCD's concurrent workgroups
@@ -688,6 +692,14 @@ __global__ __launch_bounds__(64 * NW) void k_lm_head_bf16(const bf16_t* __restri
         const int n = n0 + wn * WCOL + j * 16 + (lane & 15);
         v[j] = (n == mask_id) ? -INFINITY : scale * t.acc[i][j][r];
         if (v[j] > mx) { mx = v[j]; arg = n; }
+      }
+      if constexpr (LOGITS) {
+        const int m = m0 + wm * 64 + i * 16 + (lane >> 4) * 4 + r;
+        if (m < M) {
+          float* z = so.logits + so.at(m) * V + n0 + wn * WCOL + (lane & 15);
+#pragma unroll
+          for (int j = 0; j < FN; ++j) z[j * 16] = v[j];
+        }
       }
 #pragma unroll
       for (int off = 1; off < 16; off <<= 1) {
@@ -807,7 +819,7 @@ __global__ __launch_bounds__(256) void k_lm_head_f32(const float* __restrict__ A
                                                      float scale, const int32_t* __restrict__ Mp,
                                                      int rows_cap, float* __restrict__ pmax,
                                                      float* __restrict__ psum,
-                                                     int32_t* __restrict__ parg) {
+                                                     int32_t* __restrict__ parg, int V, StepOut so) {
   const int M = *Mp;
   const int m0 = blockIdx.y * SBM;
   if (m0 >= M) return;
@@ -825,6 +837,11 @@ __global__ __launch_bounds__(256) void k_lm_head_f32(const float* __restrict__ A
       const int n = n0 + tx + 16 * j;
       v[j] = (n == mask_id) ? -INFINITY : scale * acc[i][j];
       if (v[j] > mx || (v[j] == mx && n < arg)) { mx = v[j]; arg = n; }
+    }
+    if (so.logits && m0 + ty * 4 + i < M) {
+      float* z = so.logits + so.at(m0 + ty * 4 + i) * V + n0 + tx;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) z[16 * j] = v[j];
     }
 #pragma unroll
     for (int off = 1; off < 16; off <<= 1) {
@@ -854,7 +871,8 @@ __global__ __launch_bounds__(256) void k_lm_merge(const float* __restrict__ pmax
                                                   const float* __restrict__ psum,
                                                   const int32_t* __restrict__ parg, int ntiles,
                                                   const int32_t* __restrict__ Mp, int rows_cap,
-                                                  float* __restrict__ conf, int32_t* __restrict__ tok) {
+                                                  float* __restrict__ conf, int32_t* __restrict__ tok,
+                                                  StepOut so) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int m = blockIdx.x * 4 + wave;
   if (m >= *Mp) return;
@@ -881,6 +899,8 @@ __global__ __launch_bounds__(256) void k_lm_merge(const float* __restrict__ pmax
   if (lane == 0) {
     conf[m] = 1.0f / s;
     tok[m] = arg;
+    if (so.conf) so.conf[so.at(m)] = 1.0f / s;
+    if (so.tok) so.tok[so.at(m)] = arg;
   }
 }
 
@@ -895,13 +915,9 @@ static void launch_bf16_cfg(int epi, dim3 grid, const bf16_t* a, int lda, size_t
       k_gemm_bf16<BM, BN, EPI_ADD_F32, WQ, NW><<<grid, 64 * NW, 0, st>>>(a, lda, ap, w, ldw, N, K, M_dev, o, ldo, op, ws,
                                                                  zmax, waux);
       break;
-    case EPI_SWIGLU:
+    default:   // EPI_SWIGLU
       k_gemm_bf16<BM, BN, EPI_SWIGLU, WQ, NW><<<grid, 64 * NW, 0, st>>>(a, lda, ap, w, ldw, N, K, M_dev, o, ldo, op,
                                                                 nullptr, 1, waux);
-      break;
-    default:
-      k_gemm_bf16<BM, BN, EPI_STORE_F32, WQ, NW><<<grid, 64 * NW, 0, st>>>(a, lda, ap, w, ldw, N, K, M_dev, o, ldo, op,
-                                                                   nullptr, 1, waux);
       break;
   }
 }
@@ -948,6 +964,7 @@ hipError_t launch_gemm_planned(const GemmPlan& p, int epi, const void* A, int ld
     return hipErrorInvalidValue;
   if ((wide || mid) && wq.fmt != WQ_NONE) return hipErrorInvalidValue;   // no quantized variants
   if (mid && p.zmax != 1) return hipErrorInvalidValue;
+  if (epi != EPI_ADD_F32 && epi != EPI_SWIGLU) return hipErrorInvalidValue;
   if (N % p.bn || K % KALIGN) return hipErrorInvalidValue;
   if (p.zmax > 1 && (epi != EPI_ADD_F32 || !ws)) return hipErrorInvalidValue;
   // 1-D grid: every (split, column tile, row tile) of the row capacity, + 7
@@ -1080,48 +1097,31 @@ hipError_t launch_lm_head(bool is_bf16, const void* A, int d, size_t a_plane, co
                           int mask_id, float scale, const int32_t* M_dev, int rows_cap,
                           float* part_max,
                           float* part_sum, int32_t* part_arg, float* conf, int32_t* tok,
-                          hipStream_t st) {
+                          const StepOut& so, hipStream_t st) {
   int ntiles;
   if (is_bf16) {
     if (V % 128 || d % KALIGN) return hipErrorInvalidValue;
     const bool wide = V % 256 == 0 && rows_cap >= 2048;
     ntiles = V / (wide ? 256 : 128);
     dim3 grid(ntiles * cdiv(rows_cap, 128) + 7);
-    if (wide)
-      k_lm_head_bf16<256, 8><<<grid, 512, 0, st>>>((const bf16_t*)A, d, a_plane, (const bf16_t*)W, V, mask_id,
-                                                   scale, M_dev, rows_cap, part_max, part_sum, part_arg);
-    else
-      k_lm_head_bf16<128, 4><<<grid, 256, 0, st>>>((const bf16_t*)A, d, a_plane, (const bf16_t*)W, V, mask_id,
-                                                   scale, M_dev, rows_cap, part_max, part_sum, part_arg);
+#define BD_HEAD(BN_, NW_, LOG_)                                                                           \
+  k_lm_head_bf16<BN_, NW_, LOG_><<<grid, 64 * NW_, 0, st>>>((const bf16_t*)A, d, a_plane, (const bf16_t*)W, V, mask_id, \
+                                                            scale, M_dev, rows_cap, part_max, part_sum, part_arg, so)
+    if (wide) {
+      if (so.logits) BD_HEAD(256, 8, true); else BD_HEAD(256, 8, false);
+    } else {
+      if (so.logits) BD_HEAD(128, 4, true); else BD_HEAD(128, 4, false);
+    }
+#undef BD_HEAD
   } else {
     if (V % SBN || d % SBK) return hipErrorInvalidValue;
     ntiles = V / SBN;
     dim3 grid(ntiles, cdiv(rows_cap, SBM));
     k_lm_head_f32<<<grid, 256, 0, st>>>((const float*)A, d, (const float*)W, mask_id, scale, M_dev,
-                                       rows_cap, part_max, part_sum, part_arg);
+                                       rows_cap, part_max, part_sum, part_arg, V, so);
   }
   k_lm_merge<<<cdiv(rows_cap, 4), 256, 0, st>>>(part_max, part_sum, part_arg, ntiles, M_dev, rows_cap,
-                                                conf, tok);
-  return hipGetLastError();
-}
-
-__global__ void k_logits_post(float* __restrict__ z, int V, int mask_id, float scale,
-                              const int32_t* __restrict__ Mp) {
-  const int m = blockIdx.y;
-  if (m >= *Mp) return;
-  for (int n = blockIdx.x * blockDim.x + threadIdx.x; n < V; n += gridDim.x * blockDim.x) {
-    float& v = z[(size_t)m * V + n];
-    v = (n == mask_id) ? -INFINITY : scale * v;
-  }
-}
-
-hipError_t launch_lm_logits(bool is_bf16, const void* A, int d, size_t a_plane, const void* W, int V,
-                            int mask_id, float scale, const int32_t* M_dev, int rows_cap,
-                            float* logits, hipStream_t st) {
-  hipError_t e = launch_gemm(EPI_STORE_F32, is_bf16, A, d, a_plane, W, d, V, d, M_dev, rows_cap,
-                             logits, V, 0, st);
-  if (e != hipSuccess) return e;
-  k_logits_post<<<dim3(cdiv(V, 256 * 8), rows_cap), 256, 0, st>>>(logits, V, mask_id, scale, M_dev);
+                                                conf, tok, so);
   return hipGetLastError();
 }
 

@@ -189,17 +189,32 @@ hipError_t launch_gemm_resid(bool is_bf16, const void* A, int lda, size_t a_plan
                              int ldx, float* ws, size_t ws_floats, ResidSplit* fold, hipStream_t st,
                              WQuant wq = WQuant{});
 
+// A step's outputs as the caller indexes them, [seq][generated position]
+// (each may be NULL): confidence, argmax and scaled, mask-suppressed logits
+// ([..][V], -inf in the mask column) of the LM rows.
+struct StepOut {
+  float* conf = nullptr;
+  int32_t* tok = nullptr;
+  float* logits = nullptr;
+  const int32_t* lm_row = nullptr;    // plan: window row of each LM row
+  const int32_t* row_seq = nullptr;   // plan: sequence of each window row
+  const int32_t* row_pos = nullptr;   // plan: absolute position of each window row
+  int P = 0, G = 0;
+  // [seq][position] index of LM row m
+  __device__ __forceinline__ size_t at(int m) const {
+    const int r = lm_row[m];
+    return (size_t)row_seq[r] * G + (row_pos[r] - P);
+  }
+};
+
 // LM head: per-row softmax statistics over the vocabulary of
 // z = scale * (A . W^T), mask column suppressed.  Writes per-(tile,row)
-// partials, then merges them into conf/tok.
+// partials, then merges them into conf/tok; the outputs asked for in `so`
+// are written on the way, the logits from the head's own accumulators.
 hipError_t launch_lm_head(bool is_bf16, const void* A, int d, size_t a_plane, const void* W, int V,
                           int mask_id, float scale, const int32_t* M_dev, int rows_cap,
                           float* part_max, float* part_sum, int32_t* part_arg, float* conf,
-                          int32_t* tok, hipStream_t st);
-// Debug: full logits [rows][V] for the LM rows (scaled, mask column = -inf).
-hipError_t launch_lm_logits(bool is_bf16, const void* A, int d, size_t a_plane, const void* W, int V,
-                            int mask_id, float scale, const int32_t* M_dev, int rows_cap,
-                            float* logits, hipStream_t st);
+                          int32_t* tok, const StepOut& so, hipStream_t st);
 
 // Work item of a workgroup in an XCD-aware launch.  Launches are 1-D with at
 // least items + 7 workgroups; the dispatcher deals consecutive workgroups to
@@ -340,9 +355,6 @@ struct InitArgs {
 };
 hipError_t launch_init_decode(const InitArgs& a, hipStream_t st);
 
-// Debug scatter of per-LM-row conf/tok to [b][G].
-hipError_t launch_scatter_stats(const float* conf, const int32_t* tok, PlanView plan, int P, int G,
-                                float* dconf, int32_t* dtok, int lm_cap, hipStream_t st);
 // QKV projection of bf16 models with RoPE and the cache write in the
 // epilogue.  W is the pair-interleaved copy made by launch_permute_qk_rows
 // (in each q and k head, packed row 2i = dim i, 2i + 1 = dim i + hd/2, so a
@@ -376,9 +388,5 @@ hipError_t launch_pack_gate_up(const void* gate, const void* up, void* out, int 
 
 // Zero `bytes` (a multiple of 4) at p (4-byte aligned) with a kernel.
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t st);
-
-// Debug scatter of logits rows to [b][G][V].
-hipError_t launch_scatter_logits(const float* logits, PlanView plan, int V, int P, int G,
-                                 float* out, int lm_cap, hipStream_t st);
 
 }  // namespace bd

@@ -781,48 +781,7 @@ hipError_t launch_quant_mxfp4_rows(const void* W, int rows, int cols, int group_
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ debug
-__global__ void k_scatter_logits(const float* __restrict__ logits, const int32_t* __restrict__ hdr,
-                                 const int32_t* __restrict__ lm_row,
-                                 const int32_t* __restrict__ row_seq,
-                                 const int32_t* __restrict__ row_pos, int V, int P, int G,
-                                 float* __restrict__ out) {
-  const int i = blockIdx.y;
-  if (i >= hdr[1]) return;
-  const int r = lm_row[i];
-  const size_t o = ((size_t)row_seq[r] * G + (row_pos[r] - P)) * V;
-  for (int n = blockIdx.x * blockDim.x + threadIdx.x; n < V; n += gridDim.x * blockDim.x)
-    out[o + n] = logits[(size_t)i * V + n];
-}
-
-hipError_t launch_scatter_logits(const float* logits, PlanView plan, int V, int P, int G,
-                                 float* out, int lm_cap, hipStream_t st) {
-  k_scatter_logits<<<dim3((V + 2047) / 2048, lm_cap), 256, 0, st>>>(logits, plan.hdr, plan.lm_row,
-                                                                     plan.row_seq, plan.row_pos, V,
-                                                                     P, G, out);
-  return hipGetLastError();
-}
-
-__global__ void k_scatter_stats(const float* __restrict__ conf, const int32_t* __restrict__ tok,
-                                const int32_t* __restrict__ hdr, const int32_t* __restrict__ lm_row,
-                                const int32_t* __restrict__ row_seq,
-                                const int32_t* __restrict__ row_pos, int P, int G,
-                                float* __restrict__ dconf, int32_t* __restrict__ dtok) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= hdr[1]) return;
-  const int r = lm_row[i];
-  const size_t o = (size_t)row_seq[r] * G + (row_pos[r] - P);
-  if (dconf) dconf[o] = conf[i];
-  if (dtok) dtok[o] = tok[i];
-}
-
-hipError_t launch_scatter_stats(const float* conf, const int32_t* tok, PlanView plan, int P, int G,
-                                float* dconf, int32_t* dtok, int lm_cap, hipStream_t st) {
-  k_scatter_stats<<<(lm_cap + 255) / 256, 256, 0, st>>>(conf, tok, plan.hdr, plan.lm_row, plan.row_seq,
-                                                        plan.row_pos, P, G, dconf, dtok);
-  return hipGetLastError();
-}
-
+// ------------------------------------------------------------------ weight packing
 // Pack gate and up projections into groups of 16 rows: packed rows
 // [32q, 32q + 16) = gate rows [16q, 16q + 16), [32q + 16, 32q + 32) = up rows.
 __global__ void k_pack_gate_up(const uint8_t* __restrict__ gate, const uint8_t* __restrict__ up,
