@@ -127,7 +127,6 @@ struct bd_state {
   int cur;
   float* X;
   void* A;
-  float* QKV;
   void* Qb;
   void* Ob;
   void* Hact;
@@ -483,7 +482,6 @@ static bd_status run_forward(bd_model* m, bd_state* s, const PlanView& plan, int
   const bool bf = m->bf16;
   const hipStream_t st = m->stream;
   const int d = c.d_model, H = c.n_heads, Hkv = c.n_kv_heads, hd = c.head_dim, F = c.ffn_dim;
-  const int qkv = (H + 2 * Hkv) * hd;
   // cache layout: K [layer][seq][kv head][pos][hd], V [layer][seq][kv head]
   // [vstride / 64][hd][64] (bf16) or as K (fp32); bf16 models keep the lo
   // planes of Q and of each whole cache after the hi planes
@@ -506,26 +504,22 @@ static bd_status run_forward(bd_model* m, bd_state* s, const PlanView& plan, int
     LAUNCH(BD_PROF_NORM, launch_rmsnorm(bf, s->X, L.attn_norm, d, c.rms_eps, plan.hdr, nullptr,
                                         rows_cap, s->A, s->pl_A, pend, st));
     pend.ws = nullptr;
-    if (bf) {
-      QkvEpi e;
-      e.row_seq = plan.row_seq;
-      e.row_pos = plan.row_pos;
-      e.rope = s->rope;
-      e.Q = s->Qb;
-      e.q_plane = q_plane;
-      e.kv = kv;
-      e.H = H;
-      e.Hkv = Hkv;
-      e.hd = hd;
-      e.rows4 = s->B % 4 == 0;
+    QkvEpi e;
+    e.row_seq = plan.row_seq;
+    e.row_pos = plan.row_pos;
+    e.rope = s->rope;
+    e.Q = s->Qb;
+    e.q_plane = q_plane;
+    e.kv = kv;
+    e.H = H;
+    e.Hkv = Hkv;
+    e.hd = hd;
+    e.rows4 = s->B % 4 == 0;
+    if (bf)
       LAUNCH(BD_PROF_GEMM_QKV, launch_gemm_qkv(s->A, d, s->pl_A, L.w_qkv_p, d, plan.hdr, rows_cap, e, st,
                                                L.q_qkv));
-    } else {
-      LAUNCH(BD_PROF_GEMM_QKV, launch_gemm(EPI_STORE_F32, bf, s->A, d, s->pl_A, L.w_qkv, d, qkv, d,
-                                           plan.hdr, rows_cap, s->QKV, qkv, 0, st));
-      LAUNCH(BD_PROF_ROPE, launch_rope_kv(s->QKV, plan, rows_cap, H, Hkv, hd, m->inv_freq,
-                                          (float*)s->Qb, kv, st));
-    }
+    else
+      LAUNCH(BD_PROF_GEMM_QKV, launch_gemm_qkv_f32(s->A, d, L.w_qkv, d, plan.hdr, rows_cap, e, m->inv_freq, st));
     LAUNCH(BD_PROF_ATTN, launch_attention(bf, s->Qb, q_plane, kv,
                                           s->Ob, s->pl_O, plan, s->b, win_cap, H, Hkv, hd, s->B,
                                           kv_splits, s->attn_ws_o, s->attn_ws_ml, rows_cap, st));
@@ -681,7 +675,6 @@ static bd_status state_layout(const bd_model* m, int32_t b, int32_t P, int32_t G
   s->rows_cap = s->rows_step > s->rows_pre ? s->rows_step : s->rows_pre;
   s->lm_cap = round_up(b * nb * B, 256);
   const int d = c.d_model, H = c.n_heads, Hkv = c.n_kv_heads, hd = c.head_dim;
-  const int qkv = (H + 2 * Hkv) * hd;
   const int ntiles = c.vocab / (m->bf16 ? 128 : 64);
   // the expert gate/up product gathers its token rows by 32-bit byte
   // offsets from the start of an activation plane
@@ -712,7 +705,6 @@ static bd_status state_layout(const bd_model* m, int32_t b, int32_t P, int32_t G
     s->pl_H = (size_t)s->rows_cap * (c.n_experts ? c.n_shared * c.expert_ffn : c.ffn_dim);
     s->pl_lm = (size_t)s->lm_cap * d;
   }
-  if (!m->bf16) ALLOC(s->QKV, (size_t)s->rows_cap * qkv * 4);
   ALLOC(s->Qb, (size_t)s->rows_cap * H * hd * 4);     // fp32, or a bf16 plane pair
   ALLOC(s->Ob, (size_t)s->rows_cap * H * hd * 4);
   const int Fh = c.n_experts ? c.n_shared * c.expert_ffn : c.ffn_dim;   // dense / shared FFN width

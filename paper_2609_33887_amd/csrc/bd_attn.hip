@@ -349,9 +349,14 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float* __restrict__ ws
       make_uint2((uint32_t)lb[0] | ((uint32_t)lb[1] << 16), (uint32_t)lb[2] | ((uint32_t)lb[3] << 16));
 }
 
-// fp32 reference-precision kernel for small fp32 models: one wave64 per
-// (query row, head); each lane owns head_dim/64 output dims and keys are
-// scanned with an online softmax.
+// fp32 models: a workgroup per (query row, head), its 4 waves taking the
+// 64-key tiles in turn.  For the scores a lane owns a key (its K row against
+// the query, held in LDS), so the softmax needs one wave reduction per 64 keys;
+// for P V a lane owns hd / 64 dims and the probabilities come round by lane
+// reads, every V row a coalesced load.  The four waves' running results are
+// merged in wave order.  36 keys, 4 rows x 4 heads: 21 us with one wave walking
+// the keys one by one (six shuffles and two dependent loads a key), 5 us so.
+template <int HD>
 __global__ __launch_bounds__(256) void k_attn_f32(const float* __restrict__ Q,
                                                   const float* __restrict__ Kc,
                                                   const float* __restrict__ Vc,
@@ -359,34 +364,77 @@ __global__ __launch_bounds__(256) void k_attn_f32(const float* __restrict__ Q,
                                                   const int32_t* __restrict__ row_seq,
                                                   const int32_t* __restrict__ row_pos,
                                                   const int32_t* __restrict__ Mp, int H, int Hkv,
-                                                  int hd, int maxpos, int B, float scale) {
+                                                  int maxpos, int B, float scale) {
+  constexpr int PER = HD / 64;
+  __shared__ __attribute__((aligned(16))) float sq[HD];
+  __shared__ float so[4][HD], sm[4], sl[4];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int item = blockIdx.x * 4 + wave;
-  const int r = item / H, h = item % H;
+  const int r = blockIdx.x / H, h = blockIdx.x % H;
   if (r >= *Mp) return;
   const int s = row_seq[r], pos = row_pos[r];
   const int kend = (pos / B + 1) * B;
   const int kv = h / (H / Hkv);
-  const float* Kp = Kc + ((size_t)s * Hkv + kv) * (size_t)maxpos * hd;
-  const float* Vp = Vc + ((size_t)s * Hkv + kv) * (size_t)maxpos * hd;
-  const float* q = Q + ((size_t)r * H + h) * hd;
-  const int per = hd / 64;   // 1 or 2
-  float qv[2] = {0.f, 0.f}, acc[2] = {0.f, 0.f};
-  for (int e = 0; e < per; ++e) qv[e] = q[lane * per + e];
-  float m = -INFINITY, l = 0.f;
-  for (int j = 0; j < kend; ++j) {
-    float part = 0.f;
-    for (int e = 0; e < per; ++e) part += qv[e] * Kp[(size_t)j * hd + lane * per + e];
-    for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
-    const float sc = part * scale;
-    const float mn = fmaxf(m, sc);
-    const float a = expf(m - mn), p = expf(sc - mn);
-    l = l * a + p;
-    for (int e = 0; e < per; ++e) acc[e] = acc[e] * a + p * Vp[(size_t)j * hd + lane * per + e];
+  const float* Kp = Kc + ((size_t)s * Hkv + kv) * (size_t)maxpos * HD;
+  const float* Vp = Vc + ((size_t)s * Hkv + kv) * (size_t)maxpos * HD;
+  if (threadIdx.x < HD) sq[threadIdx.x] = Q[((size_t)r * H + h) * HD + threadIdx.x];
+  __syncthreads();
+  float acc[PER], m = -INFINITY, l = 0.f;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) acc[e] = 0.f;
+  for (int k0 = wave * 64; k0 < kend; k0 += 256) {
+    const int key = k0 + lane;
+    float sc = -INFINITY;
+    if (key < kend) {
+      const float4* kr = (const float4*)(Kp + (size_t)key * HD);
+      float p[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int e = 0; e < HD / 4; ++e) {
+        const float4 kx = kr[e], qx = *(const float4*)(sq + 4 * e);
+        p[0] += kx.x * qx.x; p[1] += kx.y * qx.y; p[2] += kx.z * qx.z; p[3] += kx.w * qx.w;
+      }
+      sc = ((p[0] + p[1]) + (p[2] + p[3])) * scale;
+    }
+    float mt = sc;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) mt = fmaxf(mt, __shfl_xor(mt, off));
+    const float mn = fmaxf(m, mt);                // finite: the tile holds a key
+    const float al = expf(m - mn), pr = expf(sc - mn);
+    float ps = pr;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) ps += __shfl_xor(ps, off);
+    l = l * al + ps;
     m = mn;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) acc[e] *= al;
+    // eight V rows in flight; past the last key the row repeats, its weight 0
+    const int n = kend - k0 < 64 ? kend - k0 : 64;
+    const float* vr = Vp + (size_t)k0 * HD + lane * PER;
+    for (int j0 = 0; j0 < n; j0 += 8) {
+#pragma unroll
+      for (int jj = 0; jj < 8; ++jj) {
+        const int j = j0 + jj;
+        const float pj = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(pr), j));
+        const float* vj = vr + (size_t)(j < n ? j : n - 1) * HD;
+#pragma unroll
+        for (int e = 0; e < PER; ++e) acc[e] += pj * vj[e];
+      }
+    }
   }
-  float* o = O + (size_t)r * H * hd + h * hd;
-  for (int e = 0; e < per; ++e) o[lane * per + e] = acc[e] / l;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) so[wave][lane * PER + e] = acc[e];
+  if (lane == 0) { sm[wave] = m; sl[wave] = l; }
+  __syncthreads();
+  if (threadIdx.x < HD) {
+    const float mx = fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
+    float o = 0.f, L = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float f = expf(sm[w] - mx);           // 0 for a wave without keys
+      o += f * so[w][threadIdx.x];
+      L += f * sl[w];
+    }
+    O[((size_t)r * H + h) * HD + threadIdx.x] = o / L;
+  }
 }
 
 // waves per workgroup for a window of win_cap rows over a key capacity of
@@ -448,10 +496,12 @@ hipError_t launch_attention(bool is_bf16, const void* Q, size_t q_plane, const K
     }
   } else {
     if (hd != 64 && hd != 128) return hipErrorInvalidValue;
-    const int items = rows_cap * H;
-    k_attn_f32<<<(items + 3) / 4, 256, 0, st>>>((const float*)Q, (const float*)kv.K, (const float*)kv.V,
-                                                (float*)O, plan.row_seq, plan.row_pos, plan.hdr, H,
-                                                Hkv, hd, kv.maxpos, B, (float)(1.0 / sqrt((double)hd)));
+    const float scale = (float)(1.0 / sqrt((double)hd));
+#define BD_ATTN_F32(HD_)                                                                                       \
+  k_attn_f32<HD_><<<rows_cap * H, 256, 0, st>>>((const float*)Q, (const float*)kv.K, (const float*)kv.V, (float*)O, \
+                                                plan.row_seq, plan.row_pos, plan.hdr, H, Hkv, kv.maxpos, B, scale)
+    if (hd == 128) BD_ATTN_F32(128); else BD_ATTN_F32(64);
+#undef BD_ATTN_F32
   }
   return hipGetLastError();
 }

@@ -24,7 +24,7 @@
 // E2M1 value x 2^X, exact in bf16), again the bf16 product with the
 // dequantized weights.  The codes are stored stage-major (WQuant), so a
 // stage's W rows are one contiguous run of 16-byte rows.
-// f32 path (small fp32 models): 64x64x16 SIMT tiles.
+// f32 path (small fp32 models): fp32 MFMA tiles with K split over the waves.
 //
 // The row count M is read from device memory so that a launch sized for the
 // largest window can be replayed every step; tiles at or past M exit.
@@ -742,120 +742,190 @@ __global__ __launch_bounds__(64 * NW) void k_lm_head_bf16(const bf16_t* __restri
   }
 }
 
-// ------------------------------------------------------------------ f32 SIMT
-constexpr int SBM = 64, SBN = 64, SBK = 16;
+// ------------------------------------------------------------------ f32 MFMA
+// fp32 models are small, so their products are bound by latency and not by
+// arithmetic: the work of a tile is split over K between the waves of a
+// workgroup, every wave has its whole share of both operands in flight at
+// once (registers straight from global memory, no staging), multiplies on the
+// fp32 matrix cores (v_mfma_f32_16x16x4_f32: fp32 operands and accumulation)
+// and the KW partial tiles are summed in wave order in LDS.  A chunk is 16
+// deep: lane (c, g) holds depths 4 g .. 4 g + 3 of row c of either operand,
+// and MFMA step s takes element s of each lane (the same permutation of the
+// depth on both sides).  Tiles: 16 x 32 with 8 waves over K, and 64 x 32 (two
+// groups of 32 rows, 4 waves over K each) where the row capacity gives at
+// least 512 of them.  4 rows, N 256, K 1024: 80 us with 64 x 64 x 16 SIMT
+// tiles (4 workgroups, 64 barrier steps), 6 us so; N 2048, K 256: 33 -> 5 us.
+constexpr int FBN = 32;      // columns of a projection tile
+constexpr int FHN = 64;      // columns of a head tile
+constexpr int FCH = 16;      // depth per chunk
+// the caller's fp32 matrices need no more than 4-byte alignment
+typedef float floatx4_u __attribute__((ext_vector_type(4), aligned(4)));
 
-__device__ __forceinline__ void simt_mainloop(const float* __restrict__ A, int lda,
-                                              const float* __restrict__ W, int ldw, int K, int m0,
-                                              int n0, float acc[4][4], float* sA, float* sB) {
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+// Columns of fragment f of a wave's tile: 16 consecutive ones from
+// col0 + f * cstep on.  red: [KW][BM][16 FN + 1].
+template <int FM, int FN, int WM, int KW>
+__device__ __forceinline__ void f32_tile(const float* __restrict__ A, int lda, const float* __restrict__ W, int ldw,
+                                         int K, int m0, int col0, int cstep, float* __restrict__ red) {
+  constexpr int BM = 16 * FM * WM, LD = 16 * FN + 1, U = FM + FN <= 3 ? 8 : 4;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wm = wave % WM, kw = wave / WM;
+  const int c = lane & 15, g = lane >> 4;
+  const int nch = K / FCH, beg = nch * kw / KW, end = nch * (kw + 1) / KW;
+  const float* ap[FM];
+  const float* wp[FN];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < FM; ++i) ap[i] = A + (size_t)(m0 + (wm * FM + i) * 16 + c) * lda + 4 * g;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-  for (int k0 = 0; k0 < K; k0 += SBK) {
-    // 64 rows x 16 k = 1024 floats per operand: 4 per thread
+  for (int j = 0; j < FN; ++j) wp[j] = W + (size_t)(col0 + j * cstep + c) * ldw + 4 * g;
+  floatx4 acc[FM][FN];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int c = tid + 256 * q, r = c >> 4, kk = c & 15;
-      sA[kk * (SBM + 1) + r] = A[(size_t)(m0 + r) * lda + k0 + kk];
-      sB[kk * (SBN + 1) + r] = W[(size_t)(n0 + r) * ldw + k0 + kk];
-    }
-    __syncthreads();
+  for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int kk = 0; kk < SBK; ++kk) {
-      float a[4], b[4];
+    for (int j = 0; j < FN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int ch = beg; ch < end; ch += U) {
+    floatx4_u a[U][FM], w[U][FN];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = sA[kk * (SBM + 1) + ty * 4 + i];
+    for (int u = 0; u < U; ++u)
+      if (ch + u < end) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = sB[kk * (SBN + 1) + tx + 16 * j];
+        for (int i = 0; i < FM; ++i) a[u][i] = *(const floatx4_u*)(ap[i] + (size_t)(ch + u) * FCH);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+        for (int j = 0; j < FN; ++j) w[u][j] = *(const floatx4_u*)(wp[j] + (size_t)(ch + u) * FCH);
+      }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
+    for (int u = 0; u < U; ++u)
+      if (ch + u < end) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i][e], w[u][j][e], acc[i][j], 0, 0, 0);
+      }
   }
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        red[((size_t)kw * BM + (wm * FM + i) * 16 + 4 * g + r) * LD + j * 16 + c] = acc[i][j][r];
+  __syncthreads();
 }
 
-template <int EPI>
-__global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, int lda,
-                                                  const float* __restrict__ W, int ldw, int N, int K,
-                                                  const int32_t* __restrict__ Mp,
-                                                  void* __restrict__ out, int ldo) {
+// Sum of the KW partials of tile element (row, col), in wave order.
+template <int BM, int LD, int KW>
+__device__ __forceinline__ float f32_sum(const float* __restrict__ red, int row, int col) {
+  float v = red[row * LD + col];
+#pragma unroll
+  for (int k = 1; k < KW; ++k) v += red[(k * BM + row) * LD + col];
+  return v;
+}
+
+template <int FM, int WM, int KW, int EPI>
+__global__ __launch_bounds__(64 * WM * KW) void k_gemm_f32(const float* __restrict__ A, int lda,
+                                                           const float* __restrict__ W, int ldw, int K,
+                                                           const int32_t* __restrict__ Mp,
+                                                           float* __restrict__ out, int ldo) {
+  constexpr int BM = 16 * FM * WM, LD = FBN + 1, NT = 64 * WM * KW;
+  __shared__ float red[KW * BM * LD];
   const int M = *Mp;
-  const int m0 = blockIdx.y * SBM;
+  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * FBN;
   if (m0 >= M) return;
-  const int n0 = blockIdx.x * SBN;
-  __shared__ float sA[SBK * (SBM + 1)], sB[SBK * (SBN + 1)];
-  float acc[4][4];
-  simt_mainloop(A, lda, W, ldw, K, m0, n0, acc, sA, sB);
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty * 4 + i;
-    if (m >= M) continue;
-    if constexpr (EPI == EPI_SWIGLU) {
-      // packed gate/up groups of 16 columns: j even = gate, j odd = up
-#pragma unroll
-      for (int j = 0; j < 4; j += 2) {
-        const int pb = n0 + 16 * j;
-        const int col = (pb >> 5) * 16 + tx;
-        ((float*)out)[(size_t)m * ldo + col] = silu(acc[i][j]) * acc[i][j + 1];
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int n = n0 + tx + 16 * j;
-        if constexpr (EPI == EPI_ADD_F32) ((float*)out)[(size_t)m * ldo + n] += acc[i][j];
-        else ((float*)out)[(size_t)m * ldo + n] = acc[i][j];
-      }
+  f32_tile<FM, 2, WM, KW>(A, lda, W, ldw, K, m0, n0, 16, red);
+  if constexpr (EPI == EPI_SWIGLU) {
+    // packed gate/up groups of 16 columns: fragment 0 = gate, 1 = up
+    for (int e = threadIdx.x; e < BM * 16; e += NT) {
+      const int r = e >> 4, c = e & 15, m = m0 + r;
+      if (m >= M) continue;
+      const float gt = f32_sum<BM, LD, KW>(red, r, c), up = f32_sum<BM, LD, KW>(red, r, 16 + c);
+      out[(size_t)m * ldo + (n0 >> 1) + c] = silu(gt) * up;
+    }
+  } else {
+    for (int e = threadIdx.x; e < BM * FBN; e += NT) {
+      const int r = e / FBN, c = e % FBN, m = m0 + r;
+      if (m >= M) continue;
+      out[(size_t)m * ldo + n0 + c] += f32_sum<BM, LD, KW>(red, r, c);
     }
   }
 }
 
-__global__ __launch_bounds__(256) void k_lm_head_f32(const float* __restrict__ A, int d,
+// fp32 QKV projection with RoPE and the cache write in the epilogue.  A tile
+// is 16 dims i .. i + 15 of one head and their rotation partners
+// i + hd/2 .. (its two column fragments), so both halves of a rotation meet in
+// one thread; angle and rotation in fp64 with one rounding to fp32, at the
+// row's absolute position.  q -> Q[row][head][hd], k and v -> the cache slots
+// [seq][kv head][pos][hd].
+template <int FM, int WM, int KW>
+__global__ __launch_bounds__(64 * WM * KW) void k_gemm_qkv_f32(const float* __restrict__ A, int lda,
+                                                               const float* __restrict__ W, int K,
+                                                               const int32_t* __restrict__ Mp, QkvEpi q,
+                                                               const double* __restrict__ inv_freq) {
+  constexpr int BM = 16 * FM * WM, LD = FBN + 1, NT = 64 * WM * KW;
+  __shared__ float red[KW * BM * LD];
+  const int M = *Mp;
+  const int m0 = blockIdx.y * BM;
+  if (m0 >= M) return;
+  const int half = q.hd / 2, tph = q.hd / FBN;              // tiles per head
+  const int head = blockIdx.x / tph, i0 = (blockIdx.x % tph) * 16;
+  f32_tile<FM, 2, WM, KW>(A, lda, W, K, K, m0, head * q.hd + i0, half, red);
+  for (int e = threadIdx.x; e < BM * 16; e += NT) {
+    const int r = e >> 4, i = i0 + (e & 15), m = m0 + r;
+    if (m >= M) continue;
+    const float x1 = f32_sum<BM, LD, KW>(red, r, e & 15), x2 = f32_sum<BM, LD, KW>(red, r, 16 + (e & 15));
+    const int s = q.row_seq[m], pos = q.row_pos[m];
+    float y1 = x1, y2 = x2;
+    float* o;
+    if (head < q.H + q.Hkv) {
+      double sn, cs;
+      sincos((double)pos * inv_freq[i], &sn, &cs);
+      y1 = (float)((double)x1 * cs - (double)x2 * sn);
+      y2 = (float)((double)x2 * cs + (double)x1 * sn);
+      o = head < q.H ? (float*)q.Q + ((size_t)m * q.H + head) * q.hd
+                     : (float*)q.kv.K + (((size_t)s * q.Hkv + (head - q.H)) * q.kv.maxpos + pos) * q.hd;
+    } else {
+      o = (float*)q.kv.V + (((size_t)s * q.Hkv + (head - q.H - q.Hkv)) * q.kv.maxpos + pos) * q.hd;
+    }
+    o[i] = y1;
+    o[i + half] = y2;
+  }
+}
+
+// fp32 LM head: 16 rows x 64 vocabulary columns, 8 waves over K; a wave then
+// takes two rows, a lane a column.
+__global__ __launch_bounds__(512) void k_lm_head_f32(const float* __restrict__ A, int d,
                                                      const float* __restrict__ W, int mask_id,
                                                      float scale, const int32_t* __restrict__ Mp,
                                                      int rows_cap, float* __restrict__ pmax,
                                                      float* __restrict__ psum,
                                                      int32_t* __restrict__ parg, int V, StepOut so) {
+  constexpr int BM = 16, LD = FHN + 1, KW = 8;
+  __shared__ float red[KW * BM * LD];
   const int M = *Mp;
-  const int m0 = blockIdx.y * SBM;
+  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * FHN;
   if (m0 >= M) return;
-  const int n0 = blockIdx.x * SBN;
-  __shared__ float sA[SBK * (SBM + 1)], sB[SBK * (SBN + 1)];
-  float acc[4][4];
-  simt_mainloop(A, d, W, d, d, m0, n0, acc, sA, sB);
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+  f32_tile<1, 4, 1, KW>(A, d, W, d, d, m0, n0, 16, red);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n = n0 + lane;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    float v[4], mx = -INFINITY;
-    int arg = 0x7fffffff;
+  for (int q = 0; q < 2; ++q) {
+    const int r = wave * 2 + q, m = m0 + r;
+    if (m >= M) continue;                                   // wave-uniform
+    const float v = n == mask_id ? -INFINITY : scale * f32_sum<BM, LD, KW>(red, r, lane);
+    if (so.logits) so.logits[so.at(m) * V + n] = v;
+    float mx = v;
+    int arg = n;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx + 16 * j;
-      v[j] = (n == mask_id) ? -INFINITY : scale * acc[i][j];
-      if (v[j] > mx || (v[j] == mx && n < arg)) { mx = v[j]; arg = n; }
-    }
-    if (so.logits && m0 + ty * 4 + i < M) {
-      float* z = so.logits + so.at(m0 + ty * 4 + i) * V + n0 + tx;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) z[16 * j] = v[j];
-    }
-#pragma unroll
-    for (int off = 1; off < 16; off <<= 1) {
+    for (int off = 1; off < 64; off <<= 1) {
       const float om = __shfl_xor(mx, off);
       const int oa = __shfl_xor(arg, off);
       if (om > mx || (om == mx && oa < arg)) { mx = om; arg = oa; }
     }
-    float s = 0.f;
+    float s = expf(v - mx);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) s += expf(v[j] - mx);
-#pragma unroll
-    for (int off = 1; off < 16; off <<= 1) s += __shfl_xor(s, off);
-    const int m = m0 + ty * 4 + i;
-    if (tx == 0 && m < M) {
+    for (int off = 1; off < 64; off <<= 1) s += __shfl_xor(s, off);
+    if (lane == 0) {
       const size_t o = (size_t)blockIdx.x * rows_cap + m;
       pmax[o] = mx;
       psum[o] = s;
@@ -1074,6 +1144,10 @@ hipError_t launch_gemm_qkv(const void* A, int lda, size_t a_plane, const void* W
   return hipGetLastError();
 }
 
+// 64 x 32 tiles instead of 16 x 32 where the row capacity holds at least 512 of
+// them (two workgroups a CU): a quarter of the operand reads per product.
+static bool f32_large(int N, int rows_cap) { return (N / FBN) * cdiv(rows_cap, 64) >= 512; }
+
 hipError_t launch_gemm(int epi, bool is_bf16, const void* A, int lda, size_t a_plane, const void* W,
                        int ldw, int N, int K, const int32_t* M_dev, int rows_cap, void* out, int ldo,
                        size_t out_plane, hipStream_t st, WQuant wq) {
@@ -1081,15 +1155,31 @@ hipError_t launch_gemm(int epi, bool is_bf16, const void* A, int lda, size_t a_p
     return launch_gemm_planned(plan_gemm(true, N, K, rows_cap, false, wq.fmt == WQ_NONE), epi, A, lda, a_plane,
                                W, ldw, N, K, M_dev, rows_cap, out, ldo, out_plane, nullptr, st, wq);
   if (wq.fmt != WQ_NONE) return hipErrorInvalidValue;
-  if (N % SBN || K % SBK) return hipErrorInvalidValue;
-  dim3 grid(N / SBN, cdiv(rows_cap, SBM));
+  if (N % FBN || K % FCH || lda % 4 || ldw % 4 || (epi != EPI_ADD_F32 && epi != EPI_SWIGLU)) return hipErrorInvalidValue;
   const float* a = (const float*)A;
   const float* w = (const float*)W;
-  switch (epi) {
-    case EPI_ADD_F32: k_gemm_f32<EPI_ADD_F32><<<grid, 256, 0, st>>>(a, lda, w, ldw, N, K, M_dev, out, ldo); break;
-    case EPI_SWIGLU: k_gemm_f32<EPI_SWIGLU><<<grid, 256, 0, st>>>(a, lda, w, ldw, N, K, M_dev, out, ldo); break;
-    default: k_gemm_f32<EPI_STORE_F32><<<grid, 256, 0, st>>>(a, lda, w, ldw, N, K, M_dev, out, ldo); break;
+#define BD_F32(FM_, WM_, KW_, EPI_)                                                                                 \
+  k_gemm_f32<FM_, WM_, KW_, EPI_><<<dim3(N / FBN, cdiv(rows_cap, 16 * FM_ * WM_)), 64 * WM_ * KW_, 0, st>>>(a, lda, w, ldw, \
+                                                                                                      K, M_dev, (float*)out, ldo)
+  if (f32_large(N, rows_cap)) {
+    if (epi == EPI_ADD_F32) BD_F32(2, 2, 4, EPI_ADD_F32); else BD_F32(2, 2, 4, EPI_SWIGLU);
+  } else {
+    if (epi == EPI_ADD_F32) BD_F32(1, 1, 8, EPI_ADD_F32); else BD_F32(1, 1, 8, EPI_SWIGLU);
   }
+#undef BD_F32
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm_qkv_f32(const void* A, int lda, const void* W, int K, const int32_t* M_dev, int rows_cap,
+                               const QkvEpi& e, const double* inv_freq, hipStream_t st) {
+  const int N = (e.H + 2 * e.Hkv) * e.hd;
+  if (e.hd % FBN || K % FCH || lda % 4) return hipErrorInvalidValue;
+  if (f32_large(N, rows_cap))
+    k_gemm_qkv_f32<2, 2, 4><<<dim3(N / FBN, cdiv(rows_cap, 64)), 512, 0, st>>>((const float*)A, lda, (const float*)W,
+                                                                               K, M_dev, e, inv_freq);
+  else
+    k_gemm_qkv_f32<1, 1, 8><<<dim3(N / FBN, cdiv(rows_cap, 16)), 512, 0, st>>>((const float*)A, lda, (const float*)W,
+                                                                               K, M_dev, e, inv_freq);
   return hipGetLastError();
 }
 
@@ -1114,10 +1204,10 @@ hipError_t launch_lm_head(bool is_bf16, const void* A, int d, size_t a_plane, co
     }
 #undef BD_HEAD
   } else {
-    if (V % SBN || d % SBK) return hipErrorInvalidValue;
-    ntiles = V / SBN;
-    dim3 grid(ntiles, cdiv(rows_cap, SBM));
-    k_lm_head_f32<<<grid, 256, 0, st>>>((const float*)A, d, (const float*)W, mask_id, scale, M_dev,
+    if (V % FHN || d % FCH) return hipErrorInvalidValue;
+    ntiles = V / FHN;
+    dim3 grid(ntiles, cdiv(rows_cap, 16));
+    k_lm_head_f32<<<grid, 512, 0, st>>>((const float*)A, d, (const float*)W, mask_id, scale, M_dev,
                                        rows_cap, part_max, part_sum, part_arg, V, so);
   }
   k_lm_merge<<<cdiv(rows_cap, 4), 256, 0, st>>>(part_max, part_sum, part_arg, ntiles, M_dev, rows_cap,

@@ -115,7 +115,7 @@ constexpr int MX_BLOCK = 32;
 // C[M][N] (+)= A[M][K] . W[N][K]^T with M read from *M_dev; grid covers rows_cap.
 // bf16 models: A is a bf16 plane pair (hi at A, lo at A + a_plane elements),
 // W bf16.  fp32 models: A and W fp32 (a_plane unused).
-//   EPI_STORE_F32 / EPI_ADD_F32: out fp32 [M][ldo]
+//   EPI_ADD_F32: added into out fp32 [M][ldo]
 //   EPI_SWIGLU: silu(gate) * up [M][ldo] (W packed gate/up in 16-row groups),
 //   as a bf16 plane pair (out_plane) for bf16 models, fp32 otherwise
 // wq (bf16 models only): the weight format (WQuant); ldw is W's row stride in
@@ -298,10 +298,6 @@ hipError_t launch_embed(bool is_bf16, const int32_t* tokens, int tok_stride, con
 hipError_t launch_rmsnorm(bool is_bf16, float* X, const float* g, int d, float eps,
                           const int32_t* M_dev, const int32_t* gather, int rows_cap, void* out,
                           size_t out_plane, const ResidSplit& fold, hipStream_t st);
-// fp32 models: RoPE of q and k at the rows' absolute positions; q ->
-// Q[row][head][hd], k and v -> the cache (layout of KvView, fp32).
-hipError_t launch_rope_kv(const float* QKV, PlanView plan, int rows_cap, int H, int Hkv, int hd,
-                          const double* inv_freq, float* Q, const KvView& kv, hipStream_t st);
 
 constexpr int BD_NSTATS = 12;
 
@@ -375,6 +371,10 @@ struct QkvEpi {
 hipError_t launch_gemm_qkv(const void* A, int lda, size_t a_plane, const void* W, int K,
                            const int32_t* M_dev, int rows_cap, const QkvEpi& e, hipStream_t st,
                            WQuant wq = WQuant{});
+// The same for fp32 models, with the caller's weight as it is (rope, q_plane
+// and rows4 unused; angles from inv_freq [hd/2]).
+hipError_t launch_gemm_qkv_f32(const void* A, int lda, const void* W, int K, const int32_t* M_dev, int rows_cap,
+                               const QkvEpi& e, const double* inv_freq, hipStream_t st);
 // Copy of a [(H + 2 Hkv) hd][d] QKV weight with the q and k head rows
 // pair-interleaved (see QkvEpi); v rows unchanged.
 hipError_t launch_permute_qk_rows(const void* W, void* out, int H, int Hkv, int hd, size_t row_bytes,

@@ -1,5 +1,4 @@
-// Row-wise kernels of the denoising step (embedding gather, RMSNorm, RoPE with
-// the K/V cache write) and the decode-state kernels (commit/compaction and
+// Row-wise kernels of the denoising step (embedding gather, RMSNorm) and the decode-state kernels (commit/compaction and
 // state initialisation).
 #include "bd_internal.h"
 
@@ -242,48 +241,6 @@ hipError_t launch_rmsnorm(bool is_bf16, float* X, const float* g, int d, float e
     k_rmsnorm<true><<<blocks, 256, 0, st>>>(X, g, d, eps, M_dev, gather, out, out_plane, fold);
   else
     k_rmsnorm<false><<<blocks, 256, 0, st>>>(X, g, d, eps, M_dev, gather, out, 0, fold);
-  return hipGetLastError();
-}
-
-// ------------------------------------------------------------------ RoPE + KV
-// fp32 models: rotate-half RoPE of q and k at the row's absolute position
-// (angle and rotation in fp64, one rounding to fp32); q -> Q[row][head][hd],
-// k and v -> the layer's cache slots [seq][kv head][pos][hd].  (bf16 models
-// do this in the QKV GEMM epilogue.)
-__global__ __launch_bounds__(256) void k_rope_kv(const float* __restrict__ QKV,
-                                                 const int32_t* __restrict__ hdr,
-                                                 const int32_t* __restrict__ row_seq,
-                                                 const int32_t* __restrict__ row_pos, int H, int Hkv,
-                                                 int hd, const double* __restrict__ inv_freq,
-                                                 float* __restrict__ Q, KvView kv) {
-  const int r = blockIdx.x;
-  if (r >= hdr[0]) return;
-  const int s = row_seq[r], pos = row_pos[r];
-  const int half = hd / 2, qkv = (H + 2 * Hkv) * hd;
-  const float* src = QKV + (size_t)r * qkv;
-  float* K = (float*)kv.K;
-  float* V = (float*)kv.V;
-  for (int idx = threadIdx.x; idx < (H + Hkv) * half; idx += blockDim.x) {
-    const int head = idx / half, i = idx % half;
-    double sn, cs;
-    sincos((double)pos * inv_freq[i], &sn, &cs);
-    const double x1 = src[head * hd + i], x2 = src[head * hd + i + half];
-    const float y1 = (float)(x1 * cs - x2 * sn), y2 = (float)(x2 * cs + x1 * sn);
-    float* o = (head < H) ? Q + ((size_t)r * H + head) * hd
-                          : K + (((size_t)s * Hkv + (head - H)) * kv.maxpos + pos) * hd;
-    o[i] = y1;
-    o[i + half] = y2;
-  }
-  for (int idx = threadIdx.x; idx < Hkv * hd; idx += blockDim.x) {
-    const int kh = idx / hd, e = idx % hd;
-    V[(((size_t)s * Hkv + kh) * kv.maxpos + pos) * hd + e] = src[(H + Hkv) * hd + idx];
-  }
-}
-
-hipError_t launch_rope_kv(const float* QKV, PlanView plan, int rows_cap, int H, int Hkv, int hd,
-                          const double* inv_freq, float* Q, const KvView& kv, hipStream_t st) {
-  k_rope_kv<<<rows_cap, 256, 0, st>>>(QKV, plan.hdr, plan.row_seq, plan.row_pos, H, Hkv, hd, inv_freq,
-                                      Q, kv);
   return hipGetLastError();
 }
 
@@ -827,7 +784,7 @@ hipError_t launch_permute_qk_rows(const void* W, void* out, int H, int Hkv, int 
 }
 
 // cos/sin of pos * inv_freq[i] in fp64 (the angle and its sine and cosine
-// computed as in k_rope_kv).
+// computed as in the fp32 QKV epilogue).
 __global__ void k_rope_table(const double* __restrict__ inv_freq, int half, int maxpos,
                              double* __restrict__ tab) {
   const int pos = blockIdx.x;
