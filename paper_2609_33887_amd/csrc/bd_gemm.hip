@@ -57,26 +57,29 @@ __device__ __forceinline__ void store_pair(bf16_t* p, size_t plane, float x) {
 // operand 16 significant bits, so that the only activation roundings of the
 // forward are the Q/K/V values stored in the KV cache.
 //
-// Main loop: K advances in stages of SK = 32 through a ring of four LDS
-// stages filled by direct buffer-to-LDS 16-byte loads (no register staging,
-// no LDS store instructions); three stages are in flight while the fourth is
-// consumed, and one barrier per stage both publishes the stage and retires
-// the one the next loads overwrite.  The bf16 operands go through buffer
-// resources rather than global (flat) addresses: the compiler counts a flat
-// load into LDS as pending LDS traffic too, which turned every LDS wait of
-// the loop into a full drain; with buffer loads the waits count the
-// fragment reads down, and the 32-bit lane offsets replace 64-bit address
-// arithmetic (130 instead of 152 VGPRs in the 128x256 tile).  A wave's load
-// instruction writes 1 KiB of LDS = 16 rows x 64 B, lane l at byte 16 l; in
-// LDS the 16-byte chunk c of row r sits at position c ^ swz(r),
-// swz(r) = (r >> 1) & 3.  A fragment read (lane l: row l & 15, chunk l >> 4)
-// is then free of bank conflicts: measured with
-// the LDS bank-conflict counter on gfx950, this pattern reads 141 B/clk per CU
-// with no conflict cycles, where the earlier (r >> 1) & 3 ^ (r >> 3) & 1 had
-// two-way conflicts (106 B/clk) and unswizzled rows 114 B/clk.
-constexpr int SK = 32;       // K per pipeline stage (KALIGN = 4 stages)
-
-__device__ __forceinline__ int swz(int r) { return (r >> 1) & 3; }
+// Main loop: K advances in stages of SK through a ring of NS LDS stages filled
+// by direct buffer-to-LDS loads (no register staging, no LDS store
+// instructions); NS - 1 stages are in flight while one is consumed, and one
+// barrier per stage both publishes the stage and retires the one the next
+// loads overwrite.  The operands go through buffer resources rather than
+// global (flat) addresses: the compiler counts a flat load into LDS as pending
+// LDS traffic too, which turned every LDS wait of the loop into a full drain.
+//
+// A tile is shared by WM x WN waves, or by KG such groups, each taking its own
+// part of every stage's depth for the whole tile: two waves a SIMD then cost
+// no more LDS reads per product than one (a wave's tile stays 64 x 64), and a
+// stage can be 64 deep, which halves the barriers.  The groups' sums meet in
+// LDS once, at the end.  Measured (us, two groups over 64-deep stages against
+// one over 32-deep ones): 512 x 16384 x 2048 76 / 85, 512 x 2048 x 8192 in 4
+// splits 30 / 34, 1024 x 2048 x 8192 in 2 splits 54 / 63, 3072 x 3072 x 2048
+// 77 / 90, 512 x 3072 x 2048 in 64 x 128 tiles 17.2 / 18.7 and 64 x 64 tiles
+// (one group, 64 deep) 19.3 / 24.8.
+//
+// LDS: rows of 2 SK bytes, the 16-byte chunk c of row r at position c ^ swz(r);
+// swz(r) = r & 7 for rows of 128 bytes and (r >> 1) & 3 for rows of 64: the 8
+// lanes that one LDS cycle serves (8 rows, one chunk) then meet 8 distinct
+// 16-byte columns (measured: no conflict cycles).
+__device__ __forceinline__ int swz(int row_bytes, int r) { return row_bytes == 128 ? (r & 7) : ((r >> 1) & 3); }
 
 typedef __attribute__((address_space(3))) void lds_void_t;
 
@@ -84,30 +87,15 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 // format (a zero format reads zeros), no index stride, no swizzle.
 constexpr int BUF_DWORD3 = 0x00020000;
 
-template <int BM, int BN, int WQ = WQ_NONE>
-struct GemmStage {
-  bf16_t ah[BM * SK];
-  bf16_t al[BM * SK];
-  // bf16 rows of 64 B, fp8 rows of 32 B, or E2M1 rows of 16 B
-  bf16_t b[WQ == WQ_NONE ? BN * SK : (WQ == WQ_FP8 ? BN * SK / 2 : BN * SK / 4)];
-  uint8_t be[WQ == WQ_MXFP4 ? BN : 0];    // the MXFP4 rows' block exponents
-};
-
-// fp8 W loads per wave and stage: BN = 128 -> one 16-byte load per lane
-// (32 rows of 32 B per wave); BN = 64 -> two 4-byte loads (8 rows each).
-template <int BN>
-struct W8Load {
-  static constexpr int bytes = BN == 128 ? 16 : 4;
-  static constexpr int loads = BN * SK / (4 * 64 * bytes);
-  static constexpr int rows = 64 * bytes / SK;      // rows per load instruction
-};
-
-// MXFP4 W loads per wave and stage: BN rows x 16 B of codes as 4-byte loads
-// (16 rows per load instruction), plus one 4-byte load of BN / 4 exponents.
-template <int BN>
-struct W4Load {
-  static constexpr int loads = BN * 16 / (4 * 64 * 4);
-};
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* p) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, -1, BUF_DWORD3);
+}
+__device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t r, void* lds, uint32_t off, uint32_t soff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)lds, 16, off, soff, 0, 0);
+}
+__device__ __forceinline__ void load_lds4(__amdgpu_buffer_rsrc_t r, void* lds, uint32_t off, uint32_t soff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)lds, 4, off, soff, 0, 0);
+}
 
 // Eight E2M1 codes (nibbles of v, k order, low nibble first) times the block
 // scale -> eight bf16 (exact).
@@ -136,13 +124,6 @@ __device__ __forceinline__ bf16x8 fp8x8_to_bf16(uint2 v) {
   return o;
 }
 
-// NW waves per workgroup in a 2 x (NW / 2) arrangement: each wave owns
-// (BM / 2) x (2 BN / NW) of the tile.
-template <int BM, int BN, int NW = 4>
-struct MfmaTile {
-  floatx4 acc[BM / 32][BN / (8 * NW)];
-};
-
 // s_waitcnt vmcnt(N) lgkmcnt(0) (gfx9 encoding): before a stage barrier the
 // wave's global->LDS loads but the N youngest have landed and all of its LDS
 // reads have returned, so that no wave overwrites a stage another still
@@ -153,251 +134,340 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (0 << 8));
 }
 
-// Per-thread sources of one tile's loads: the lane's 16-byte chunk of its A
-// rows (hi and lo planes) and W rows, as byte offsets into buffer resources
-// for A and bf16 W, as pointers for quantized W.
-template <int BM, int BN, int WQ = WQ_NONE, int NW = 4>
-struct TileSrc {
-  // A planes and bf16 W through buffer resources (the range check off): the
-  // lane's byte offset from the resource base; the stage adds 2 k bytes
-  __amdgpu_buffer_rsrc_t ra_h, ra_l, rw;
-  uint32_t a[BM / (16 * NW)];
-  uint32_t w[WQ == WQ_NONE ? BN / (16 * NW) : 1];
-  const uint8_t* w8[WQ == WQ_FP8 ? W8Load<BN>::loads : 1];
-  const uint8_t* w4[WQ == WQ_MXFP4 ? W4Load<BN>::loads : 1];
-  const uint8_t* we;        // MXFP4: this lane's 4 exponents of the first stage
-  size_t kstep;             // MXFP4: rows per stage block (codes advance 16 bytes a row)
+// One stage.  W rows: bf16 (2 SK bytes, swizzled), fp8 codes (SK bytes,
+// swizzled), or E2M1 codes as [SK / 32][BN][16 bytes] with the blocks'
+// exponents [SK / 32][BN].
+template <int BM, int BN, int SK, int WQ>
+struct GemmStage {
+  bf16_t a[2][BM * SK];
+  uint8_t b[WQ == WQ_NONE ? BN * SK * 2 : (WQ == WQ_FP8 ? BN * SK : BN * SK / 2)];
+  uint8_t be[WQ == WQ_MXFP4 ? BN * SK / MX_BLOCK : 0];
 };
 
-template <int BM, int BN, int WQ, int NW = 4>
-__device__ __forceinline__ void stage_issue(const TileSrc<BM, BN, WQ, NW>& src, size_t a_plane, int k,
-                                            GemmStage<BM, BN, WQ>& s, int wave) {
-  static_assert(WQ == WQ_NONE || NW == 4, "quantized weights take four waves");
-#pragma unroll
-  for (int i = 0; i < BM / (16 * NW); ++i) {
-    const int r = (i * NW + wave) * 16;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(src.ra_h, (lds_void_t*)(s.ah + r * SK), 16, src.a[i], 2 * k, 0, 0);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(src.ra_l, (lds_void_t*)(s.al + r * SK), 16, src.a[i], 2 * k, 0, 0);
+// The ring's stages are separate LDS objects (declared by the kernel, see
+// BD_GEMM_SMEM) so that the compiler can tell the loads into one stage from
+// the reads of another; those past NS are never touched and take no space.
+template <class St>
+struct GemmRing {
+  St &s0, &s1, &s2, &s3;
+  template <int I>
+  __device__ __forceinline__ St& at() const {
+    if constexpr (I == 0) return s0;
+    else if constexpr (I == 1) return s1;
+    else if constexpr (I == 2) return s2;
+    else return s3;
   }
-  if constexpr (WQ == WQ_FP8) {
-    typedef W8Load<BN> L;
-    uint8_t* b8 = (uint8_t*)s.b;
-#pragma unroll
-    for (int i = 0; i < L::loads; ++i) {
-      const int r = (wave * L::loads + i) * L::rows;
-      __builtin_amdgcn_global_load_lds((const void*)(src.w8[i] + k), (lds_void_t*)(b8 + r * SK), L::bytes, 0, 0);
-    }
-  } else if constexpr (WQ == WQ_MXFP4) {
-    // stage k is block k / SK: codes advance kstep rows of 16 bytes a block,
-    // exponents kstep bytes; wave w fills 256-byte runs (16 rows) of codes and
-    // exponent bytes [w BN / 4, (w + 1) BN / 4) with its first BN / 16 lanes
-    typedef W4Load<BN> L;
-    const size_t kb = (size_t)(k / SK);
-    uint8_t* b4 = (uint8_t*)s.b;
-#pragma unroll
-    for (int i = 0; i < L::loads; ++i)
-      __builtin_amdgcn_global_load_lds((const void*)(src.w4[i] + kb * src.kstep * 16),
-                                       (lds_void_t*)(b4 + (wave * L::loads + i) * 256), 4, 0, 0);
-    if ((threadIdx.x & 63) < BN / 16)
-      __builtin_amdgcn_global_load_lds((const void*)(src.we + kb * src.kstep), (lds_void_t*)(s.be + wave * (BN / 4)),
-                                       4, 0, 0);
-  } else {
-#pragma unroll
-    for (int i = 0; i < BN / (16 * NW); ++i) {
-      const int r = (i * NW + wave) * 16;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(src.rw, (lds_void_t*)(s.b + r * SK), 16, src.w[i], 2 * k, 0, 0);
-    }
-  }
-}
+};
+#define BD_GEMM_SMEM(G)                                                     \
+  __shared__ __attribute__((aligned(1024))) typename G::Stage gs0, gs1, gs2, gs3; \
+  const typename G::Ring ring{gs0, gs1, gs2, gs3}
 
-// One stage of MFMAs: NW waves in a 2 x (NW/2) arrangement, each
-// accumulating a (BM/2) x (2BN/NW) sub-tile of MFMA 16x16x32 tiles.
-template <int BM, int BN, int WQ, int NW = 4>
-__device__ __forceinline__ void stage_mfma(const GemmStage<BM, BN, WQ>& s, MfmaTile<BM, BN, NW>& t, int wave) {
-  constexpr int FM = BM / 32, FN = BN / (8 * NW), WCOL = 2 * BN / NW;
-  const int lane = threadIdx.x & 63;
-  const int wm = wave / (NW / 2), wn = wave % (NW / 2);
-  const int r16 = lane & 15;
-  const int pos = ((lane >> 4) ^ swz(r16)) * 8;   // fragment rows are r16 + 16 j
-  u32x4 bfr[FN];
-  if constexpr (WQ == WQ_FP8) {
-    // fp8 rows of 32 B, unswizzled: a fragment's 16 rows are 512 contiguous bytes
-    const uint8_t* b8 = (const uint8_t*)s.b;
+template <int BM_, int BN_, int WM, int WN, int KG_, int SK_, int NS, int WQ_>
+struct Gemm {
+  static constexpr int BM = BM_, BN = BN_, KG = KG_, SK = SK_, WQ = WQ_;
+  static constexpr int NW = WM * WN * KG, NT = 64 * NW;
+  static constexpr int WROWS = BM / WM, WCOLS = BN / WN;          // a wave's part of the tile
+  static constexpr int FM = WROWS / 16, FN = WCOLS / 16;
+  static constexpr int KS = SK / 32 / KG;                         // MFMA depths per wave and stage
+  static constexpr int ARB = SK * 2;                              // bytes of an A row in LDS
+  static constexpr int ARPI = 1024 / ARB;                         // rows per 1 KiB load instruction
+  static constexpr int LA = BM / (ARPI * NW);
+  // W load instructions per wave and stage, and their bytes per lane
+  static constexpr int WB = WQ == WQ_NONE ? BN * SK * 2 : (WQ == WQ_FP8 ? BN * SK : BN * SK / 2);
+  static constexpr int WLB = WQ != WQ_MXFP4 && WB >= 1024 * NW ? 16 : 4;
+  static constexpr int LB = WB / (64 * WLB * NW);
+  static constexpr int EXPB = WQ == WQ_MXFP4 ? BN * SK / MX_BLOCK / NW : 0;   // exponent bytes per wave
+  static constexpr int LPS = 2 * LA + LB + (WQ == WQ_MXFP4 ? 1 : 0);          // load instructions per stage
+  static_assert(LA >= 1 && LB >= 1 && LA * ARPI * NW == BM && LB * 64 * WLB * NW == WB, "whole loads per wave");
+  static_assert(KS >= 1 && (WQ == WQ_NONE || (SK == 64 && KG == 2)), "quantized weights: two groups, 64 deep");
+  static_assert(NS >= 2 && NS <= 4 && (KALIGN / SK) % 2 == 0, "ring");
+  typedef GemmStage<BM, BN, SK, WQ> Stage;
+  typedef GemmRing<Stage> Ring;
+  // output tile in LDS (see to_lds): half of the rows in each of two stages
+  static constexpr int LD = BN + 4;
+  static constexpr bool TILE_FITS = sizeof(Stage) >= sizeof(float) * (BM / 2) * LD;
+
+  floatx4 acc[FM][FN];
+  __amdgpu_buffer_rsrc_t rah, ral, rw, re;
+  uint32_t ao[LA], wo[LB], eo;
+  uint32_t wstep, estep;         // W (and exponent) bytes per stage
+  int lane, wave, wm, wn, kg;
+
+  // 16-byte chunk of an A row for group g of the lanes at MFMA depth q: the
+  // depths are permuted alike on both sides; fp8 rows are read 16 codes at a
+  // time, of which group kg takes 8
+  __device__ __forceinline__ int achunk(int q, int g) const {
+    return WQ == WQ_FP8 ? 2 * g + kg : (kg * KS + q) * 4 + g;
+  }
+
+  __device__ __forceinline__ void issue(Stage& s, int kt) {
+    const uint32_t ka = (uint32_t)kt * ARB;
+#pragma unroll
+    for (int i = 0; i < LA; ++i) {
+      const int r = (i * NW + wave) * ARPI;
+      load_lds16(rah, s.a[0] + r * SK, ao[i], ka);
+      load_lds16(ral, s.a[1] + r * SK, ao[i], ka);
+    }
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {
+      uint8_t* d = s.b + (i * NW + wave) * (64 * WLB);
+      if constexpr (WLB == 16) load_lds16(rw, d, wo[i], (uint32_t)kt * wstep);
+      else load_lds4(rw, d, wo[i], (uint32_t)kt * wstep);
+    }
+    if constexpr (WQ == WQ_MXFP4)
+      if (lane < EXPB / 4) load_lds4(re, s.be + wave * EXPB, eo, (uint32_t)kt * estep);
+  }
+
+  __device__ __forceinline__ void mfma(const Stage& s) {
+    const int r16 = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int q = 0; q < KS; ++q) {
+      const int pos = (achunk(q, g) ^ swz(ARB, r16)) * 8;
+      u32x4 b[FN];
+#pragma unroll
+      for (int j = 0; j < FN; ++j) {
+        const int row = wn * WCOLS + j * 16 + r16;
+        if constexpr (WQ == WQ_FP8) {
+          const uint2 raw = *(const uint2*)(s.b + row * SK + ((g ^ swz(SK, r16)) * 16) + kg * 8);
+          b[j] = __builtin_bit_cast(u32x4, fp8x8_to_bf16(raw));
+        } else if constexpr (WQ == WQ_MXFP4) {
+          // 2^(e - 127) (e >= 1; e = 0 only in all-zero blocks, whose codes are zero)
+          const uint32_t raw = *(const uint32_t*)(s.b + (kg * BN + row) * 16 + g * 4);
+          b[j] = __builtin_bit_cast(u32x4, fp4x8_to_bf16(raw, __uint_as_float((uint32_t)s.be[kg * BN + row] << 23)));
+        } else {
+          b[j] = *(const u32x4*)((const bf16_t*)s.b + row * SK + pos);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < FM; ++i) {
+        const int row = wm * WROWS + i * 16 + r16;
+        const bf16x8 ah = __builtin_bit_cast(bf16x8, *(const u32x4*)(s.a[0] + row * SK + pos));
+        const bf16x8 al = __builtin_bit_cast(bf16x8, *(const u32x4*)(s.a[1] + row * SK + pos));
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, __builtin_bit_cast(bf16x8, b[j]), acc[i][j], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, __builtin_bit_cast(bf16x8, b[j]), acc[i][j], 0, 0, 0);
+      }
+    }
+  }
+
+  // steady state, stages t .. t + NS - 1: own loads of the stage done (the
+  // younger ones may still be in flight), barrier (everyone's loads done,
+  // everyone past the stage before), refill that one, compute
+  template <int I>
+  __device__ __forceinline__ void group(const Ring& rg, int t) {
+    if constexpr (I < NS) {
+      wait_vmcnt<(NS - 2) * LPS>();
+      __builtin_amdgcn_s_barrier();
+      issue(rg.template at<(I + NS - 1) % NS>(), t + I + NS - 1);
+      mfma(rg.template at<I>());
+      group<I + 1>(rg, t);
+    }
+  }
+  // the last REM stages, of which NS - 1 (or all, if fewer) are in flight
+  template <int I, int REM>
+  __device__ __forceinline__ void tail(const Ring& rg, int t) {
+    if constexpr (I < REM) {
+      constexpr int LEFT = REM - 1 - I;
+      wait_vmcnt<(LEFT < NS - 2 ? LEFT : NS - 2) * LPS>();
+      __builtin_amdgcn_s_barrier();
+      if constexpr (I + NS - 1 < REM) issue(rg.template at<(I + NS - 1) % NS>(), t + I + NS - 1);
+      mfma(rg.template at<I % NS>());
+      tail<I + 1, REM>(rg, t);
+    }
+  }
+
+  // K range [k0, k0 + klen), klen a positive multiple of KALIGN (so the stage
+  // count is even, and a multiple of 4 for SK 32).  The A rows are m0 + r, or
+  // gathered through arows (rows past nvalid repeat the first listed one; their
+  // results are discarded by the caller).  Weights: bf16 or fp8 rows of stride
+  // ldw, or (MXFP4) the stage-major blocks of ldw rows with the exponents wexp.
+  // Resources start at the tile's first row (gathered rows: at row 0, so a
+  // plane's rows x lda x 2 bytes must stay below 4 GiB, checked on the host).
+  __device__ __forceinline__ void run(const Ring& rg, const bf16_t* __restrict__ A, int lda, size_t a_plane,
+                                      const void* __restrict__ Wv, int ldw, const uint8_t* __restrict__ wexp, int k0,
+                                      int klen, int m0, int n0, const int32_t* __restrict__ arows = nullptr,
+                                      int nvalid = 0) {
+    lane = threadIdx.x & 63;
+    wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    wn = wave % WN; wm = (wave / WN) % WM; kg = wave / (WN * WM);
+    m0 = __builtin_amdgcn_readfirstlane(m0);
+    n0 = __builtin_amdgcn_readfirstlane(n0);
+    k0 = __builtin_amdgcn_readfirstlane(k0);
+    const bf16_t* ab = A + (arows ? (size_t)0 : (size_t)m0 * lda) + k0;
+    rah = buf_rsrc(ab);
+    ral = buf_rsrc(ab + a_plane);
+    const int ars = lane / (ARB / 16);                            // row of the lane within a load
+#pragma unroll
+    for (int i = 0; i < LA; ++i) {
+      const int r = (i * NW + wave) * ARPI + ars;
+      const int row = arows ? arows[r < nvalid ? r : 0] : r;
+      ao[i] = ((uint32_t)row * (uint32_t)lda + ((lane % (ARB / 16)) ^ swz(ARB, r)) * 8) * 2u;
+    }
+    if constexpr (WQ == WQ_MXFP4) {
+      const size_t kb0 = (size_t)(k0 / MX_BLOCK);
+      rw = buf_rsrc((const uint8_t*)Wv + (kb0 * ldw + n0) * 16);
+      re = buf_rsrc(wexp + kb0 * ldw + n0);
+      wstep = (uint32_t)ldw * (16 * SK / MX_BLOCK);
+      estep = (uint32_t)ldw * (SK / MX_BLOCK);
+#pragma unroll
+      for (int i = 0; i < LB; ++i) {
+        const int by = (i * NW + wave) * 256 + lane * 4;          // byte in [blocks][BN][16]
+        wo[i] = (uint32_t)(by / (BN * 16)) * (uint32_t)ldw * 16u + by % (BN * 16);
+      }
+      const int eb = wave * EXPB + (lane < EXPB / 4 ? lane : 0) * 4;
+      eo = (uint32_t)(eb / BN) * (uint32_t)ldw + eb % BN;
+    } else {
+      constexpr int WRB = WQ == WQ_FP8 ? SK : SK * 2, ES = WQ == WQ_FP8 ? 1 : 2;
+      rw = buf_rsrc((const uint8_t*)Wv + ((size_t)n0 * ldw + k0) * ES);
+      wstep = WRB;
+#pragma unroll
+      for (int i = 0; i < LB; ++i) {
+        const int by = (i * NW + wave) * (64 * WLB) + lane * WLB, r = by / WRB, in = by % WRB;
+        wo[i] = (uint32_t)r * (uint32_t)ldw * ES + ((in >> 4) ^ swz(WRB, r)) * 16 + (in & 15);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    const int nk = __builtin_amdgcn_readfirstlane(klen / SK);
+    // no scalar load left in flight: the loop's LDS waits can then count the
+    // fragment reads down instead of draining them
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    issue(rg.template at<0>(), 0);
+    if constexpr (NS > 2) issue(rg.template at<1>(), 1);
+    if constexpr (NS > 3) if (SK == 32 || nk > 2) issue(rg.template at<2>(), 2);
+    int t = 0;
+    for (; t + 2 * NS - 1 <= nk; t += NS) group<0>(rg, t);
+    const int rem = nk - t;
+    if constexpr (NS == 2 || (NS == 4 && SK == 32)) {
+      tail<0, NS>(rg, t);                                         // nk is a multiple of NS
+    } else if constexpr (NS == 3) {
+      if (rem == 2) tail<0, 2>(rg, t);
+      else if (rem == 3) tail<0, 3>(rg, t);
+      else tail<0, 4>(rg, t);
+    } else {
+      if (rem == 2) tail<0, 2>(rg, t);
+      else if (rem == 4) tail<0, 4>(rg, t);
+      else tail<0, 6>(rg, t);
+    }
+  }
+
+  // fp8 weights: multiply each accumulator column n by the weight's row scale
+  // sc[n], a power of two
+  __device__ __forceinline__ void scale_columns(const float* __restrict__ sc, int n0) {
 #pragma unroll
     for (int j = 0; j < FN; ++j) {
-      const uint2 raw = *(const uint2*)(b8 + (wn * WCOL + j * 16 + r16) * SK + (lane >> 4) * 8);
-      bfr[j] = __builtin_bit_cast(u32x4, fp8x8_to_bf16(raw));
-    }
-  } else if constexpr (WQ == WQ_MXFP4) {
-    // E2M1 rows of 16 B: a fragment's 16 rows are 256 contiguous bytes; the
-    // lane's 8 codes are 4 bytes, scaled by 2^(e - 127) (e >= 1; e = 0 only
-    // in all-zero blocks, whose codes are zero)
-    const uint8_t* b4 = (const uint8_t*)s.b;
+      const float f = sc[n0 + wn * WCOLS + j * 16 + (lane & 15)];
 #pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      const int row = wn * WCOL + j * 16 + r16;
-      const uint32_t raw = *(const uint32_t*)(b4 + row * 16 + (lane >> 4) * 4);
-      const float sc = __uint_as_float((uint32_t)s.be[row] << 23);
-      bfr[j] = __builtin_bit_cast(u32x4, fp4x8_to_bf16(raw, sc));
-    }
-  } else {
+      for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int j = 0; j < FN; ++j) bfr[j] = *(const u32x4*)(&s.b[(wn * WCOL + j * 16 + r16) * SK + pos]);
+        for (int r = 0; r < 4; ++r) acc[i][j][r] *= f;
+    }
   }
+
+  // The output tile in LDS, fp32 rows of LD floats: rows [0, BM / 2) in stage
+  // 0, the rest in stage 1.  Two groups' sums are added on the way (first the
+  // second group's values are laid down, then the first group adds its own).
+  struct Tile {
+    float *p0, *p1;
+    __device__ __forceinline__ float* row(int r) const { return r < BM / 2 ? p0 + r * LD : p1 + (r - BM / 2) * LD; }
+  };
+  __device__ __forceinline__ Tile to_lds(const Ring& rg) {
+    static_assert(TILE_FITS && KG <= 2, "tile in LDS");
+    const Tile o{(float*)&rg.template at<0>(), (float*)&rg.template at<1>()};
+    __syncthreads();              // every wave is past its last stage
 #pragma unroll
-  for (int i = 0; i < FM; ++i) {
-    const int row = wm * (BM / 2) + i * 16 + r16;
-    const bf16x8 ah = __builtin_bit_cast(bf16x8, *(const u32x4*)(&s.ah[row * SK + pos]));
-    const bf16x8 al = __builtin_bit_cast(bf16x8, *(const u32x4*)(&s.al[row * SK + pos]));
+    for (int ph = KG - 1; ph >= 0; --ph) {
+      if (kg == ph) {
 #pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      const bf16x8 bj = __builtin_bit_cast(bf16x8, bfr[j]);
-      t.acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bj, t.acc[i][j], 0, 0, 0);
-      t.acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bj, t.acc[i][j], 0, 0, 0);
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            float* p = o.row(wm * WROWS + i * 16 + (lane >> 4) * 4 + r) + wn * WCOLS + (lane & 15);
+#pragma unroll
+            for (int j = 0; j < FN; ++j) p[j * 16] = ph == KG - 1 ? acc[i][j][r] : p[j * 16] + acc[i][j][r];
+          }
+      }
+      __syncthreads();
     }
+    return o;
+  }
+};
+
+// Tiles in use.  W and W2 (bf16 weights, windows of at least 2048 rows):
+// 128 x 256 with 8 waves and a four-stage ring, one workgroup a CU, or 4
+// waves and two stages, two workgroups a CU, which cover each other's waits and
+// epilogues where the grid has a few rounds of them.
+template <int WQ> using Tile128 = Gemm<128, 128, 2, 2, 2, 64, 3, WQ>;
+template <int WQ> using Tile64x128 = Gemm<64, 128, 2, 2, 2, 64, 4, WQ>;
+template <int WQ> using Tile64 = Gemm<64, 64, 2, 2, 2, 64, 3, WQ>;
+using TileW = Gemm<128, 256, 2, 4, 1, 32, 4, WQ_NONE>;
+using TileW2 = Gemm<128, 256, 2, 2, 1, 32, 2, WQ_NONE>;
+
+// Eight values as bf16 pairs: 16 bytes to each plane (p 16-byte aligned).
+__device__ __forceinline__ void store_pair8(bf16_t* p, size_t plane, const float v[8]) {
+  uint32_t h[4], l[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const bf16_t h0 = f2bf(v[2 * e]), h1 = f2bf(v[2 * e + 1]);
+    h[e] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+    l[e] = (uint32_t)f2bf(v[2 * e] - bf2f(h0)) | ((uint32_t)f2bf(v[2 * e + 1] - bf2f(h1)) << 16);
+  }
+  *(u32x4*)p = u32x4{h[0], h[1], h[2], h[3]};
+  *(u32x4*)(p + plane) = u32x4{l[0], l[1], l[2], l[3]};
+}
+
+__device__ __forceinline__ void store_pair4(bf16_t* p, size_t plane, const float v[4]) {
+  bf16_t h[4], l[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    h[e] = f2bf(v[e]);
+    l[e] = f2bf(v[e] - bf2f(h[e]));
+  }
+  *(uint2*)p = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
+  *(uint2*)(p + plane) =
+      make_uint2((uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16));
+}
+
+// SwiGLU of a packed gate/up tile (16 gate columns, then their 16 up columns)
+// in LDS: rows [0, rows) go to out rows of stride ldo from feature f0 on, 8
+// features a thread, one 16-byte store per plane.
+template <class G>
+__device__ __forceinline__ void swiglu_tile(const typename G::Tile& tl, int rows, bf16_t* __restrict__ out, int ldo,
+                                            size_t out_plane) {
+  constexpr int NO = G::BN / 16;             // 8-feature runs per row
+  for (int it = threadIdx.x; it < rows * NO; it += G::NT) {
+    const int r = it / NO, o = it % NO;
+    const float* x = tl.row(r) + (o >> 1) * 32 + (o & 1) * 8;
+    float y[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) y[k] = silu(x[k]) * x[16 + k];
+    store_pair8(out + (size_t)r * ldo + o * 8, out_plane, y);
   }
 }
 
-// Main loop of one group of 4 waves (wave = 0..3 within the group) over the
-// K range [k0, k0 + klen), klen a positive multiple of KALIGN.  The A rows
-// are m0 + r, or gathered through arows (rows past nvalid repeat the first
-// listed row; their results are discarded by the caller).  The four stages
-// are separate LDS objects so the compiler can tell the loads into one stage
-// from the reads of another.  All waves of the workgroup must run the same
-// number of stages (the barriers are workgroup-wide).
-// Weights: bf16 or fp8 rows of stride ldw, or (MXFP4) the stage-major block
-// of ldw rows per 32-deep stage with the exponents wexp.
-template <int BM, int BN, int WQ = WQ_NONE, int NW = 4>
-__device__ __forceinline__ void mfma_mainloop(const bf16_t* __restrict__ A, int lda, size_t a_plane,
-                                              const void* __restrict__ Wv, int ldw,
-                                              const uint8_t* __restrict__ wexp, int k0,
-                                              int klen, int m0, int n0, MfmaTile<BM, BN, NW>& t,
-                                              GemmStage<BM, BN, WQ>& s0, GemmStage<BM, BN, WQ>& s1,
-                                              GemmStage<BM, BN, WQ>& s2, GemmStage<BM, BN, WQ>& s3,
-                                              int wave, const int32_t* __restrict__ arows = nullptr,
-                                              int nvalid = 0) {
-  // load instructions per thread per stage
-  constexpr int LPS = 2 * (BM / (16 * NW)) +
-                      (WQ == WQ_FP8 ? W8Load<BN>::loads
-                                    : (WQ == WQ_MXFP4 ? W4Load<BN>::loads + 1 : BN / (16 * NW)));
-  const int lane = threadIdx.x & 63;
-  const int rsub = lane >> 2, chunk = (lane & 3) ^ swz(rsub);
-  TileSrc<BM, BN, WQ, NW> src;
-  // resources start at the tile's first row (gathered rows: at row 0, so a
-  // plane's rows x lda x 2 bytes must stay below 4 GiB, checked on the host)
-  const bf16_t* ab = A + (arows ? (size_t)0 : (size_t)m0 * lda) + k0;
-  src.ra_h = __builtin_amdgcn_make_buffer_rsrc((void*)ab, 0, -1, BUF_DWORD3);
-  src.ra_l = __builtin_amdgcn_make_buffer_rsrc((void*)(ab + a_plane), 0, -1, BUF_DWORD3);
-#pragma unroll
-  for (int i = 0; i < BM / (16 * NW); ++i) {
-    const int r = (i * NW + wave) * 16 + rsub;
-    const int grow = arows ? arows[r < nvalid ? r : 0] : r;
-    src.a[i] = ((uint32_t)grow * (uint32_t)lda + chunk * 8) * 2u;
-  }
-  if constexpr (WQ == WQ_FP8) {
-    typedef W8Load<BN> L;
-    const uint8_t* W = (const uint8_t*)Wv;
-    const int per_row = SK / L::bytes;       // lanes per 32-byte row
-#pragma unroll
-    for (int i = 0; i < L::loads; ++i) {
-      const int r = (wave * L::loads + i) * L::rows + lane / per_row;
-      src.w8[i] = W + (size_t)(n0 + r) * ldw + k0 + (lane % per_row) * L::bytes;
-    }
-  } else if constexpr (WQ == WQ_MXFP4) {
-    typedef W4Load<BN> L;
-    const size_t kb0 = (size_t)(k0 / SK);
-    const uint8_t* W = (const uint8_t*)Wv + (kb0 * ldw + n0) * 16;
-#pragma unroll
-    for (int i = 0; i < L::loads; ++i) src.w4[i] = W + (wave * L::loads + i) * 256 + lane * 4;
-    src.we = wexp + kb0 * ldw + n0 + wave * (BN / 4) + (lane < BN / 16 ? lane : 0) * 4;
-    src.kstep = (size_t)ldw;
-  } else {
-    src.rw = __builtin_amdgcn_make_buffer_rsrc((void*)((const bf16_t*)Wv + (size_t)n0 * ldw + k0), 0, -1, BUF_DWORD3);
-#pragma unroll
-    for (int i = 0; i < BN / (16 * NW); ++i)
-      src.w[i] = ((uint32_t)((i * NW + wave) * 16 + rsub) * (uint32_t)ldw + chunk * 8) * 2u;
-  }
-#pragma unroll
-  for (int i = 0; i < BM / 32; ++i)
-#pragma unroll
-    for (int j = 0; j < BN / (8 * NW); ++j) t.acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-  const int nk = klen / SK;     // multiple of 4, >= 4
-  // no scalar load left in flight: the loop's LDS waits can then count the
-  // fragment reads down instead of draining them
-  __builtin_amdgcn_s_waitcnt(0xC07F);
-  stage_issue<BM, BN, WQ, NW>(src, a_plane, 0, s0, wave);
-  stage_issue<BM, BN, WQ, NW>(src, a_plane, SK, s1, wave);
-  stage_issue<BM, BN, WQ, NW>(src, a_plane, 2 * SK, s2, wave);
-  int kt = 0;
-  // each step: own loads of stage kt done (the two younger stages may still
-  // be in flight), barrier (everyone's loads done, everyone past stage kt-1),
-  // refill the stage of kt-1 with kt+3, compute stage kt
-#define BD_GEMM_STEP(CUR, NXT, KNEXT)                            \
-  wait_vmcnt<2 * LPS>();                                         \
-  __builtin_amdgcn_s_barrier();                                  \
-  stage_issue<BM, BN, WQ, NW>(src, a_plane, (KNEXT) * SK, NXT, wave);    \
-  stage_mfma<BM, BN, WQ, NW>(CUR, t, wave);
-  for (; kt + 4 < nk; kt += 4) {
-    BD_GEMM_STEP(s0, s3, kt + 3)
-    BD_GEMM_STEP(s1, s0, kt + 4)
-    BD_GEMM_STEP(s2, s1, kt + 5)
-    BD_GEMM_STEP(s3, s2, kt + 6)
-  }
-#undef BD_GEMM_STEP
-  // the last four stages (kt + 3 == nk - 1)
-  wait_vmcnt<2 * LPS>();
-  __builtin_amdgcn_s_barrier();
-  stage_issue<BM, BN, WQ, NW>(src, a_plane, (kt + 3) * SK, s3, wave);
-  stage_mfma<BM, BN, WQ, NW>(s0, t, wave);
-  wait_vmcnt<2 * LPS>();
-  __builtin_amdgcn_s_barrier();
-  stage_mfma<BM, BN, WQ, NW>(s1, t, wave);
-  wait_vmcnt<LPS>();
-  __builtin_amdgcn_s_barrier();
-  stage_mfma<BM, BN, WQ, NW>(s2, t, wave);
-  wait_vmcnt<0>();
-  __builtin_amdgcn_s_barrier();
-  stage_mfma<BM, BN, WQ, NW>(s3, t, wave);
-}
-
-#define BD_GEMM_SMEM(BM, BN, WQ)                                                 \
-  __shared__ __attribute__((aligned(1024))) GemmStage<BM, BN, WQ> gs0, gs1, gs2, gs3
-
-// fp8 weights: multiply accumulator column n (of this wave's fragments) by
-// the row scale sc[n] of the weight, a power of two.
-template <int BM, int BN>
-__device__ __forceinline__ void scale_columns(MfmaTile<BM, BN>& t, const float* __restrict__ sc, int n0,
-                                              int wave) {
-  const int lane = threadIdx.x & 63, wn = wave & 1;
-#pragma unroll
-  for (int j = 0; j < BN / 32; ++j) {
-    const float f = sc[n0 + wn * (BN / 2) + j * 16 + (lane & 15)];
-#pragma unroll
-    for (int i = 0; i < BM / 32; ++i)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) t.acc[i][j][r] *= f;
-  }
-}
-
-// GEMM, epilogue applied in registers.  Items (split z, column tile x, row
-// tile y) are numbered z-major, then in bands of row tiles (band_tile): an
-// XCD's concurrent workgroups share the A slices of a few row tiles and the
-// W slices of a few column tiles of one split.  For
-// EPI_ADD_F32 with a split workspace, the kernel picks S = resid_splits(M)
-// K-splits on the device (zmax is the largest allowed); with S > 1 every
-// split stores its raw partial tile to ws[split][row][col] (rows padded to
-// whole tiles) and the next RMSNorm of the residual stream adds the partials
-// in split order.
-template <int BM, int BN, int EPI, int WQ, int NW = 4>
-__global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const bf16_t* __restrict__ A, int lda,
-                                                   size_t a_plane, const void* __restrict__ W,
-                                                   int ldw, int N, int K,
-                                                   const int32_t* __restrict__ Mp,
-                                                   void* __restrict__ out, int ldo, size_t out_plane,
-                                                   float* __restrict__ ws, int zmax,
-                                                   const void* __restrict__ waux) {
-  constexpr int FM = BM / 32, FN = BN / (8 * NW), WCOL = 2 * BN / NW;
+// GEMM.  Items (split z, column tile x, row tile y) are numbered z-major, then
+// in bands of row tiles (band_tile): an XCD's concurrent workgroups share the A
+// slices of a few row tiles and the W slices of a few column tiles of one
+// split.  For EPI_ADD_F32 with a split workspace, the kernel picks
+// S = resid_splits(M) K-splits on the device (zmax is the largest allowed);
+// with S > 1 every split stores its raw partial tile to ws[split][row][col]
+// (rows padded to whole tiles) and the next RMSNorm of the residual stream adds
+// the partials in split order.
+template <class G, int EPI>
+__global__ __launch_bounds__(G::NT) void k_gemm_bf16(const bf16_t* __restrict__ A, int lda,
+                                                     size_t a_plane, const void* __restrict__ W,
+                                                     int ldw, int N, int K,
+                                                     const int32_t* __restrict__ Mp,
+                                                     void* __restrict__ out, int ldo, size_t out_plane,
+                                                     float* __restrict__ ws, int zmax,
+                                                     const void* __restrict__ waux) {
+  constexpr int BM = G::BM, BN = G::BN, WQ = G::WQ;
   const int M = *Mp;
   const int X = N / BN, Y = (M + BM - 1) / BM;
   int S = 1;
@@ -414,36 +484,51 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const bf16_t* __restrict_
   band_tile(u % (X * Y), X, Y, BAND_R, tx, ty);
   const int m0 = ty * BM, n0 = tx * BN;
   const int klen = K / S;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  BD_GEMM_SMEM(BM, BN, WQ);
-  MfmaTile<BM, BN, NW> t;
-  mfma_mainloop<BM, BN, WQ, NW>(A, lda, a_plane, W, WQ == WQ_MXFP4 ? N : ldw, (const uint8_t*)waux,
-                                z * klen, klen, m0, n0, t, gs0, gs1, gs2, gs3, wave);
-  if constexpr (WQ == WQ_FP8) scale_columns<BM, BN>(t, (const float*)waux, n0, wave);
-  const int wm = wave / (NW / 2), wn = wave % (NW / 2);
-  float* wz = (EPI == EPI_ADD_F32 && S > 1) ? ws + (size_t)z * ((M + BM - 1) / BM) * BM * N
-                                            : nullptr;
-#pragma unroll
-  for (int i = 0; i < FM; ++i) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int m = m0 + wm * (BM / 2) + i * 16 + (lane >> 4) * 4 + r;
-      if (m >= M) continue;
-      if constexpr (EPI == EPI_SWIGLU) {
-#pragma unroll
-        for (int j = 0; j < FN; j += 2) {
-          const int pb = n0 + wn * WCOL + j * 16;        // packed column of the gate group
-          const int col = (pb >> 5) * 16 + (lane & 15);  // output feature
-          const float g = t.acc[i][j][r], u = t.acc[i][j + 1][r];
-          store_pair((bf16_t*)out + (size_t)m * ldo + col, out_plane, silu(g) * u);
+  BD_GEMM_SMEM(G);
+  G t;
+  t.run(ring, A, lda, a_plane, W, WQ == WQ_MXFP4 ? N : ldw, (const uint8_t*)waux, z * klen, klen, m0, n0);
+  if constexpr (WQ == WQ_FP8) t.scale_columns((const float*)waux, n0);
+  float* wz = (EPI == EPI_ADD_F32 && S > 1) ? ws + (size_t)z * Y * BM * N : nullptr;
+  if constexpr (G::TILE_FITS) {
+    const typename G::Tile tl = t.to_lds(ring);
+    const int rows = M - m0 < BM ? M - m0 : BM;
+    if constexpr (EPI == EPI_SWIGLU) {
+      swiglu_tile<G>(tl, rows, (bf16_t*)out + (size_t)m0 * ldo + (n0 >> 1), ldo, out_plane);
+    } else {
+      constexpr int NQ = BN / 4;
+      for (int it = threadIdx.x; it < rows * NQ; it += G::NT) {
+        const int r = it / NQ, c = (it % NQ) * 4;
+        const floatx4 v = *(const floatx4*)(tl.row(r) + c);
+        if (S > 1) {
+          *(floatx4*)(wz + (size_t)(m0 + r) * N + n0 + c) = v;
+        } else {
+          floatx4* o = (floatx4*)((float*)out + (size_t)(m0 + r) * ldo + n0 + c);
+          *o += v;
         }
-      } else {
+      }
+    }
+  } else {
+    // the wide tiles do not fit the ring: straight from the accumulators
 #pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          const int n = n0 + wn * WCOL + j * 16 + (lane & 15);
-          const float v = t.acc[i][j][r];
-          if (EPI == EPI_ADD_F32 && S > 1) wz[(size_t)m * N + n] = v;
-          else ((float*)out)[(size_t)m * ldo + n] += v;
+    for (int i = 0; i < G::FM; ++i) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = m0 + t.wm * G::WROWS + i * 16 + (t.lane >> 4) * 4 + r;
+        if (m >= M) continue;
+        if constexpr (EPI == EPI_SWIGLU) {
+#pragma unroll
+          for (int j = 0; j < G::FN; j += 2) {
+            const int pb = n0 + t.wn * G::WCOLS + j * 16;    // packed column of the gate group
+            const int col = (pb >> 5) * 16 + (t.lane & 15);  // output feature
+            store_pair((bf16_t*)out + (size_t)m * ldo + col, out_plane, silu(t.acc[i][j][r]) * t.acc[i][j + 1][r]);
+          }
+        } else {
+#pragma unroll
+          for (int j = 0; j < G::FN; ++j) {
+            const int n = n0 + t.wn * G::WCOLS + j * 16 + (t.lane & 15);
+            if (S > 1) wz[(size_t)m * N + n] = t.acc[i][j][r];
+            else ((float*)out)[(size_t)m * ldo + n] += t.acc[i][j][r];
+          }
         }
       }
     }
@@ -451,31 +536,21 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const bf16_t* __restrict_
 }
 
 // QKV projection with RoPE and the K/V cache write in the epilogue (bf16).
-// In the accumulator layout a lane holds rows mb + r (r < 4) of column n;
-// the pair-interleaved weight puts the rotation partner of column n in
-// column n ^ 1, i.e. lane ^ 1.  q and k: y(i) = x(i) cos - x(i + hd/2) sin,
-// y(i + hd/2) = x(i + hd/2) cos + x(i) sin in fp64 with one rounding to
-// fp32, stored at the original dimension; v: four consecutive rows of one
-// sequence are four consecutive positions of one V^T tile row (one 8-byte store
-// per plane).
-__device__ __forceinline__ void store_pair4(bf16_t* p, size_t plane, const float v[4]) {
-  bf16_t h[4], l[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    h[e] = f2bf(v[e]);
-    l[e] = f2bf(v[e] - bf2f(h[e]));
-  }
-  *(uint2*)p = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
-  *(uint2*)(p + plane) =
-      make_uint2((uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16));
-}
-
-template <int BM, int BN, int WQ, int NW = 4>
-__global__ __launch_bounds__(64 * NW) void k_gemm_qkv(const bf16_t* __restrict__ A, int lda,
-                                                  size_t a_plane, const void* __restrict__ W,
-                                                  int K, const int32_t* __restrict__ Mp, QkvEpi e,
-                                                  const void* __restrict__ waux) {
-  constexpr int FM = BM / 32, FN = BN / (8 * NW), WCOL = 2 * BN / NW;
+// The tile goes through LDS, so that every store is a 16-byte run of a plane
+// and every table read 128 bytes.  q and k: the pair-interleaved weight puts
+// both halves of a rotation in adjacent columns; a thread takes 8 pairs of a
+// row (16 columns): y(i) = x(i) cos - x(i + hd/2) sin, y(i + hd/2) =
+// x(i + hd/2) cos + x(i) sin in fp64 with one rounding to fp32, dims i .. i + 7
+// and i + hd/2 ..  v: a thread takes a column (dim) and the 8 rows of one slot
+// run of a 32-row group; where the group is 32 positions of one sequence from
+// a multiple of 32 on, they are one 16-byte store per plane, else 4-position
+// runs or single values.
+template <class G>
+__global__ __launch_bounds__(G::NT) void k_gemm_qkv(const bf16_t* __restrict__ A, int lda,
+                                                    size_t a_plane, const void* __restrict__ W,
+                                                    int K, const int32_t* __restrict__ Mp, QkvEpi e,
+                                                    const void* __restrict__ waux) {
+  constexpr int BM = G::BM, BN = G::BN, WQ = G::WQ;
   const int M = *Mp;
   const int X = (e.H + 2 * e.Hkv) * e.hd / BN, Y = (M + BM - 1) / BM;
   const int u = xcd_item(blockIdx.x, X * Y);
@@ -483,69 +558,74 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_qkv(const bf16_t* __restrict__
   int tx, ty;
   band_tile(u, X, Y, BAND_R, tx, ty);
   const int m0 = ty * BM, n0 = tx * BN;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  BD_GEMM_SMEM(BM, BN, WQ);
-  MfmaTile<BM, BN, NW> t;
-  mfma_mainloop<BM, BN, WQ, NW>(A, lda, a_plane, W, WQ == WQ_MXFP4 ? X * BN : K, (const uint8_t*)waux, 0, K,
-                                m0, n0, t, gs0, gs1, gs2, gs3, wave);
-  if constexpr (WQ == WQ_FP8) scale_columns<BM, BN>(t, (const float*)waux, n0, wave);
-  const int wm = wave / (NW / 2), wn = wave % (NW / 2);
+  BD_GEMM_SMEM(G);
+  G t;
+  t.run(ring, A, lda, a_plane, W, WQ == WQ_MXFP4 ? X * BN : K, (const uint8_t*)waux, 0, K, m0, n0);
+  if constexpr (WQ == WQ_FP8) t.scale_columns((const float*)waux, n0);
+  const typename G::Tile tl = t.to_lds(ring);
   const int hd = e.hd, half = hd >> 1;
   const int qcols = e.H * hd, qkcols = (e.H + e.Hkv) * hd;
+  const int rows = M - m0 < BM ? M - m0 : BM;
   bf16_t* Q = (bf16_t*)e.Q;
   bf16_t* Kc = (bf16_t*)e.kv.K;
   bf16_t* Vc = (bf16_t*)e.kv.V;
+  // columns [n0, n0 + nqk) of the tile belong to q and k heads, the rest to v
+  const int nqk = qkcols - n0 < 0 ? 0 : (qkcols - n0 < BN ? qkcols - n0 : BN);
+  const int cg = nqk >> 4;                                   // 16-column groups
+  for (int it = threadIdx.x; it < rows * cg; it += G::NT) {
+    const int r = it / cg, c0 = (it % cg) * 16, m = m0 + r, n = n0 + c0;
+    const int head = n / hd, i0 = (n % hd) >> 1;
+    const int seq = e.row_seq[m], pos = e.row_pos[m];
+    const double* cs = e.rope + ((size_t)pos * half + i0) * 2;
+    const float* x = tl.row(r) + c0;
+    float y1[8], y2[8];
 #pragma unroll
-  for (int i = 0; i < FM; ++i) {
-    const int mb = m0 + wm * (BM / 2) + i * 16 + (lane >> 4) * 4;   // the lane's first row
-    int seq[4], pos[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const bool ok = mb + r < M;
-      seq[r] = ok ? e.row_seq[mb + r] : 0;
-      pos[r] = ok ? e.row_pos[mb + r] : 0;
+    for (int k = 0; k < 8; ++k) {
+      const double x1 = x[2 * k], x2 = x[2 * k + 1], cc = cs[2 * k], sn = cs[2 * k + 1];
+      y1[k] = (float)(x1 * cc - x2 * sn);
+      y2[k] = (float)(x2 * cc + x1 * sn);
     }
+    const bool isq = n < qcols;
+    bf16_t* o = isq ? Q + ((size_t)m * e.H + head) * hd
+                    : Kc + (((size_t)seq * e.Hkv + (head - e.H)) * e.kv.maxpos + pos) * hd;
+    const size_t plane = isq ? e.q_plane : e.kv.k_plane;
+    store_pair8(o + i0, plane, y1);
+    store_pair8(o + half + i0, plane, y2);
+  }
+  const int nv = BN - nqk;                                   // v columns, from column nqk on
+  for (int it = threadIdx.x; it < nv * (BM / 8); it += G::NT) {
+    const int j = it & 3, c = nqk + (it >> 2) % nv, g0 = (it >> 2) / nv * 32;   // slot run j of rows g0 .. g0 + 31
+    if (g0 >= rows) continue;
+    const int vn = n0 + c - qkcols, kh = vn / hd, dim = vn % hd;
+    float v[8];
 #pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      const int n = n0 + wn * WCOL + j * 16 + (lane & 15);
-      float v[4], pv[4];
+    for (int k = 0; k < 8; ++k) v[k] = tl.row(g0 + (k >> 2) * 16 + 4 * j + (k & 3))[c];
+    const int m = m0 + g0;
+    bool run = g0 + 31 < rows;
+    if (run) {
+      const int p0 = e.row_pos[m];
+      run = p0 % 32 == 0 && e.row_pos[m + 31] == p0 + 31 && e.row_seq[m] == e.row_seq[m + 31];
+      if (run)
+        store_pair8(Vc + ((size_t)e.row_seq[m] * e.Hkv + kh) * hd * e.kv.vstride + vt_row(p0, dim, hd) + p0 % VTILE +
+                        8 * j,
+                    e.kv.v_plane, v);
+    }
+    if (run) continue;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        v[r] = t.acc[i][j][r];
-        pv[r] = __shfl_xor(v[r], 1);
-      }
-      // a 16-column fragment lies inside one head, so the branch is uniform
-      if (n < qkcols) {
-        const int cp = n % hd, ip = cp >> 1;
-        const bool odd = cp & 1;
-        const int dim = odd ? ip + half : ip;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          if (mb + r >= M) continue;
-          const double* cs = e.rope + ((size_t)pos[r] * half + ip) * 2;
-          const double x1 = odd ? (double)pv[r] : (double)v[r];
-          const double x2 = odd ? (double)v[r] : (double)pv[r];
-          const float y = odd ? (float)(x2 * cs[0] + x1 * cs[1]) : (float)(x1 * cs[0] - x2 * cs[1]);
-          if (n < qcols) {
-            store_pair(Q + ((size_t)(mb + r) * e.H + n / hd) * hd + dim, e.q_plane, y);
-          } else {
-            const int kh = (n - qcols) / hd;
-            store_pair(Kc + (((size_t)seq[r] * e.Hkv + kh) * e.kv.maxpos + pos[r]) * hd + dim,
-                       e.kv.k_plane, y);
-          }
-        }
+    for (int hf = 0; hf < 2; ++hf) {
+      const int r = g0 + hf * 16 + 4 * j;                    // 4 rows from r on
+      if (r >= rows) continue;
+      if (e.rows4 && r + 3 < rows) {
+        store_pair4(Vc + ((size_t)e.row_seq[m0 + r] * e.Hkv + kh) * hd * e.kv.vstride +
+                        vt_off(e.row_pos[m0 + r], dim, hd),
+                    e.kv.v_plane, v + 4 * hf);
       } else {
-        const int vn = n - qkcols, kh = vn / hd, dim = vn % hd;
-        if (e.rows4 && mb + 3 < M) {
-          store_pair4(Vc + ((size_t)seq[0] * e.Hkv + kh) * hd * e.kv.vstride + vt_off(pos[0], dim, hd),
-                      e.kv.v_plane, v);
-        } else {
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (mb + r < M)
-              store_pair(Vc + ((size_t)seq[r] * e.Hkv + kh) * hd * e.kv.vstride + vt_off(pos[r], dim, hd),
-                         e.kv.v_plane, v[r]);
-        }
+        for (int k = 0; k < 4; ++k)
+          if (r + k < rows)
+            store_pair(Vc + ((size_t)e.row_seq[m0 + r + k] * e.Hkv + kh) * hd * e.kv.vstride +
+                           vt_off(e.row_pos[m0 + r + k], dim, hd),
+                       e.kv.v_plane, v[4 * hf + k]);
       }
     }
   }
@@ -558,56 +638,43 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_qkv(const bf16_t* __restrict__
 // expert-sorted layout itself.  W of expert e starts e * w_stride weight
 // elements in (its codes, for quantized weights); fp8 row scales at
 // waux + e * N, MXFP4 exponents at waux + e * w_stride / 32.
-template <int EPI, int WQ, int NW = 4>
-__global__ __launch_bounds__(64 * NW) void k_gemm_grouped(const bf16_t* __restrict__ A, int lda,
-                                                      size_t a_plane, const void* __restrict__ W,
-                                                      int ldw, int K, GroupTiles g,
-                                                      void* __restrict__ out, int ldo,
-                                                      size_t out_plane,
-                                                      const void* __restrict__ waux, int N) {
-  constexpr int BM = 128, BN = 128, FM = BM / 32, FN = BN / (8 * NW), WCOL = 2 * BN / NW;
+template <class G, int EPI>
+__global__ __launch_bounds__(G::NT) void k_gemm_grouped(const bf16_t* __restrict__ A, int lda,
+                                                        size_t a_plane, const void* __restrict__ W,
+                                                        int ldw, int K, GroupTiles g,
+                                                        void* __restrict__ out, int ldo,
+                                                        size_t out_plane,
+                                                        const void* __restrict__ waux, int N) {
+  constexpr int BN = G::BN, WQ = G::WQ;
+  static_assert(G::BM == GROUP_BM, "expert row tiles");
   const int ti = blockIdx.y;
   if (ti >= *g.ntiles) return;
   const int e = g.tile_e[ti], m0 = g.tile_m0[ti];
   const int cnt = g.e_cnt[e], base = g.e_off[e];
   const int n0 = blockIdx.x * BN;
-  BD_GEMM_SMEM(BM, BN, WQ);
-  MfmaTile<BM, BN, NW> t;
+  BD_GEMM_SMEM(G);
+  G t;
   const size_t eoff = (size_t)e * g.w_stride;
   const void* We = WQ == WQ_NONE  ? (const void*)((const bf16_t*)W + eoff)
                    : WQ == WQ_FP8 ? (const void*)((const uint8_t*)W + eoff)
                                   : (const void*)((const uint8_t*)W + eoff / 2);
   const uint8_t* wexp = WQ == WQ_MXFP4 ? (const uint8_t*)waux + eoff / MX_BLOCK : nullptr;
-  const int ldw_e = WQ == WQ_MXFP4 ? N : ldw;
-  if (g.a_rows)
-    mfma_mainloop<BM, BN, WQ, NW>(A, lda, a_plane, We, ldw_e, wexp, 0, K, 0, n0, t, gs0, gs1, gs2, gs3,
-                              threadIdx.x >> 6, g.a_rows + base + m0, cnt - m0);
+  // EPI_SWIGLU: gate/up over gathered token rows; else down over sorted rows
+  if constexpr (EPI == EPI_SWIGLU)
+    t.run(ring, A, lda, a_plane, We, WQ == WQ_MXFP4 ? N : ldw, wexp, 0, K, 0, n0, g.a_rows + base + m0, cnt - m0);
   else
-    mfma_mainloop<BM, BN, WQ, NW>(A, lda, a_plane, We, ldw_e, wexp, 0, K, base + m0, n0, t, gs0, gs1, gs2, gs3,
-                              threadIdx.x >> 6);
-  if constexpr (WQ == WQ_FP8)
-    scale_columns<BM, BN>(t, (const float*)waux + (size_t)e * N, n0, threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave / (NW / 2), wn = wave % (NW / 2);
-#pragma unroll
-  for (int i = 0; i < FM; ++i) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int ml = m0 + wm * (BM / 2) + i * 16 + (lane >> 4) * 4 + r;
-      if (ml >= cnt) continue;
-      const size_t orow = (size_t)(base + ml);
-      if constexpr (EPI == EPI_SWIGLU) {
-#pragma unroll
-        for (int j = 0; j < FN; j += 2) {
-          const int pb = n0 + wn * WCOL + j * 16;
-          const int col = (pb >> 5) * 16 + (lane & 15);
-          store_pair((bf16_t*)out + orow * ldo + col, out_plane, silu(t.acc[i][j][r]) * t.acc[i][j + 1][r]);
-        }
-      } else {
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-          ((float*)out)[orow * ldo + n0 + wn * WCOL + j * 16 + (lane & 15)] = t.acc[i][j][r];
-      }
+    t.run(ring, A, lda, a_plane, We, WQ == WQ_MXFP4 ? N : ldw, wexp, 0, K, base + m0, n0);
+  if constexpr (WQ == WQ_FP8) t.scale_columns((const float*)waux + (size_t)e * N, n0);
+  const typename G::Tile tl = t.to_lds(ring);
+  const int rows = cnt - m0 < GROUP_BM ? cnt - m0 : GROUP_BM;
+  const size_t row0 = (size_t)(base + m0);
+  if constexpr (EPI == EPI_SWIGLU) {
+    swiglu_tile<G>(tl, rows, (bf16_t*)out + row0 * ldo + (n0 >> 1), ldo, out_plane);
+  } else {
+    constexpr int NQ = BN / 4;
+    for (int it = threadIdx.x; it < rows * NQ; it += G::NT) {
+      const int r = it / NQ, c = (it % NQ) * 4;
+      *(floatx4*)((float*)out + (row0 + r) * ldo + n0 + c) = *(const floatx4*)(tl.row(r) + c);
     }
   }
 }
@@ -618,16 +685,12 @@ hipError_t launch_gemm_grouped(int epi, const void* A, int lda, size_t a_plane, 
   if (N % 128 || K % KALIGN) return hipErrorInvalidValue;
   if ((wq.fmt != WQ_NONE) != (wq.aux != nullptr) || wq.fmt < WQ_NONE || wq.fmt > WQ_MXFP4)
     return hipErrorInvalidValue;
+  if ((epi == EPI_SWIGLU) != (g.a_rows != nullptr)) return hipErrorInvalidValue;
   dim3 grid(N / 128, max_tiles);
   const bf16_t* a = (const bf16_t*)A;
-// waves per grouped tile: 8 (2 x 4 of 64 x 32) for the bf16 gate/up product
-// (expert gate/up per MoE decode 366 -> 355 ms against 4 waves of 64 x 64),
-// 4 for the down product (8 waves: 230 -> 234) and quantized weights
-#define GROUPED_NW(EPI_, WQ_) ((EPI_) == EPI_SWIGLU && (WQ_) == WQ_NONE ? 8 : 4)
-#define BD_GROUPED(EPI_, WQ_, OP_) \
-  k_gemm_grouped<EPI_, WQ_, GROUPED_NW(EPI_, WQ_)><<<grid, 64 * GROUPED_NW(EPI_, WQ_), 0, st>>>(a, lda, a_plane, W, \
-                                                                                              ldw, K, g, out, ldo, OP_, \
-                                                                                              wq.aux, N)
+#define BD_GROUPED(EPI_, WQ_, OP_)                                                                                   \
+  k_gemm_grouped<Tile128<WQ_>, EPI_><<<grid, Tile128<WQ_>::NT, 0, st>>>(a, lda, a_plane, W, ldw, K, g, out, ldo, OP_, \
+                                                                        wq.aux, N)
   if (epi == EPI_SWIGLU) {
     if (wq.fmt == WQ_FP8) BD_GROUPED(EPI_SWIGLU, WQ_FP8, out_plane);
     else if (wq.fmt == WQ_MXFP4) BD_GROUPED(EPI_SWIGLU, WQ_MXFP4, out_plane);
@@ -638,106 +701,152 @@ hipError_t launch_gemm_grouped(int epi, const void* A, int lda, size_t a_plane, 
     else BD_GROUPED(EPI_STORE_F32, WQ_NONE, 0);
   }
 #undef BD_GROUPED
-#undef GROUPED_NW
   return hipGetLastError();
 }
 
-// Fused LM head: for its TBN vocabulary columns the workgroup reduces each row
+// Fused LM head: for its BN vocabulary columns the workgroup reduces each row
 // to (max z, sum exp(z - max), lowest argmax) and writes one partial per
-// (column tile, row); logits never leave registers.  Tiles of 128 x 256
-// with 8 waves of 64 x 64 (the gate/up tile) where the LM rows reach 2048,
-// else 128 x 128 with 4 waves of 64 x 64: on the multi-block decode's
-// 3072-row capacity the LM head went from 1065 to 772 us per launch.
-// LOGITS: the tile's logits also go to the caller's [seq][position][V] buffer
-// straight from the accumulators (64-byte runs per row).  They used to come
-// from a second product of the same size, a scaling pass and a scatter pass
-// over [rows][V]: 199 us for 3072 rows x 4096 columns (d 2048) on top of the
-// head's 118, and 246 on top of 242 for 96 x 152064.
-template <int TBN, int NW, bool LOGITS>
-__global__ __launch_bounds__(64 * NW) void k_lm_head_bf16(const bf16_t* __restrict__ A, int d,
-                                                      size_t a_plane,
-                                                      const bf16_t* __restrict__ W, int V, int mask_id,
-                                                      float scale, const int32_t* __restrict__ Mp,
-                                                      int rows_cap, float* __restrict__ pmax,
-                                                      float* __restrict__ psum,
-                                                      int32_t* __restrict__ parg, StepOut so) {
-  constexpr int TBM = 128, FN = TBN / (8 * NW), WCOL = 2 * TBN / NW, NP = NW / 2;
+// (column tile, row); without LOGITS the logits never leave the workgroup.
+// LOGITS: the tile's logits also go to the caller's [seq][position][V] buffer.
+// They used to come from a second product of the same size, a scaling pass and
+// a scatter pass over [rows][V]: 199 us for 3072 rows x 4096 columns (d 2048)
+// on top of the head's 118, and 246 on top of 242 for 96 x 152064.
+// Tiles that fit the ring go through LDS, four threads a row; the wide ones
+// (LM rows from 2048 on) reduce in the accumulators, 16 lanes a row.
+template <class G, bool LOGITS>
+__global__ __launch_bounds__(G::NT) void k_lm_head_bf16(const bf16_t* __restrict__ A, int d,
+                                                        size_t a_plane,
+                                                        const bf16_t* __restrict__ W, int V, int mask_id,
+                                                        float scale, const int32_t* __restrict__ Mp,
+                                                        int rows_cap, float* __restrict__ pmax,
+                                                        float* __restrict__ psum,
+                                                        int32_t* __restrict__ parg, StepOut so) {
+  constexpr int BM = G::BM, BN = G::BN;
   const int M = *Mp;
   // items in bands of row tiles (band_tile): an XCD's concurrent workgroups
   // share a few row tiles of the operand and a few vocabulary tiles of the head
-  const int X = V / TBN, Y = (M + TBM - 1) / TBM;
+  const int X = V / BN, Y = (M + BM - 1) / BM;
   const int u = xcd_item(blockIdx.x, X * Y);
   if (u >= X * Y) return;
   int vt, ty;
   band_tile(u, X, Y, BAND_R, vt, ty);
-  const int m0 = ty * TBM, n0 = vt * TBN;
-  BD_GEMM_SMEM(TBM, TBN, WQ_NONE);
-  // per-row partials of the NP column groups of waves
-  __shared__ float red_m[NP][TBM], red_s[NP][TBM];
-  __shared__ int32_t red_a[NP][TBM];
-  MfmaTile<TBM, TBN, NW> t;
-  mfma_mainloop<TBM, TBN, WQ_NONE, NW>(A, d, a_plane, W, d, nullptr, 0, d, m0, n0, t, gs0, gs1, gs2, gs3,
-                                       threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave / NP, wn = wave % NP;
+  const int m0 = ty * BM, n0 = vt * BN;
+  BD_GEMM_SMEM(G);
+  G t;
+  t.run(ring, A, d, a_plane, W, d, nullptr, 0, d, m0, n0);
+  if constexpr (G::TILE_FITS) {
+    const typename G::Tile tl = t.to_lds(ring);
+    constexpr int TPR = G::NT / BM, NC = BN / TPR;            // threads per row, columns per thread
+    static_assert(TPR == 4 || TPR == 8, "lanes of a row are neighbours");
+    const int rl = threadIdx.x / TPR, q = threadIdx.x % TPR, m = m0 + rl;
+    // runs of 4 columns, the row's threads side by side
+    float* x = tl.row(rl) + q * 4;
+    float mx = -INFINITY;
+    int arg = 0x7fffffff;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+    for (int k = 0; k < NC / 4; ++k) {
+      floatx4 v = *(floatx4*)(x + k * TPR * 4);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      float v[FN];
-      float mx = -INFINITY;
-      int arg = 0x7fffffff;
-#pragma unroll
-      for (int j = 0; j < FN; ++j) {
-        const int n = n0 + wn * WCOL + j * 16 + (lane & 15);
-        v[j] = (n == mask_id) ? -INFINITY : scale * t.acc[i][j][r];
-        if (v[j] > mx) { mx = v[j]; arg = n; }
+      for (int c = 0; c < 4; ++c) {
+        const int n = n0 + k * TPR * 4 + q * 4 + c;
+        v[c] = n == mask_id ? -INFINITY : scale * v[c];
+        if (v[c] > mx) { mx = v[c]; arg = n; }
       }
-      if constexpr (LOGITS) {
-        const int m = m0 + wm * 64 + i * 16 + (lane >> 4) * 4 + r;
-        if (m < M) {
-          float* z = so.logits + so.at(m) * V + n0 + wn * WCOL + (lane & 15);
+      *(floatx4*)(x + k * TPR * 4) = v;
+    }
 #pragma unroll
-          for (int j = 0; j < FN; ++j) z[j * 16] = v[j];
-        }
-      }
+    for (int off = 1; off < TPR; off <<= 1) {
+      const float om = __shfl_xor(mx, off);
+      const int oa = __shfl_xor(arg, off);
+      if (om > mx || (om == mx && oa < arg)) { mx = om; arg = oa; }
+    }
+    float s = 0.f;
 #pragma unroll
-      for (int off = 1; off < 16; off <<= 1) {
-        const float om = __shfl_xor(mx, off);
-        const int oa = __shfl_xor(arg, off);
-        if (om > mx || (om == mx && oa < arg)) { mx = om; arg = oa; }
-      }
-      float s = 0.f;
+    for (int k = 0; k < NC / 4; ++k) {
+      const floatx4 v = *(const floatx4*)(x + k * TPR * 4);
 #pragma unroll
-      for (int j = 0; j < FN; ++j) s += expf(v[j] - mx);
+      for (int c = 0; c < 4; ++c) s += expf(v[c] - mx);
+    }
 #pragma unroll
-      for (int off = 1; off < 16; off <<= 1) s += __shfl_xor(s, off);
-      if ((lane & 15) == 0) {
-        const int rl = wm * 64 + i * 16 + (lane >> 4) * 4 + r;
-        red_m[wn][rl] = mx;
-        red_s[wn][rl] = s;
-        red_a[wn][rl] = arg;
+    for (int off = 1; off < TPR; off <<= 1) s += __shfl_xor(s, off);
+    if (q == 0 && m < M) {
+      const size_t o = (size_t)vt * rows_cap + m;
+      pmax[o] = mx;
+      psum[o] = s;
+      parg[o] = arg;
+    }
+    if constexpr (LOGITS) {
+      __syncthreads();
+      const int rows = M - m0 < BM ? M - m0 : BM;
+      for (int it = threadIdx.x; it < rows * BN; it += G::NT) {
+        const int r = it / BN, c = it % BN;
+        so.logits[so.at(m0 + r) * V + n0 + c] = tl.row(r)[c];
       }
     }
-  }
-  __syncthreads();
-  if (threadIdx.x < TBM) {
-    const int rl = threadIdx.x, m = m0 + rl;
-    if (m < M) {
-      // column groups in order: the first group holding the maximum gives
-      // the (lowest) argmax
-      float mm = red_m[0][rl];
-      int a = red_a[0][rl];
+  } else {
+    constexpr int FN = G::FN, NP = BN / G::WCOLS;
+    // per-row partials of the NP column groups of waves
+    __shared__ float red_m[NP][BM], red_s[NP][BM];
+    __shared__ int32_t red_a[NP][BM];
+    const int lane = t.lane, wm = t.wm, wn = t.wn;
 #pragma unroll
-      for (int p = 1; p < NP; ++p)
-        if (red_m[p][rl] > mm) { mm = red_m[p][rl]; a = red_a[p][rl]; }
-      float s = 0.f;
+    for (int i = 0; i < G::FM; ++i) {
 #pragma unroll
-      for (int p = 0; p < NP; ++p) s += red_s[p][rl] * expf(red_m[p][rl] - mm);
-      const size_t o = (size_t)vt * rows_cap + m;
-      pmax[o] = mm;
-      psum[o] = s;
-      parg[o] = a;
+      for (int r = 0; r < 4; ++r) {
+        float v[FN];
+        float mx = -INFINITY;
+        int arg = 0x7fffffff;
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          const int n = n0 + wn * G::WCOLS + j * 16 + (lane & 15);
+          v[j] = (n == mask_id) ? -INFINITY : scale * t.acc[i][j][r];
+          if (v[j] > mx) { mx = v[j]; arg = n; }
+        }
+        const int rl = wm * G::WROWS + i * 16 + (lane >> 4) * 4 + r;
+        if constexpr (LOGITS) {
+          if (m0 + rl < M) {
+            float* z = so.logits + so.at(m0 + rl) * V + n0 + wn * G::WCOLS + (lane & 15);
+#pragma unroll
+            for (int j = 0; j < FN; ++j) z[j * 16] = v[j];
+          }
+        }
+#pragma unroll
+        for (int off = 1; off < 16; off <<= 1) {
+          const float om = __shfl_xor(mx, off);
+          const int oa = __shfl_xor(arg, off);
+          if (om > mx || (om == mx && oa < arg)) { mx = om; arg = oa; }
+        }
+        float s = 0.f;
+#pragma unroll
+        for (int j = 0; j < FN; ++j) s += expf(v[j] - mx);
+#pragma unroll
+        for (int off = 1; off < 16; off <<= 1) s += __shfl_xor(s, off);
+        if ((lane & 15) == 0) {
+          red_m[wn][rl] = mx;
+          red_s[wn][rl] = s;
+          red_a[wn][rl] = arg;
+        }
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x < BM) {
+      const int rl = threadIdx.x, m = m0 + rl;
+      if (m < M) {
+        // column groups in order: the first group holding the maximum gives
+        // the (lowest) argmax
+        float mm = red_m[0][rl];
+        int a = red_a[0][rl];
+#pragma unroll
+        for (int p = 1; p < NP; ++p)
+          if (red_m[p][rl] > mm) { mm = red_m[p][rl]; a = red_a[p][rl]; }
+        float s = 0.f;
+#pragma unroll
+        for (int p = 0; p < NP; ++p) s += red_s[p][rl] * expf(red_m[p][rl] - mm);
+        const size_t o = (size_t)vt * rows_cap + m;
+        pmax[o] = mm;
+        psum[o] = s;
+        parg[o] = a;
+      }
     }
   }
 }
@@ -976,20 +1085,14 @@ __global__ __launch_bounds__(256) void k_lm_merge(const float* __restrict__ pmax
 
 // ------------------------------------------------------------------ launchers
 
-template <int BM, int BN, int WQ, int NW = 4>
-static void launch_bf16_cfg(int epi, dim3 grid, const bf16_t* a, int lda, size_t ap, const void* w,
-                            int ldw, int N, int K, const int32_t* M_dev, void* o, int ldo, size_t op,
-                            float* ws, int zmax, const void* waux, hipStream_t st) {
-  switch (epi) {
-    case EPI_ADD_F32:
-      k_gemm_bf16<BM, BN, EPI_ADD_F32, WQ, NW><<<grid, 64 * NW, 0, st>>>(a, lda, ap, w, ldw, N, K, M_dev, o, ldo, op, ws,
-                                                                 zmax, waux);
-      break;
-    default:   // EPI_SWIGLU
-      k_gemm_bf16<BM, BN, EPI_SWIGLU, WQ, NW><<<grid, 64 * NW, 0, st>>>(a, lda, ap, w, ldw, N, K, M_dev, o, ldo, op,
-                                                                nullptr, 1, waux);
-      break;
-  }
+template <class G>
+static void launch_tile(int epi, dim3 grid, const bf16_t* a, int lda, size_t ap, const void* w,
+                        int ldw, int N, int K, const int32_t* M_dev, void* o, int ldo, size_t op,
+                        float* ws, int zmax, const void* waux, hipStream_t st) {
+  if (epi == EPI_ADD_F32)
+    k_gemm_bf16<G, EPI_ADD_F32><<<grid, G::NT, 0, st>>>(a, lda, ap, w, ldw, N, K, M_dev, o, ldo, op, ws, zmax, waux);
+  else   // EPI_SWIGLU
+    k_gemm_bf16<G, EPI_SWIGLU><<<grid, G::NT, 0, st>>>(a, lda, ap, w, ldw, N, K, M_dev, o, ldo, op, nullptr, 1, waux);
 }
 
 // Tile choice: 128x256 (8 waves of 64 x 64, two per SIMD; 128 KB of LDS) over
@@ -1041,21 +1144,20 @@ hipError_t launch_gemm_planned(const GemmPlan& p, int epi, const void* A, int ld
   // (see xcd_item)
   dim3 grid((N / p.bn) * cdiv(rows_cap, p.bm) * p.zmax + 7);
   const bf16_t* a = (const bf16_t*)A;
-#define BD_CFG(BM_, BN_, WQ_) \
-  launch_bf16_cfg<BM_, BN_, WQ_>(epi, grid, a, lda, a_plane, W, ldw, N, K, M_dev, out, ldo, out_plane, ws, p.zmax, \
-                                 wq.aux, st)
+#define BD_TILE(G_) \
+  launch_tile<G_>(epi, grid, a, lda, a_plane, W, ldw, N, K, M_dev, out, ldo, out_plane, ws, p.zmax, wq.aux, st)
   if (wq.fmt == WQ_FP8) {
-    if (big) BD_CFG(128, 128, WQ_FP8); else BD_CFG(64, 64, WQ_FP8);
+    if (big) BD_TILE(Tile128<WQ_FP8>); else BD_TILE(Tile64<WQ_FP8>);
   } else if (wq.fmt == WQ_MXFP4) {
-    if (big) BD_CFG(128, 128, WQ_MXFP4); else BD_CFG(64, 64, WQ_MXFP4);
+    if (big) BD_TILE(Tile128<WQ_MXFP4>); else BD_TILE(Tile64<WQ_MXFP4>);
   } else {
-    if (wide) launch_bf16_cfg<128, 256, WQ_NONE, 8>(epi, grid, a, lda, a_plane, W, ldw, N, K, M_dev, out, ldo,
-                                                     out_plane, ws, p.zmax, nullptr, st);
-    else if (big) BD_CFG(128, 128, WQ_NONE);
-    else if (mid) BD_CFG(64, 128, WQ_NONE);
-    else BD_CFG(64, 64, WQ_NONE);
+    if (wide && epi == EPI_SWIGLU) BD_TILE(TileW2);
+    else if (wide) BD_TILE(TileW);
+    else if (big) BD_TILE(Tile128<WQ_NONE>);
+    else if (mid) BD_TILE(Tile64x128<WQ_NONE>);
+    else BD_TILE(Tile64<WQ_NONE>);
   }
-#undef BD_CFG
+#undef BD_TILE
   return hipGetLastError();
 }
 
@@ -1115,30 +1217,27 @@ hipError_t launch_gemm_qkv(const void* A, int lda, size_t a_plane, const void* W
   if (e.hd % 16 || e.kv.vstride % 64 || K % KALIGN) return hipErrorInvalidValue;
   if ((wq.fmt != WQ_NONE) != (wq.aux != nullptr) || wq.fmt < WQ_NONE || wq.fmt > WQ_MXFP4)
     return hipErrorInvalidValue;
-  // bf16 weights where the product would fill at least 512 tiles of 128 x 256
-  // over the row capacity (the 6144-row multi-block window of a 3072-wide
-  // QKV): 128x128 tiles with 8 waves of 64 x 32.  Per
-  // decode, QKV took 428 ms in 4-wave 128x128 tiles, 383 in 8-wave 128x256
-  // tiles (312 tiles for 256 CUs: a nearly empty second round) and 335 in
-  // 8-wave 128x128 tiles (624 tiles, three half-length rounds).  The MoE
-  // (4096-row) and long-prefix (2048-row) windows, whose live rows fall well
-  // below the capacity, keep the 4-wave tiling: 8-wave tiles there ran 13%
-  // slower and no faster.
-  GemmPlan p = plan_gemm(true, N, K, rows_cap, false, false);
-  const bool eight = wq.fmt == WQ_NONE && N % 256 == 0 && (N / 256) * cdiv(rows_cap, 128) >= 512;
-  if (eight) p = GemmPlan{128, 128, 1};
-  if (N % p.bn) return hipErrorInvalidValue;
-  dim3 grid((N / p.bn) * cdiv(rows_cap, p.bm) + 7);
+  // Tile by the workgroups it gives over half the row capacity (the rows a step
+  // window usually holds; a prefill holds twice that): 128 x 128, then
+  // 64 x 128, where there are at least 192 of them, else 64 x 64.  Measured for
+  // N 3072, K 2048 (us, 128 x 128 / 64 x 128 / 64 x 64): 96 rows - / 14.3 /
+  // 11.8, 512 rows 24.9 / 17.2 / 19.1, 1024 rows 28.8 / 32.3 / 30.4, 3072 rows
+  // 77 / - / -.
+  const int half_cap = cdiv(rows_cap, 2);
+  const int bm = N % 128 == 0 && (N / 128) * cdiv(half_cap, 128) >= 192 ? 128 : 64;
+  const int bn = bm == 128 || (wq.fmt == WQ_NONE && N % 128 == 0 && (N / 128) * cdiv(half_cap, 64) >= 192) ? 128 : 64;
+  if (N % bn) return hipErrorInvalidValue;
+  dim3 grid((N / bn) * cdiv(rows_cap, bm) + 7);
   const bf16_t* a = (const bf16_t*)A;
-#define BD_QKV(BM_, WQ_) k_gemm_qkv<BM_, BM_, WQ_><<<grid, 256, 0, st>>>(a, lda, a_plane, W, K, M_dev, e, wq.aux)
+#define BD_QKV(G_) k_gemm_qkv<G_><<<grid, G_::NT, 0, st>>>(a, lda, a_plane, W, K, M_dev, e, wq.aux)
   if (wq.fmt == WQ_FP8) {
-    if (p.bm == 128) BD_QKV(128, WQ_FP8); else BD_QKV(64, WQ_FP8);
+    if (bm == 128) BD_QKV(Tile128<WQ_FP8>); else BD_QKV(Tile64<WQ_FP8>);
   } else if (wq.fmt == WQ_MXFP4) {
-    if (p.bm == 128) BD_QKV(128, WQ_MXFP4); else BD_QKV(64, WQ_MXFP4);
-  } else if (eight) {
-    k_gemm_qkv<128, 128, WQ_NONE, 8><<<grid, 512, 0, st>>>(a, lda, a_plane, W, K, M_dev, e, nullptr);
+    if (bm == 128) BD_QKV(Tile128<WQ_MXFP4>); else BD_QKV(Tile64<WQ_MXFP4>);
   } else {
-    if (p.bm == 128) BD_QKV(128, WQ_NONE); else BD_QKV(64, WQ_NONE);
+    if (bm == 128) BD_QKV(Tile128<WQ_NONE>);
+    else if (bn == 128) BD_QKV(Tile64x128<WQ_NONE>);
+    else BD_QKV(Tile64<WQ_NONE>);
   }
 #undef BD_QKV
   return hipGetLastError();
@@ -1192,15 +1291,19 @@ hipError_t launch_lm_head(bool is_bf16, const void* A, int d, size_t a_plane, co
   if (is_bf16) {
     if (V % 128 || d % KALIGN) return hipErrorInvalidValue;
     const bool wide = V % 256 == 0 && rows_cap >= 2048;
+    // 64-row tiles where 128-row ones would leave CUs without one
+    const bool low = !wide && (V / 128) * cdiv(rows_cap, 128) < 256;
     ntiles = V / (wide ? 256 : 128);
-    dim3 grid(ntiles * cdiv(rows_cap, 128) + 7);
-#define BD_HEAD(BN_, NW_, LOG_)                                                                           \
-  k_lm_head_bf16<BN_, NW_, LOG_><<<grid, 64 * NW_, 0, st>>>((const bf16_t*)A, d, a_plane, (const bf16_t*)W, V, mask_id, \
-                                                            scale, M_dev, rows_cap, part_max, part_sum, part_arg, so)
+    dim3 grid(ntiles * cdiv(rows_cap, low ? 64 : 128) + 7);
+#define BD_HEAD(G_, LOG_)                                                                                       \
+  k_lm_head_bf16<G_, LOG_><<<grid, G_::NT, 0, st>>>((const bf16_t*)A, d, a_plane, (const bf16_t*)W, V, mask_id, scale, \
+                                                    M_dev, rows_cap, part_max, part_sum, part_arg, so)
     if (wide) {
-      if (so.logits) BD_HEAD(256, 8, true); else BD_HEAD(256, 8, false);
+      if (so.logits) BD_HEAD(TileW2, true); else BD_HEAD(TileW2, false);
+    } else if (low) {
+      if (so.logits) BD_HEAD(Tile64x128<WQ_NONE>, true); else BD_HEAD(Tile64x128<WQ_NONE>, false);
     } else {
-      if (so.logits) BD_HEAD(128, 4, true); else BD_HEAD(128, 4, false);
+      if (so.logits) BD_HEAD(Tile128<WQ_NONE>, true); else BD_HEAD(Tile128<WQ_NONE>, false);
     }
 #undef BD_HEAD
   } else {
