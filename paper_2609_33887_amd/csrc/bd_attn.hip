@@ -349,13 +349,21 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float* __restrict__ ws
       make_uint2((uint32_t)lb[0] | ((uint32_t)lb[1] << 16), (uint32_t)lb[2] | ((uint32_t)lb[3] << 16));
 }
 
-// fp32 models: a workgroup per (query row, head), its 4 waves taking the
-// 64-key tiles in turn.  For the scores a lane owns a key (its K row against
-// the query, held in LDS), so the softmax needs one wave reduction per 64 keys;
-// for P V a lane owns hd / 64 dims and the probabilities come round by lane
-// reads, every V row a coalesced load.  The four waves' running results are
-// merged in wave order.  36 keys, 4 rows x 4 heads: 21 us with one wave walking
-// the keys one by one (six shuffles and two dependent loads a key), 5 us so.
+// a * b, not fused into the sum that takes it
+__device__ __forceinline__ float rounded_mul(float a, float b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+
+// fp32 models: a wave per (query row, head), keys in tiles of 64.  For the
+// scores a lane owns a key: the products of its K row with the query (held in
+// LDS) are summed over the binary tree of dim indices (i + 32, then 16, .. 1;
+// two trees' values are first added for hd 128), and the running maximum,
+// weights and rescale factors of the online softmax are then formed for all
+// keys of the tile at once.  For P V a lane owns hd / 64 dims and walks the keys
+// in order, every V row a coalesced load, the tile's all in flight at once.  The arithmetic is
+// that of a wave walking the keys one by one (one butterfly sum and one rescale
+// per key), which took 21 us for 36 keys, 4 rows x 4 heads, against 7.
 template <int HD>
 __global__ __launch_bounds__(256) void k_attn_f32(const float* __restrict__ Q,
                                                   const float* __restrict__ Kc,
@@ -366,75 +374,80 @@ __global__ __launch_bounds__(256) void k_attn_f32(const float* __restrict__ Q,
                                                   const int32_t* __restrict__ Mp, int H, int Hkv,
                                                   int maxpos, int B, float scale) {
   constexpr int PER = HD / 64;
-  __shared__ __attribute__((aligned(16))) float sq[HD];
-  __shared__ float so[4][HD], sm[4], sl[4];
+  __shared__ __attribute__((aligned(16))) float sq_all[4][HD];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int r = blockIdx.x / H, h = blockIdx.x % H;
+  const int item = blockIdx.x * 4 + wave;
+  const int r = item / H, h = item % H;
   if (r >= *Mp) return;
+  float* sq = sq_all[wave];
   const int s = row_seq[r], pos = row_pos[r];
   const int kend = (pos / B + 1) * B;
   const int kv = h / (H / Hkv);
   const float* Kp = Kc + ((size_t)s * Hkv + kv) * (size_t)maxpos * HD;
   const float* Vp = Vc + ((size_t)s * Hkv + kv) * (size_t)maxpos * HD;
-  if (threadIdx.x < HD) sq[threadIdx.x] = Q[((size_t)r * H + h) * HD + threadIdx.x];
-  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < PER; ++e) sq[e * 64 + lane] = Q[((size_t)r * H + h) * HD + e * 64 + lane];
+  __builtin_amdgcn_wave_barrier();
   float acc[PER], m = -INFINITY, l = 0.f;
 #pragma unroll
   for (int e = 0; e < PER; ++e) acc[e] = 0.f;
-  for (int k0 = wave * 64; k0 < kend; k0 += 256) {
-    const int key = k0 + lane;
-    float sc = -INFINITY;
-    if (key < kend) {
-      const float4* kr = (const float4*)(Kp + (size_t)key * HD);
-      float p[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int e = 0; e < HD / 4; ++e) {
-        const float4 kx = kr[e], qx = *(const float4*)(sq + 4 * e);
-        p[0] += kx.x * qx.x; p[1] += kx.y * qx.y; p[2] += kx.z * qx.z; p[3] += kx.w * qx.w;
-      }
-      sc = ((p[0] + p[1]) + (p[2] + p[3])) * scale;
-    }
-    float mt = sc;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mt = fmaxf(mt, __shfl_xor(mt, off));
-    const float mn = fmaxf(m, mt);                // finite: the tile holds a key
-    const float al = expf(m - mn), pr = expf(sc - mn);
-    float ps = pr;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) ps += __shfl_xor(ps, off);
-    l = l * al + ps;
-    m = mn;
-#pragma unroll
-    for (int e = 0; e < PER; ++e) acc[e] *= al;
-    // eight V rows in flight; past the last key the row repeats, its weight 0
+  for (int k0 = 0; k0 < kend; k0 += 64) {
     const int n = kend - k0 < 64 ? kend - k0 : 64;
+    const int key = k0 + (lane < n ? lane : n - 1);
+    const float4* kr = (const float4*)(Kp + (size_t)key * HD);
+    // this lane's dims of every V row of the tile, in flight from here on
     const float* vr = Vp + (size_t)k0 * HD + lane * PER;
-    for (int j0 = 0; j0 < n; j0 += 8) {
+    float v[64][PER];
 #pragma unroll
-      for (int jj = 0; jj < 8; ++jj) {
-        const int j = j0 + jj;
-        const float pj = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(pr), j));
-        const float* vj = vr + (size_t)(j < n ? j : n - 1) * HD;
+    for (int j = 0; j < 64; ++j)
 #pragma unroll
-        for (int e = 0; e < PER; ++e) acc[e] += pj * vj[e];
+      for (int e = 0; e < PER; ++e) v[j][e] = j < n ? vr[(size_t)j * HD + e] : 0.f;
+    float t[64];                       // one value per lane of a wave summing this key
+#pragma unroll
+    for (int x = 0; x < HD / 4; ++x) {
+      const float4 kx = kr[x], qx = *(const float4*)(sq + 4 * x);
+      if constexpr (PER == 1) {
+        t[4 * x] = rounded_mul(qx.x, kx.x); t[4 * x + 1] = rounded_mul(qx.y, kx.y);
+        t[4 * x + 2] = rounded_mul(qx.z, kx.z); t[4 * x + 3] = rounded_mul(qx.w, kx.w);
+      } else {
+        t[2 * x] = fmaf(qx.y, kx.y, rounded_mul(qx.x, kx.x));
+        t[2 * x + 1] = fmaf(qx.w, kx.w, rounded_mul(qx.z, kx.z));
       }
     }
-  }
 #pragma unroll
-  for (int e = 0; e < PER; ++e) so[wave][lane * PER + e] = acc[e];
-  if (lane == 0) { sm[wave] = m; sl[wave] = l; }
-  __syncthreads();
-  if (threadIdx.x < HD) {
-    const float mx = fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
-    float o = 0.f, L = 0.f;
+    for (int off = 32; off > 0; off >>= 1)
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const float f = expf(sm[w] - mx);           // 0 for a wave without keys
-      o += f * so[w][threadIdx.x];
-      L += f * sl[w];
+      for (int i = 0; i < off; ++i) t[i] += t[i + off];
+    const float sc = lane < n ? t[0] * scale : -INFINITY;
+    // running maximum up to and including each key, and before it
+    float mi = sc;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const float o = __shfl_up(mi, off);
+      if (lane >= off) mi = fmaxf(mi, o);
     }
-    O[((size_t)r * H + h) * HD + threadIdx.x] = o / L;
+    mi = fmaxf(mi, m);
+    float mb = __shfl_up(mi, 1);
+    if (lane == 0) mb = m;
+    const float al = expf(mb - mi), pr = expf(fmaf(t[0], scale, -mi));   // keys past the last one are not walked
+#pragma unroll
+    for (int j0 = 0; j0 < 64; j0 += 8) {
+      if (j0 >= n) break;              // wave-uniform, as below
+#pragma unroll
+      for (int j = j0; j < j0 + 8; ++j) {
+        if (j >= n) break;
+        const float a = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(al), j));
+        const float p = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(pr), j));
+        l = l * a + p;
+#pragma unroll
+        for (int e = 0; e < PER; ++e) acc[e] = fmaf(acc[e], a, p * v[j][e]);
+      }
+    }
+    m = __shfl(mi, n - 1);
   }
+  float* o = O + ((size_t)r * H + h) * HD;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) o[lane * PER + e] = acc[e] / l;
 }
 
 // waves per workgroup for a window of win_cap rows over a key capacity of
@@ -498,7 +511,7 @@ hipError_t launch_attention(bool is_bf16, const void* Q, size_t q_plane, const K
     if (hd != 64 && hd != 128) return hipErrorInvalidValue;
     const float scale = (float)(1.0 / sqrt((double)hd));
 #define BD_ATTN_F32(HD_)                                                                                       \
-  k_attn_f32<HD_><<<rows_cap * H, 256, 0, st>>>((const float*)Q, (const float*)kv.K, (const float*)kv.V, (float*)O, \
+  k_attn_f32<HD_><<<(rows_cap * H + 3) / 4, 256, 0, st>>>((const float*)Q, (const float*)kv.K, (const float*)kv.V, (float*)O, \
                                                 plan.row_seq, plan.row_pos, plan.hdr, H, Hkv, kv.maxpos, B, scale)
     if (hd == 128) BD_ATTN_F32(128); else BD_ATTN_F32(64);
 #undef BD_ATTN_F32

@@ -24,7 +24,7 @@
 // E2M1 value x 2^X, exact in bf16), again the bf16 product with the
 // dequantized weights.  The codes are stored stage-major (WQuant), so a
 // stage's W rows are one contiguous run of 16-byte rows.
-// f32 path (small fp32 models): fp32 MFMA tiles with K split over the waves.
+// f32 path (small fp32 models): fp32 MFMA tiles, the sums in order of depth.
 //
 // The row count M is read from device memory so that a launch sized for the
 // largest window can be replayed every step; tiles at or past M exit.
@@ -853,144 +853,205 @@ __global__ __launch_bounds__(G::NT) void k_lm_head_bf16(const bf16_t* __restrict
 
 // ------------------------------------------------------------------ f32 MFMA
 // fp32 models are small, so their products are bound by latency and not by
-// arithmetic: the work of a tile is split over K between the waves of a
-// workgroup, every wave has its whole share of both operands in flight at
-// once (registers straight from global memory, no staging), multiplies on the
-// fp32 matrix cores (v_mfma_f32_16x16x4_f32: fp32 operands and accumulation)
-// and the KW partial tiles are summed in wave order in LDS.  A chunk is 16
-// deep: lane (c, g) holds depths 4 g .. 4 g + 3 of row c of either operand,
-// and MFMA step s takes element s of each lane (the same permutation of the
-// depth on both sides).  Tiles: 16 x 32 with 8 waves over K, and 64 x 32 (two
-// groups of 32 rows, 4 waves over K each) where the row capacity gives at
-// least 512 of them.  4 rows, N 256, K 1024: 80 us with 64 x 64 x 16 SIMT
-// tiles (4 workgroups, 64 barrier steps), 6 us so; N 2048, K 256: 33 -> 5 us.
+// arithmetic.  A wave owns one 16 x 16 block and takes the whole depth in order
+// on the fp32 matrix cores: v_mfma_f32_16x16x4_f32 adds its four products to
+// the accumulator one after the other, each with one rounding, so the chain
+// equals fmaf over k = 0, 1, .. K - 1 to the last bit (checked on gfx950,
+// subnormal values included).  What is left is to keep the operands coming:
+// chunks of 128 depths go straight into a ring of LDS stages, up to 384 depths
+// in flight, for WM x WN waves that share the tile's rows.  Tiles: 16 x 32 with
+// two waves, and 64 x 32 with eight where the row capacity holds at least 512
+// of them.  4 rows, N 256, K 1024: 80 us with 64 x 64 x 16 SIMT tiles (4
+// workgroups, 64 barrier steps, each thread the same sequential sum), 14 so;
+// N 2048, K 256: 33 -> 5.6.
 constexpr int FBN = 32;      // columns of a projection tile
 constexpr int FHN = 64;      // columns of a head tile
-constexpr int FCH = 16;      // depth per chunk
-// the caller's fp32 matrices need no more than 4-byte alignment
-typedef float floatx4_u __attribute__((ext_vector_type(4), aligned(4)));
+constexpr int FKC = 128;     // depth per stage
 
-// Columns of fragment f of a wave's tile: 16 consecutive ones from
-// col0 + f * cstep on.  red: [KW][BM][16 FN + 1].
-template <int FM, int FN, int WM, int KW>
-__device__ __forceinline__ void f32_tile(const float* __restrict__ A, int lda, const float* __restrict__ W, int ldw,
-                                         int K, int m0, int col0, int cstep, float* __restrict__ red) {
-  constexpr int BM = 16 * FM * WM, LD = 16 * FN + 1, U = FM + FN <= 3 ? 8 : 4;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave % WM, kw = wave / WM;
-  const int c = lane & 15, g = lane >> 4;
-  const int nch = K / FCH, beg = nch * kw / KW, end = nch * (kw + 1) / KW;
-  const float* ap[FM];
-  const float* wp[FN];
+template <int ROWS>
+struct F32Stage {
+  float x[ROWS * FKC];       // A rows, then W rows, 512 bytes each; 16-byte chunk c of row r at c ^ (r & 7)
+};
+
+template <int WM_, int WN_, int NS>
+struct GemmF32 {
+  static constexpr int WM = WM_, WN = WN_, NW = WM * WN, NT = 64 * NW;
+  static constexpr int BM = 16 * WM, BN = 16 * WN, ROWS = BM + BN, LD = BN + 1;
+  static constexpr int LN = ROWS / (2 * NW);      // 1 KiB loads (two rows) per wave and stage
+  static_assert(LN * 2 * NW == ROWS && (NS - 1) * LN < 64, "whole loads per wave, all countable");
+  typedef F32Stage<ROWS> Stage;
+  typedef GemmRing<Stage> Ring;
+  floatx4 acc;
+  __amdgpu_buffer_rsrc_t ra, rw;
+  uint32_t off[LN];
+  int lane, wave;
+
+  // rows 2 q, 2 q + 1 of the stage by load q; BM is a multiple of 16, so a
+  // load is all A or all W.  Lanes past the depth are masked off: the chain
+  // does not read those chunks.
+  __device__ __forceinline__ void issue(Stage& s, int t, int K) {
+    const int src = (lane & 31);
 #pragma unroll
-  for (int i = 0; i < FM; ++i) ap[i] = A + (size_t)(m0 + (wm * FM + i) * 16 + c) * lda + 4 * g;
-#pragma unroll
-  for (int j = 0; j < FN; ++j) wp[j] = W + (size_t)(col0 + j * cstep + c) * ldw + 4 * g;
-  floatx4 acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  for (int ch = beg; ch < end; ch += U) {
-    floatx4_u a[U][FM], w[U][FN];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (ch + u < end) {
-#pragma unroll
-        for (int i = 0; i < FM; ++i) a[u][i] = *(const floatx4_u*)(ap[i] + (size_t)(ch + u) * FCH);
-#pragma unroll
-        for (int j = 0; j < FN; ++j) w[u][j] = *(const floatx4_u*)(wp[j] + (size_t)(ch + u) * FCH);
+    for (int i = 0; i < LN; ++i) {
+      const int q = i * NW + wave, r = 2 * q + (lane >> 5);
+      if (t * FKC + (src ^ (r & 7)) * 4 < K) {
+        if (q < BM / 2) load_lds16(ra, s.x + 2 * q * FKC, off[i], (uint32_t)t * (FKC * 4));
+        else load_lds16(rw, s.x + 2 * q * FKC, off[i], (uint32_t)t * (FKC * 4));
       }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (ch + u < end) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i][e], w[u][j][e], acc[i][j], 0, 0, 0);
-      }
+    }
   }
+  __device__ __forceinline__ void chain(const Stage& s, int steps) {
+    const int c = lane & 15, g = lane >> 4;
+    const float* pa = s.x + ((wave / WN) * 16 + c) * FKC + g;
+    const float* pw = s.x + (BM + (wave % WN) * 16 + c) * FKC + g;
+    const int sw = c & 7;     // blocks of 16 rows start at multiples of 8
+    // four steps' operands are read while the four before them multiply (past
+    // the last step the stage's first ones are read again, unused)
+    float a[4], w[4], an[4], wn[4];
+    auto read = [&](float* x, float* y, int q) {
 #pragma unroll
-  for (int i = 0; i < FM; ++i)
+      for (int e = 0; e < 4; ++e) {
+        x[e] = pa[((q + e) ^ sw) * 4];
+        y[e] = pw[((q + e) ^ sw) * 4];
+      }
+    };
+    auto mul = [&](const float* x, const float* y) {
 #pragma unroll
-    for (int j = 0; j < FN; ++j)
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], y[e], acc, 0, 0, 0);
+    };
+    read(a, w, 0);
+    for (int q = 0; q < steps; q += 8) {
+      read(an, wn, q + 4 < steps ? q + 4 : 0);
+      mul(a, w);
+      if (q + 4 < steps) {
+        read(a, w, q + 8 < steps ? q + 8 : 0);
+        mul(an, wn);
+      }
+    }
+  }
+  template <int I, int REM, bool LAST>
+  __device__ __forceinline__ void steps(const Ring& rg, int t, int K) {
+    if constexpr (I < REM) {
+      constexpr int LEFT = LAST ? (REM - 1 - I < NS - 2 ? REM - 1 - I : NS - 2) : NS - 2;
+      wait_vmcnt<LEFT * LN>();
+      __builtin_amdgcn_s_barrier();
+      if constexpr (!LAST || I + NS - 1 < REM) issue(rg.template at<(I + NS - 1) % NS>(), t + I + NS - 1, K);
+      const int left = (K - (t + I) * FKC) / 4;
+      chain(rg.template at<I % NS>(), left < FKC / 4 ? left : FKC / 4);
+      steps<I + 1, REM, LAST>(rg, t, K);
+    }
+  }
+  template <int REM>
+  __device__ __forceinline__ void tails(const Ring& rg, int t, int rem, int K) {
+    if constexpr (REM <= 2 * NS - 2) {
+      if (rem == REM) steps<0, REM, true>(rg, t, K);
+      else tails<REM + 1>(rg, t, rem, K);
+    }
+  }
+  // K a multiple of 16; the tile's W rows are wrow0 + n for n < 16 and, from
+  // column 16 on, wrow0 + wstep + n - 16, .. (wstep rows per 16 columns)
+  __device__ __forceinline__ void run(const Ring& rg, const float* __restrict__ A, int lda,
+                                      const float* __restrict__ W, int ldw, int K, int m0, int wrow0, int wstep) {
+    lane = threadIdx.x & 63;
+    wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    m0 = __builtin_amdgcn_readfirstlane(m0);
+    wrow0 = __builtin_amdgcn_readfirstlane(wrow0);
+    ra = buf_rsrc(A + (size_t)m0 * lda);
+    rw = buf_rsrc(W + (size_t)wrow0 * ldw);
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        red[((size_t)kw * BM + (wm * FM + i) * 16 + 4 * g + r) * LD + j * 16 + c] = acc[i][j][r];
-  __syncthreads();
-}
+    for (int i = 0; i < LN; ++i) {
+      const int r = 2 * (i * NW + wave) + (lane >> 5);
+      const uint32_t c = ((lane & 31) ^ (r & 7)) * 4;
+      const int n = r - BM;
+      off[i] = (r < BM ? (uint32_t)r * (uint32_t)lda + c
+                       : (uint32_t)((n >> 4) * wstep + (n & 15)) * (uint32_t)ldw + c) * 4u;
+    }
+    acc = floatx4{0.f, 0.f, 0.f, 0.f};
+    const int nk = (K + FKC - 1) / FKC;
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    issue(rg.template at<0>(), 0, K);
+    if (nk > 1) issue(rg.template at<1>(), 1, K);
+    if constexpr (NS > 3) if (nk > 2) issue(rg.template at<2>(), 2, K);
+    int t = 0;
+    for (; t + 2 * NS - 1 <= nk; t += NS) steps<0, NS, false>(rg, t, K);
+    tails<1>(rg, t, nk - t, K);
+  }
+  // the tile in LDS (stage 0), rows of LD floats
+  __device__ __forceinline__ float* to_lds(const Ring& rg) {
+    static_assert(sizeof(Stage) >= sizeof(float) * BM * LD, "tile in a stage");
+    float* o = rg.template at<0>().x;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      o[((wave / WN) * 16 + 4 * (lane >> 4) + r) * LD + (wave % WN) * 16 + (lane & 15)] = acc[r];
+    __syncthreads();
+    return o;
+  }
+};
+typedef GemmF32<1, 2, 4> F32Small;
+typedef GemmF32<4, 2, 3> F32Large;
+typedef GemmF32<1, 4, 3> F32Head;
 
-// Sum of the KW partials of tile element (row, col), in wave order.
-template <int BM, int LD, int KW>
-__device__ __forceinline__ float f32_sum(const float* __restrict__ red, int row, int col) {
-  float v = red[row * LD + col];
-#pragma unroll
-  for (int k = 1; k < KW; ++k) v += red[(k * BM + row) * LD + col];
-  return v;
-}
-
-template <int FM, int WM, int KW, int EPI>
-__global__ __launch_bounds__(64 * WM * KW) void k_gemm_f32(const float* __restrict__ A, int lda,
-                                                           const float* __restrict__ W, int ldw, int K,
-                                                           const int32_t* __restrict__ Mp,
-                                                           float* __restrict__ out, int ldo) {
-  constexpr int BM = 16 * FM * WM, LD = FBN + 1, NT = 64 * WM * KW;
-  __shared__ float red[KW * BM * LD];
+template <class G, int EPI>
+__global__ __launch_bounds__(G::NT) void k_gemm_f32(const float* __restrict__ A, int lda,
+                                                    const float* __restrict__ W, int ldw, int K,
+                                                    const int32_t* __restrict__ Mp,
+                                                    float* __restrict__ out, int ldo) {
+  constexpr int BM = G::BM, LD = G::LD;
   const int M = *Mp;
   const int m0 = blockIdx.y * BM, n0 = blockIdx.x * FBN;
   if (m0 >= M) return;
-  f32_tile<FM, 2, WM, KW>(A, lda, W, ldw, K, m0, n0, 16, red);
+  BD_GEMM_SMEM(G);
+  G t;
+  t.run(ring, A, lda, W, ldw, K, m0, n0, 16);
+  const float* x = t.to_lds(ring);
   if constexpr (EPI == EPI_SWIGLU) {
-    // packed gate/up groups of 16 columns: fragment 0 = gate, 1 = up
-    for (int e = threadIdx.x; e < BM * 16; e += NT) {
+    // packed gate/up groups of 16 columns
+    for (int e = threadIdx.x; e < BM * 16; e += G::NT) {
       const int r = e >> 4, c = e & 15, m = m0 + r;
-      if (m >= M) continue;
-      const float gt = f32_sum<BM, LD, KW>(red, r, c), up = f32_sum<BM, LD, KW>(red, r, 16 + c);
-      out[(size_t)m * ldo + (n0 >> 1) + c] = silu(gt) * up;
+      if (m < M) out[(size_t)m * ldo + (n0 >> 1) + c] = silu(x[r * LD + c]) * x[r * LD + 16 + c];
     }
   } else {
-    for (int e = threadIdx.x; e < BM * FBN; e += NT) {
+    for (int e = threadIdx.x; e < BM * FBN; e += G::NT) {
       const int r = e / FBN, c = e % FBN, m = m0 + r;
-      if (m >= M) continue;
-      out[(size_t)m * ldo + n0 + c] += f32_sum<BM, LD, KW>(red, r, c);
+      if (m < M) out[(size_t)m * ldo + n0 + c] += x[r * LD + c];
     }
   }
 }
 
 // fp32 QKV projection with RoPE and the cache write in the epilogue.  A tile
 // is 16 dims i .. i + 15 of one head and their rotation partners
-// i + hd/2 .. (its two column fragments), so both halves of a rotation meet in
+// i + hd/2 .. (its two column blocks), so both halves of a rotation meet in
 // one thread; angle and rotation in fp64 with one rounding to fp32, at the
 // row's absolute position.  q -> Q[row][head][hd], k and v -> the cache slots
 // [seq][kv head][pos][hd].
-template <int FM, int WM, int KW>
-__global__ __launch_bounds__(64 * WM * KW) void k_gemm_qkv_f32(const float* __restrict__ A, int lda,
-                                                               const float* __restrict__ W, int K,
-                                                               const int32_t* __restrict__ Mp, QkvEpi q,
-                                                               const double* __restrict__ inv_freq) {
-  constexpr int BM = 16 * FM * WM, LD = FBN + 1, NT = 64 * WM * KW;
-  __shared__ float red[KW * BM * LD];
+template <class G>
+__global__ __launch_bounds__(G::NT) void k_gemm_qkv_f32(const float* __restrict__ A, int lda,
+                                                        const float* __restrict__ W, int K,
+                                                        const int32_t* __restrict__ Mp, QkvEpi q,
+                                                        const double* __restrict__ inv_freq) {
+  constexpr int BM = G::BM, LD = G::LD;
   const int M = *Mp;
   const int m0 = blockIdx.y * BM;
   if (m0 >= M) return;
   const int half = q.hd / 2, tph = q.hd / FBN;              // tiles per head
   const int head = blockIdx.x / tph, i0 = (blockIdx.x % tph) * 16;
-  f32_tile<FM, 2, WM, KW>(A, lda, W, K, K, m0, head * q.hd + i0, half, red);
-  for (int e = threadIdx.x; e < BM * 16; e += NT) {
+  BD_GEMM_SMEM(G);
+  G t;
+  t.run(ring, A, lda, W, K, K, m0, head * q.hd + i0, half);
+  const float* x = t.to_lds(ring);
+  for (int e = threadIdx.x; e < BM * 16; e += G::NT) {
     const int r = e >> 4, i = i0 + (e & 15), m = m0 + r;
     if (m >= M) continue;
-    const float x1 = f32_sum<BM, LD, KW>(red, r, e & 15), x2 = f32_sum<BM, LD, KW>(red, r, 16 + (e & 15));
+    const double x1 = x[r * LD + (e & 15)], x2 = x[r * LD + 16 + (e & 15)];
     const int s = q.row_seq[m], pos = q.row_pos[m];
-    float y1 = x1, y2 = x2;
+    float y1 = (float)x1, y2 = (float)x2;
     float* o;
     if (head < q.H + q.Hkv) {
       double sn, cs;
       sincos((double)pos * inv_freq[i], &sn, &cs);
-      y1 = (float)((double)x1 * cs - (double)x2 * sn);
-      y2 = (float)((double)x2 * cs + (double)x1 * sn);
+      y1 = (float)(x1 * cs - x2 * sn);
+      y2 = (float)(x2 * cs + x1 * sn);
       o = head < q.H ? (float*)q.Q + ((size_t)m * q.H + head) * q.hd
                      : (float*)q.kv.K + (((size_t)s * q.Hkv + (head - q.H)) * q.kv.maxpos + pos) * q.hd;
     } else {
@@ -1001,27 +1062,29 @@ __global__ __launch_bounds__(64 * WM * KW) void k_gemm_qkv_f32(const float* __re
   }
 }
 
-// fp32 LM head: 16 rows x 64 vocabulary columns, 8 waves over K; a wave then
-// takes two rows, a lane a column.
-__global__ __launch_bounds__(512) void k_lm_head_f32(const float* __restrict__ A, int d,
+// fp32 LM head: 16 rows x 64 vocabulary columns; a wave then takes four rows,
+// a lane a column.  The exponentials are summed over columns c, c + 16, c + 32,
+// c + 48 and then over a tree of c.
+__global__ __launch_bounds__(256) void k_lm_head_f32(const float* __restrict__ A, int d,
                                                      const float* __restrict__ W, int mask_id,
                                                      float scale, const int32_t* __restrict__ Mp,
                                                      int rows_cap, float* __restrict__ pmax,
                                                      float* __restrict__ psum,
                                                      int32_t* __restrict__ parg, int V, StepOut so) {
-  constexpr int BM = 16, LD = FHN + 1, KW = 8;
-  __shared__ float red[KW * BM * LD];
+  typedef F32Head G;
   const int M = *Mp;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * FHN;
+  const int m0 = blockIdx.y * G::BM, n0 = blockIdx.x * FHN;
   if (m0 >= M) return;
-  f32_tile<1, 4, 1, KW>(A, d, W, d, d, m0, n0, 16, red);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n = n0 + lane;
+  BD_GEMM_SMEM(G);
+  G t;
+  t.run(ring, A, d, W, d, d, m0, n0, 16);
+  const float* x = t.to_lds(ring);
+  const int lane = t.lane, n = n0 + lane;
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int r = wave * 2 + q, m = m0 + r;
+  for (int q = 0; q < 4; ++q) {
+    const int r = t.wave * 4 + q, m = m0 + r;
     if (m >= M) continue;                                   // wave-uniform
-    const float v = n == mask_id ? -INFINITY : scale * f32_sum<BM, LD, KW>(red, r, lane);
+    const float v = n == mask_id ? -INFINITY : scale * x[r * G::LD + lane];
     if (so.logits) so.logits[so.at(m) * V + n] = v;
     float mx = v;
     int arg = n;
@@ -1031,9 +1094,12 @@ __global__ __launch_bounds__(512) void k_lm_head_f32(const float* __restrict__ A
       const int oa = __shfl_xor(arg, off);
       if (om > mx || (om == mx && oa < arg)) { mx = om; arg = oa; }
     }
-    float s = expf(v - mx);
+    const float p = expf(v - mx);
+    float s = 0.f;
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) s += __shfl_xor(s, off);
+    for (int j = 0; j < 4; ++j) s += __shfl(p, (lane & 15) + 16 * j);
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) s += __shfl_xor(s, off);
     if (lane == 0) {
       const size_t o = (size_t)blockIdx.x * rows_cap + m;
       pmax[o] = mx;
@@ -1254,16 +1320,16 @@ hipError_t launch_gemm(int epi, bool is_bf16, const void* A, int lda, size_t a_p
     return launch_gemm_planned(plan_gemm(true, N, K, rows_cap, false, wq.fmt == WQ_NONE), epi, A, lda, a_plane,
                                W, ldw, N, K, M_dev, rows_cap, out, ldo, out_plane, nullptr, st, wq);
   if (wq.fmt != WQ_NONE) return hipErrorInvalidValue;
-  if (N % FBN || K % FCH || lda % 4 || ldw % 4 || (epi != EPI_ADD_F32 && epi != EPI_SWIGLU)) return hipErrorInvalidValue;
+  if (N % FBN || K % 16 || (epi != EPI_ADD_F32 && epi != EPI_SWIGLU)) return hipErrorInvalidValue;
   const float* a = (const float*)A;
   const float* w = (const float*)W;
-#define BD_F32(FM_, WM_, KW_, EPI_)                                                                                 \
-  k_gemm_f32<FM_, WM_, KW_, EPI_><<<dim3(N / FBN, cdiv(rows_cap, 16 * FM_ * WM_)), 64 * WM_ * KW_, 0, st>>>(a, lda, w, ldw, \
-                                                                                                      K, M_dev, (float*)out, ldo)
+#define BD_F32(G_, EPI_)                                                                                             \
+  k_gemm_f32<G_, EPI_><<<dim3(N / FBN, cdiv(rows_cap, G_::BM)), G_::NT, 0, st>>>(a, lda, w, ldw, K, M_dev, (float*)out, \
+                                                                                 ldo)
   if (f32_large(N, rows_cap)) {
-    if (epi == EPI_ADD_F32) BD_F32(2, 2, 4, EPI_ADD_F32); else BD_F32(2, 2, 4, EPI_SWIGLU);
+    if (epi == EPI_ADD_F32) BD_F32(F32Large, EPI_ADD_F32); else BD_F32(F32Large, EPI_SWIGLU);
   } else {
-    if (epi == EPI_ADD_F32) BD_F32(1, 1, 8, EPI_ADD_F32); else BD_F32(1, 1, 8, EPI_SWIGLU);
+    if (epi == EPI_ADD_F32) BD_F32(F32Small, EPI_ADD_F32); else BD_F32(F32Small, EPI_SWIGLU);
   }
 #undef BD_F32
   return hipGetLastError();
@@ -1272,13 +1338,13 @@ hipError_t launch_gemm(int epi, bool is_bf16, const void* A, int lda, size_t a_p
 hipError_t launch_gemm_qkv_f32(const void* A, int lda, const void* W, int K, const int32_t* M_dev, int rows_cap,
                                const QkvEpi& e, const double* inv_freq, hipStream_t st) {
   const int N = (e.H + 2 * e.Hkv) * e.hd;
-  if (e.hd % FBN || K % FCH || lda % 4) return hipErrorInvalidValue;
-  if (f32_large(N, rows_cap))
-    k_gemm_qkv_f32<2, 2, 4><<<dim3(N / FBN, cdiv(rows_cap, 64)), 512, 0, st>>>((const float*)A, lda, (const float*)W,
-                                                                               K, M_dev, e, inv_freq);
-  else
-    k_gemm_qkv_f32<1, 1, 8><<<dim3(N / FBN, cdiv(rows_cap, 16)), 512, 0, st>>>((const float*)A, lda, (const float*)W,
-                                                                               K, M_dev, e, inv_freq);
+  if (e.hd % FBN || K % 16) return hipErrorInvalidValue;
+  const float* a = (const float*)A;
+  const float* w = (const float*)W;
+#define BD_QKV_F32(G_) \
+  k_gemm_qkv_f32<G_><<<dim3(N / FBN, cdiv(rows_cap, G_::BM)), G_::NT, 0, st>>>(a, lda, w, K, M_dev, e, inv_freq)
+  if (f32_large(N, rows_cap)) BD_QKV_F32(F32Large); else BD_QKV_F32(F32Small);
+#undef BD_QKV_F32
   return hipGetLastError();
 }
 
@@ -1307,10 +1373,10 @@ hipError_t launch_lm_head(bool is_bf16, const void* A, int d, size_t a_plane, co
     }
 #undef BD_HEAD
   } else {
-    if (V % FHN || d % FCH) return hipErrorInvalidValue;
+    if (V % FHN || d % 16) return hipErrorInvalidValue;
     ntiles = V / FHN;
-    dim3 grid(ntiles, cdiv(rows_cap, 16));
-    k_lm_head_f32<<<grid, 512, 0, st>>>((const float*)A, d, (const float*)W, mask_id, scale, M_dev,
+    dim3 grid(ntiles, cdiv(rows_cap, F32Head::BM));
+    k_lm_head_f32<<<grid, F32Head::NT, 0, st>>>((const float*)A, d, (const float*)W, mask_id, scale, M_dev,
                                        rows_cap, part_max, part_sum, part_arg, V, so);
   }
   k_lm_merge<<<cdiv(rows_cap, 4), 256, 0, st>>>(part_max, part_sum, part_arg, ntiles, M_dev, rows_cap,
