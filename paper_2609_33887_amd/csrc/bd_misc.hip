@@ -51,12 +51,18 @@ hipError_t launch_embed(bool is_bf16, const int32_t* tokens, int tok_stride, con
 // ------------------------------------------------------------------ RMSNorm
 // y = x / sqrt(mean(x^2) + eps) * g in fp32.  Output as fp32 (fp32 models)
 // or as the bf16 pair hi = bf16(y), lo = bf16(y - hi) in two planes (bf16
-// models: the matmul operand format).  Rows with d % 256 == 0 and d < 2048
-// are spread over min(256, d / 4) threads, one to four float4 per thread,
-// all loads (x and the pending split partials) in flight at once; the sum of
-// squares is reduced in a fixed order (lane shuffles, then the row's waves).
-// Rows of 2048 to 4096 (d % 256 == 0) take one wave each, 8 to 16 float4 per
-// lane; other widths one wave per row, element by element.
+// models: the matmul operand format).  Pending residual split partials are
+// added to x first (split order), written back.  Three kernels, each row's sum
+// of squares in a fixed order (lane shuffles, then the row's waves):
+//  - k_rmsnorm_rows, d % 256 == 0 and d <= 4096, where the launch covers at
+//    most 256 rows or d < 2048: min(256, d / 4) threads a row, one to four
+//    float4 each, x, the gain and every partial in flight at once.  Few rows
+//    are bound by latency: 96 rows of 2048 with 8 partials took 8.1 us with a
+//    wave a row, 5.6 so; at 512 rows the two are level (7.2 / 6.7).
+//  - k_rmsnorm_wave, 2048 <= d <= 4096 over more rows: a wave a row, which
+//    needs no barrier (3072 rows of 2048: 10.5 us, 4.8 TB/s; 1024 rows with 2
+//    partials 9.9, with threads side by side over a row 12.8).
+//  - k_rmsnorm_any, other widths: a wave a row, element by element.
 __device__ __forceinline__ void put4(void* out, size_t plane, size_t idx, float4 y, bool pair) {
   if (!pair) {
     *(float4*)((float*)out + idx) = y;
@@ -75,133 +81,164 @@ __device__ __forceinline__ void put4(void* out, size_t plane, size_t idx, float4
       make_uint2((uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16));
 }
 
-template <bool PAIR>
-__global__ __launch_bounds__(256) void k_rmsnorm(float* __restrict__ X,
-                                                 const float* __restrict__ g, int d, float eps,
-                                                 const int32_t* __restrict__ Mp,
-                                                 const int32_t* __restrict__ gather,
-                                                 void* __restrict__ out, size_t plane,
-                                                 ResidSplit fold) {
+// Splits pending for X and the stride between their partials.
+__device__ __forceinline__ int fold_splits(const ResidSplit& fold, int d, size_t& zstride) {
+  zstride = 0;
+  if (!fold.ws) return 1;
+  const int Mg = *fold.Mp;
+  zstride = (size_t)((Mg + fold.bm - 1) / fold.bm) * fold.bm * d;
+  return resid_splits(Mg, fold);
+}
+
+__device__ __forceinline__ float4 scaled(float4 v, float inv, float4 g) {
+  return make_float4(v.x * inv * g.x, v.y * inv * g.y, v.z * inv * g.z, v.w * inv * g.w);
+}
+
+template <bool PAIR, int NV>
+__global__ __launch_bounds__(256) void k_rmsnorm_rows(float* __restrict__ X,
+                                                      const float* __restrict__ g, int d, float eps,
+                                                      const int32_t* __restrict__ Mp,
+                                                      const int32_t* __restrict__ gather,
+                                                      void* __restrict__ out, size_t plane,
+                                                      ResidSplit fold) {
   __shared__ float red[4];
-  const int M = *Mp;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // pending residual split partials: x += p_0 + ... + p_{S-1}, written back
-  int S = 1;
-  size_t zstride = 0;
-  if (fold.ws) {
-    const int Mg = *fold.Mp;
-    S = resid_splits(Mg, fold);
-    zstride = (size_t)((Mg + fold.bm - 1) / fold.bm) * fold.bm * d;
-  }
-  if (d % 256 == 0 && d >= 2048 && d <= 4096) {
-    // wide rows: one wave per row, d / 256 float4 per lane (a row's loads all
-    // in flight at once), shuffle-only reduction; split partials added in
-    // split order, each split's loads in flight together (multi-block decode:
-    // 118 -> 91 ms of RMSNorm per decode against a workgroup per row)
-    const int row = blockIdx.x * 4 + wave;
-    if (row >= M) return;
-    const int src = gather ? gather[row] : row;
-    float4* x4 = (float4*)(X + (size_t)src * d);
-    const int nv = d >> 8;                     // 8 .. 16
-    float4 v[16];
+  const int nf = d >> 2, tpr = min(256, nf);   // threads per row: 64, 128, 192 or 256
+  const int rpb = 256 / tpr;
+  const int row = blockIdx.x * rpb + (int)threadIdx.x / tpr;
+  const int t = (int)threadIdx.x % tpr;
+  const float4* g4 = (const float4*)g;
+  // without a gather the row is in X whether it is live or not (the launch
+  // covers the row capacity), so its loads need not wait for the row count
+  const bool in_grid = (int)threadIdx.x < rpb * tpr;
+  float4 v[NV], gg[NV];
+  if (!gather && in_grid) {
+    const float4* x4 = (const float4*)(X + (size_t)row * d);
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
-      if (i < nv) v[i] = x4[lane + 64 * i];
+    for (int i = 0; i < NV; ++i)
+      if (t + i * tpr < nf) v[i] = x4[t + i * tpr];
+  }
+#pragma unroll
+  for (int i = 0; i < NV; ++i)
+    if (t + i * tpr < nf) gg[i] = g4[t + i * tpr];
+  const int M = *Mp;
+  if (blockIdx.x * rpb >= M) return;
+  size_t zstride;
+  const int S = fold_splits(fold, d, zstride);
+  const bool valid = in_grid && row < M;
+  const int src = valid ? (gather ? gather[row] : row) : 0;
+  float4* x4 = (float4*)(X + (size_t)src * d);
+  float ss = 0.f;
+  if (valid) {
+    if (gather) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+        if (t + i * tpr < nf) v[i] = x4[t + i * tpr];
+    }
     if (S > 1) {
       const float4* pz = (const float4*)(fold.ws + (size_t)src * d);
-      for (int z = 0; z < S; ++z) {
+      float4 p[NV][8];
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
-          if (i < nv) {
-            const float4 p = pz[z * (zstride >> 2) + lane + 64 * i];
-            v[i].x += p.x; v[i].y += p.y; v[i].z += p.z; v[i].w += p.w;
+      for (int i = 0; i < NV; ++i)
+#pragma unroll
+        for (int z = 0; z < 8; ++z)
+          if (t + i * tpr < nf && z < S) p[i][z] = pz[z * (zstride >> 2) + t + i * tpr];
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+#pragma unroll
+        for (int z = 0; z < 8; ++z)
+          if (t + i * tpr < nf && z < S) {
+            v[i].x += p[i][z].x; v[i].y += p[i][z].y; v[i].z += p[i][z].z; v[i].w += p[i][z].w;
           }
-      }
 #pragma unroll
-      for (int i = 0; i < 16; ++i)
-        if (i < nv) x4[lane + 64 * i] = v[i];
+      for (int i = 0; i < NV; ++i)
+        if (t + i * tpr < nf) x4[t + i * tpr] = v[i];
     }
-    float ss = 0.f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
-      if (i < nv) ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
-    const float inv = 1.0f / sqrtf(ss / (float)d + eps);
-    const float4* g4 = (const float4*)g;
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-      if (i < nv) {
-        const int c4 = lane + 64 * i;
-        const float4 gg = g4[c4];
-        const float4 y = make_float4(v[i].x * inv * gg.x, v[i].y * inv * gg.y, v[i].z * inv * gg.z,
-                                     v[i].w * inv * gg.w);
-        put4(out, plane, (size_t)row * d + 4 * c4, y, PAIR);
-      }
-    return;
+    for (int i = 0; i < NV; ++i)
+      if (t + i * tpr < nf) ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
   }
-  if (d % 256 == 0 && d <= 4096) {
-    const int tpr = min(256, d >> 2);          // threads per row: 64, 128 or 256
-    const int rpb = 256 / tpr;
-    const int row = blockIdx.x * rpb + (int)threadIdx.x / tpr;
-    const int t = (int)threadIdx.x % tpr;
-    const int nv = (d >> 2) / tpr;             // float4 per thread, <= 4
-    const bool valid = row < M;
-    const int src = valid ? (gather ? gather[row] : row) : 0;
-    float4* x4 = (float4*)(X + (size_t)src * d);
-    float4 v[4];
-    float ss = 0.f;
-    if (valid) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (i < nv) v[i] = x4[t + i * tpr];
-      if (S > 1) {
-        const float4* pz = (const float4*)(fold.ws + (size_t)src * d);
-        float4 p[4][8];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int z = 0; z < 8; ++z)
-            if (i < nv && z < S) p[i][z] = pz[z * (zstride >> 2) + t + i * tpr];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int z = 0; z < 8; ++z)
-            if (i < nv && z < S) {
-              v[i].x += p[i][z].x; v[i].y += p[i][z].y; v[i].z += p[i][z].z; v[i].w += p[i][z].w;
-            }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (i < nv) x4[t + i * tpr] = v[i];
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (i < nv) ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
-    const int wpr = tpr >> 6;                  // waves per row
-    if (wpr > 1) {
-      if (lane == 0) red[wave] = ss;
-      __syncthreads();
-      const int w0 = (wave / wpr) * wpr;
-      ss = 0.f;
-      for (int w = 0; w < wpr; ++w) ss += red[w0 + w];
-    }
-    if (!valid) return;
-    const float inv = 1.0f / sqrtf(ss / (float)d + eps);
-    const float4* g4 = (const float4*)g;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (i < nv) {
-        const int c4 = t + i * tpr;
-        const float4 gg = g4[c4];
-        const float4 y = make_float4(v[i].x * inv * gg.x, v[i].y * inv * gg.y, v[i].z * inv * gg.z,
-                                     v[i].w * inv * gg.w);
-        put4(out, plane, (size_t)row * d + 4 * c4, y, PAIR);
-      }
-    return;
+  for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
+  const int wpr = tpr >> 6;                    // waves per row
+  if (wpr > 1) {
+    if (lane == 0) red[wave] = ss;
+    __syncthreads();
+    const int w0 = (wave / wpr) * wpr;
+    ss = 0.f;
+    for (int w = w0; w < min(w0 + wpr, 4); ++w) ss += red[w];
   }
+  if (!valid) return;
+  const float inv = 1.0f / sqrtf(ss / (float)d + eps);
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int c4 = t + i * tpr;
+    if (c4 < nf) put4(out, plane, (size_t)row * d + 4 * c4, scaled(v[i], inv, gg[i]), PAIR);
+  }
+}
+
+// NV >= d / 256 float4 per lane.  At most two waves a SIMD, so that the
+// compiler keeps a row's loads, and one split's partials, in flight together.
+template <bool PAIR, int NV>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3)))
+void k_rmsnorm_wave(float* __restrict__ X, const float* __restrict__ g, int d, float eps,
+                    const int32_t* __restrict__ Mp, const int32_t* __restrict__ gather,
+                    void* __restrict__ out, size_t plane, ResidSplit fold) {
+  const int M = *Mp;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int row = blockIdx.x * 4 + wave;
+  if (row >= M) return;
+  const int src = gather ? gather[row] : row;
+  float4* x4 = (float4*)(X + (size_t)src * d);
+  const int nv = NV == 8 ? 8 : d >> 8;         // 8 .. 16
+  float4 v[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i)
+    if (i < nv) v[i] = x4[lane + 64 * i];
+  size_t zstride;
+  const int S = fold_splits(fold, d, zstride);
+  if (S > 1) {
+    const float4* pz = (const float4*)(fold.ws + (size_t)src * d);
+    for (int z = 0; z < S; ++z) {
+      float4 p[NV];
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+        if (i < nv) p[i] = pz[z * (zstride >> 2) + lane + 64 * i];
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+        if (i < nv) { v[i].x += p[i].x; v[i].y += p[i].y; v[i].z += p[i].z; v[i].w += p[i].w; }
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+      if (i < nv) x4[lane + 64 * i] = v[i];
+  }
+  float ss = 0.f;
+#pragma unroll
+  for (int i = 0; i < NV; ++i)
+    if (i < nv) ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
+  const float inv = 1.0f / sqrtf(ss / (float)d + eps);
+  const float4* g4 = (const float4*)g;
+#pragma unroll
+  for (int i = 0; i < NV; ++i)
+    if (i < nv) {
+      const int c4 = lane + 64 * i;
+      put4(out, plane, (size_t)row * d + 4 * c4, scaled(v[i], inv, g4[c4]), PAIR);
+    }
+}
+
+template <bool PAIR>
+__global__ __launch_bounds__(256) void k_rmsnorm_any(float* __restrict__ X,
+                                                     const float* __restrict__ g, int d, float eps,
+                                                     const int32_t* __restrict__ Mp,
+                                                     const int32_t* __restrict__ gather,
+                                                     void* __restrict__ out, size_t plane,
+                                                     ResidSplit fold) {
+  const int M = *Mp;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  size_t zstride;
+  const int S = fold_splits(fold, d, zstride);
   const int row = blockIdx.x * 4 + wave;
   if (row >= M) return;
   const int src = gather ? gather[row] : row;
@@ -230,17 +267,32 @@ __global__ __launch_bounds__(256) void k_rmsnorm(float* __restrict__ X,
   }
 }
 
+template <bool PAIR>
+static void launch_rmsnorm_as(float* X, const float* g, int d, float eps, const int32_t* M_dev, const int32_t* gather,
+                              int rows_cap, void* out, size_t plane, const ResidSplit& fold, hipStream_t st) {
+  const int b4 = (rows_cap + 3) / 4;
+  if (d % 256 || d > 4096) {
+    k_rmsnorm_any<PAIR><<<b4, 256, 0, st>>>(X, g, d, eps, M_dev, gather, out, plane, fold);
+  } else if (d >= 2048 && rows_cap > 256) {
+    if (d == 2048) k_rmsnorm_wave<PAIR, 8><<<b4, 256, 0, st>>>(X, g, d, eps, M_dev, gather, out, plane, fold);
+    else k_rmsnorm_wave<PAIR, 16><<<b4, 256, 0, st>>>(X, g, d, eps, M_dev, gather, out, plane, fold);
+  } else {
+    const int rpb = 256 / min(256, d >> 2);
+    const int blocks = (rows_cap + rpb - 1) / rpb;
+    if (d <= 1024)
+      k_rmsnorm_rows<PAIR, 1><<<blocks, 256, 0, st>>>(X, g, d, eps, M_dev, gather, out, plane, fold);
+    else if (d <= 2048)
+      k_rmsnorm_rows<PAIR, 2><<<blocks, 256, 0, st>>>(X, g, d, eps, M_dev, gather, out, plane, fold);
+    else
+      k_rmsnorm_rows<PAIR, 4><<<blocks, 256, 0, st>>>(X, g, d, eps, M_dev, gather, out, plane, fold);
+  }
+}
+
 hipError_t launch_rmsnorm(bool is_bf16, float* X, const float* g, int d, float eps,
                           const int32_t* M_dev, const int32_t* gather, int rows_cap, void* out,
                           size_t out_plane, const ResidSplit& fold, hipStream_t st) {
-  // rows per block: 4 (a wave per row) for wide rows and widths off the
-  // float4 paths, else 256 threads over 256 / (d / 4) rows
-  const int rpb = (d % 256 == 0 && d < 2048) ? 256 / min(256, d >> 2) : 4;
-  const int blocks = (rows_cap + rpb - 1) / rpb;
-  if (is_bf16)
-    k_rmsnorm<true><<<blocks, 256, 0, st>>>(X, g, d, eps, M_dev, gather, out, out_plane, fold);
-  else
-    k_rmsnorm<false><<<blocks, 256, 0, st>>>(X, g, d, eps, M_dev, gather, out, 0, fold);
+  if (is_bf16) launch_rmsnorm_as<true>(X, g, d, eps, M_dev, gather, rows_cap, out, out_plane, fold, st);
+  else launch_rmsnorm_as<false>(X, g, d, eps, M_dev, gather, rows_cap, out, 0, fold, st);
   return hipGetLastError();
 }
 

@@ -38,3 +38,50 @@ F32 = [
 @pytest.mark.parametrize("w", F32, ids=lambda w: w.name)
 def test_f32_tiles_and_keys(w):
     check(w)
+
+
+NORM = [
+    # RMSNorm widths: below and off the float4 paths (d 384: not a multiple of 256), 1280 (two partly filled float4
+    # a thread), 2048 and 2304 over few rows (threads side by side) and, from 257 rows on, a wave a row (8 float4 a
+    # lane, and 9 of 16); the O and down products leave split partials to fold
+    small("v_norm_384", seed=130, d_model=384, n_heads=3, n_kv_heads=3, head_dim=128, ffn_dim=1024, batch=2),
+    small("v_norm_1280", seed=131, d_model=1280, n_heads=4, n_kv_heads=4, head_dim=64, ffn_dim=1024, batch=2),
+    small("v_norm_2048", seed=132, d_model=2048, n_heads=4, n_kv_heads=2, head_dim=128, ffn_dim=4096, batch=1,
+          n_layers=1, prompt_len=16, gen_len=32),
+    small("v_norm_2048w", seed=133, d_model=2048, n_heads=4, n_kv_heads=2, head_dim=128, ffn_dim=1024, batch=5,
+          n_layers=1, prompt_len=96, gen_len=32),
+    small("v_norm_2304w", seed=134, d_model=2304, n_heads=4, n_kv_heads=2, head_dim=128, ffn_dim=512, batch=5,
+          n_layers=1, prompt_len=96, gen_len=32),
+]
+
+
+@pytest.mark.parametrize("w", NORM, ids=lambda w: w.name)
+def test_rmsnorm_widths(w):
+    check(w)
+
+
+TILES = [
+    # one 128-deep K of two 64-deep stages (fewer than the ring holds) and depths of 3, 4 and 5 pairs of stages
+    # (every tail of the three- and four-stage rings), single live rows and row remainders
+    small("v_tile_k128", seed=140, d_model=128, n_heads=2, n_kv_heads=1, head_dim=64, ffn_dim=128, vocab=256, batch=1,
+          prompt_len=1, block_size=1, n_inflight=1, gen_len=4),
+    small("v_tile_k384", seed=141, d_model=384, n_heads=6, n_kv_heads=3, head_dim=64, ffn_dim=640, vocab=384, batch=3,
+          prompt_len=51, block_size=17, n_inflight=1, gen_len=34),
+    # QKV, O and head over 65 and 129 live rows of 64- and 128-row tiles (positions off multiples of 32: the V store's
+    # shorter runs), hd 64 and 128
+    small("v_tile_rows", seed=142, n_heads=4, n_kv_heads=2, head_dim=128, batch=3, prompt_len=43, block_size=43,
+          n_inflight=1, gen_len=86),
+    small("v_tile_rows64", seed=143, n_heads=8, n_kv_heads=4, head_dim=64, batch=13, prompt_len=15, block_size=5,
+          n_inflight=2, gen_len=20),
+]
+
+
+@pytest.mark.parametrize("w", TILES, ids=lambda w: w.name)
+def test_gemm_tiles(w):
+    check(w)
+
+
+@pytest.mark.parametrize("wq", ["fp8", "mxfp4"])
+@pytest.mark.parametrize("w", TILES[:3], ids=lambda w: w.name)
+def test_gemm_tiles_quantized(w, wq):
+    check(w, wq=wq)
