@@ -521,7 +521,7 @@ static bd_status run_forward(bd_model* m, bd_state* s, const PlanView& plan, int
     else
       LAUNCH(BD_PROF_GEMM_QKV, launch_gemm_qkv_f32(s->A, d, L.w_qkv, d, plan.hdr, rows_cap, e, m->inv_freq, st));
     LAUNCH(BD_PROF_ATTN, launch_attention(bf, s->Qb, q_plane, kv,
-                                          s->Ob, s->pl_O, plan, s->b, win_cap, H, Hkv, hd, s->B,
+                                          s->Ob, s->pl_O, plan, s->b, win_cap, lm ? s->nb * s->B : win_cap, H, Hkv, hd, s->B,
                                           kv_splits, s->attn_ws_o, s->attn_ws_ml, rows_cap, st));
     LAUNCH(BD_PROF_GEMM_O, launch_gemm_resid(bf, s->Ob, H * hd, s->pl_O, L.w_o, H * hd, d, H * hd,
                                              plan.hdr, rows_cap, s->X, d, s->resid_ws, s->resid_ws_floats, &pend, st,
@@ -749,7 +749,7 @@ static bd_status state_layout(const bd_model* m, int32_t b, int32_t P, int32_t G
     s->pl_act = assign_cap * Fe;
     ALLOC(s->y_sorted, assign_cap * d * 4);
   }
-  s->attn_splits = m->bf16 ? attention_splits(b, s->win_step, nb * B, H, Hkv, hd, s->maxpos) : 1;
+  s->attn_splits = m->bf16 ? attention_splits(b, nb * B, H, Hkv, s->maxpos) : 1;
   if (s->attn_splits > 1) {
     ALLOC(s->attn_ws_o, (size_t)s->attn_splits * s->rows_step * H * hd * 4);
     ALLOC(s->attn_ws_ml, (size_t)s->attn_splits * s->rows_step * H * 2 * 4);

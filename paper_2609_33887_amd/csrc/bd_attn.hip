@@ -5,22 +5,26 @@
 // so one key range [0, end of the query's block) covers prefix and window.
 //
 // bf16 kernel (Q, K and V are bf16 hi/lo pairs in two planes; V is kept
-// transposed in the cache, in tiles of 64 keys [dim][64 slots], the keys of
-// each 32-key group in the slot order of vt_slot): one workgroup =
-// 16 NW queries of one (sequence, kv head) -- window rows x the q-heads that
-// share the kv head -- as NW wave64s x 16 queries (NW = 2 when a window
-// holds at most 32 such queries, 8 for 512 or more over long key ranges,
-// else 4); a wave with no query of its own
-// only helps stage the tiles.  Key tiles of 64
-// positions stream from HBM through LDS with 16-byte coalesced loads (K rows
-// and V^T tile rows, each tile a contiguous block), and the wave computes
-// S^T = K Q^T and O^T += V^T P^T with MFMA 16x16x32 bf16 (three products
+// transposed in the cache, in tiles of 32 keys [dim][32 slots] in the slot
+// order of vt_slot).  The queries of one (sequence, kv head) are its window
+// rows x the q-heads that share the kv head; a wave takes 32 of them, a
+// workgroup QW x KW waves: QW groups of 32 queries, the keys of every stage
+// dealt to KW waves of each group.  A wave computes S^T = K Q^T and
+// O^T += V^T P^T on tiles of 32 keys with MFMA 32x32x16 bf16 (three products
 // hi.hi + hi.lo + lo.hi per pair of operands; the output leaves as the hi/lo
-// pair of the next matmul operand), so each lane owns one query column: the
-// online-softmax state and the O rescale stay in the lane, and P^T is fed to
-// the second MFMA straight from the score registers (the two products use
-// the same permutation of the key index).  The block mask is applied in
-// registers, only on tiles that reach the query's block.
+// pair of the next matmul operand), so each lane owns one query column and half
+// of a tile's keys: softmax state and rescale stay in the lane (one exchange
+// with lane ^ 32 per tile), and P^T is fed to the second MFMA straight from
+// the score registers (the two products use the same permutation of the key
+// index).  32 queries a wave are what keeps the kernel off the LDS bandwidth:
+// every K or V fragment read from LDS serves 32 columns, 2 KiB of LDS reads per
+// three MFMAs of 32 cycles; with 16 queries a wave and 16x16x32 MFMAs the reads
+// took a third longer than the products they fed, and the softmax twice the
+// vector instructions per score.
+// Stages of 32 KW keys stream from HBM straight into LDS (two stages; buffer
+// loads, no registers), the next one while a stage is consumed, one barrier a
+// stage.  The block mask is applied in registers, only on tiles that reach the
+// query's block.
 #include "bd_internal.h"
 
 #include <math.h>
@@ -34,13 +38,15 @@ __device__ __forceinline__ bf16_t f2bf_a(float f) {
   return (bf16_t)(u >> 16);
 }
 
-constexpr int AK = 64;    // keys per tile
+constexpr int AK = 32;    // keys per tile
 // Fourth word of a raw buffer resource (gfx9 family): 32-bit data format (a
 // zero format reads zeros), no index stride.
 constexpr int ATT_BUF_DWORD3 = 0x00020000;
 
 typedef __bf16 bf16x2_a __attribute__((ext_vector_type(2)));
 typedef float floatx2_a __attribute__((ext_vector_type(2)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef __attribute__((address_space(3))) void att_lds_t;
 
 // (x0, x1) -> the hi bf16 pair (round to nearest even, one v_cvt_pk_bf16_f32)
 // in hi and the lo pair, the rounded remainders x - hi (exact in fp32), in lo
@@ -50,29 +56,42 @@ __device__ __forceinline__ void split_pair2(float x0, float x1, uint32_t& hi, ui
   lo = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2_a){x0 - h0, x1 - h1}, bf16x2_a));
 }
 
-template <int HD, int NW>
-__global__ __launch_bounds__(64 * NW) void k_attn_bf16(const bf16_t* __restrict__ Q, size_t q_plane,
-                                                   const bf16_t* __restrict__ Kc, size_t k_plane,
-                                                   const bf16_t* __restrict__ Vt, size_t v_plane,
-                                                   int vstride, bf16_t* __restrict__ O,
-                                                   size_t o_plane,
-                                                   const int32_t* __restrict__ seq_row_start,
-                                                   const int32_t* __restrict__ seq_win_len,
-                                                   const int32_t* __restrict__ seq_win_start, int H,
-                                                   int Hkv, int maxpos, int B, float scale_log2,
-                                                   int kv_splits, float* __restrict__ ws_o,
-                                                   float* __restrict__ ws_ml, int rows_cap,
-                                                   int b, int nqt) {
-  constexpr int KP = HD + 8;        // padded K row (elements)
-  constexpr int VP = AK + 8;        // padded transposed-V row
-  constexpr int CH = AK * HD / 8;   // 16-byte chunks per K (or V) tile and plane
-  constexpr int NT = 64 * NW;       // threads
-  constexpr int AQ = 16 * NW;       // queries per workgroup
-  constexpr int NCH = CH / NT;      // chunks per thread
-  __shared__ __attribute__((aligned(16))) bf16_t sKh[AK * KP];
-  __shared__ __attribute__((aligned(16))) bf16_t sKl[AK * KP];
-  __shared__ __attribute__((aligned(16))) bf16_t sVh[HD * VP];
-  __shared__ __attribute__((aligned(16))) bf16_t sVl[HD * VP];
+__device__ __forceinline__ void att_load_lds(__amdgpu_buffer_rsrc_t r, void* lds, uint32_t off, uint32_t soff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (att_lds_t*)lds, 16, off, soff, 0, 0);
+}
+
+// K: [plane][key][HD], 16-byte chunk c of key r at c ^ k_swz(r); V:
+// [plane][tile][dim][32 slots], chunk c of dim r at c ^ v_swz(r).  A 16-byte
+// LDS read serves lanes 0-3, 12-15 and 20-27 together, then 4-11, 16-19 and
+// 28-31, and so on 32 lanes up; rows being lanes, each such set of 16 meets 16
+// distinct 16-byte columns of the 256 bytes that the banks span (the
+// bank-conflict counter reads zero; with r & 7 and (r >> 1) & 3 it read half
+// the active cycles).
+template <int HD>
+__device__ __forceinline__ int k_swz(int r) { return HD == 128 ? (r & 15) : ((r >> 1) & 7); }
+__device__ __forceinline__ int v_swz(int r) { return (r >> 2) & 3; }
+template <int HD, int KW>
+struct AttStage {
+  bf16_t k[2][KW * AK * HD];
+  bf16_t v[2][KW * AK * HD];
+};
+
+template <int HD, int QW, int KW>
+__global__ __launch_bounds__(64 * QW * KW) __attribute__((amdgpu_waves_per_eu(KW == 1 ? 2 : 1, 2)))
+void k_attn_bf16(const bf16_t* __restrict__ Q, size_t q_plane, const bf16_t* __restrict__ Kc, size_t k_plane,
+                 const bf16_t* __restrict__ Vt, size_t v_plane, int vstride, bf16_t* __restrict__ O, size_t o_plane,
+                 const int32_t* __restrict__ seq_row_start, const int32_t* __restrict__ seq_win_len,
+                 const int32_t* __restrict__ seq_win_start, int H, int Hkv, int maxpos, int B, float scale_log2,
+                 int kv_splits, float* __restrict__ ws_o, float* __restrict__ ws_ml, int rows_cap, int b) {
+  constexpr int NW = QW * KW;
+  constexpr int AQ = 32 * QW;             // queries per workgroup
+  constexpr int SK = AK * KW;             // keys per stage
+  constexpr int KCH = HD / 8;             // 16-byte chunks of a K row
+  constexpr int LP = HD / 16 / QW;        // 1 KiB loads per wave, stage, operand and plane
+  constexpr int NS = HD / 16;             // MFMA depths of the score product
+  static_assert(LP >= 1, "every wave loads");
+  typedef AttStage<HD, KW> Stage;
+  __shared__ __attribute__((aligned(1024))) Stage st0, st1;
 
   // The queries of one (sequence s, kv head kv) are numbered qi = r * G + j
   // for window row r and q-head kv * G + j (G = H / Hkv heads share the kv
@@ -80,232 +99,295 @@ __global__ __launch_bounds__(64 * NW) void k_attn_bf16(const bf16_t* __restrict_
   // serves all G heads of the rows it covers.
   // Items u = ((s * Hkv + kv) * kv_splits + split) * nqt + qt: the nqt query
   // tiles that read the same keys are neighbours, so they share one XCD's L2.
+  // nqt is counted from the longest window alive and not from the launch's
+  // capacity (usually twice that): tiles without queries would otherwise stand
+  // between the others and hold a CU's LDS until they have found out.
+  // The windows' lengths, first rows and positions come in one round of loads,
+  // one sequence a lane; past 64 sequences the workgroup reads its own again.
   const int G = H / Hkv;
+  const int wl = threadIdx.x & 63;
+  int nqt = 0, w_len = 0, w_row = 0, w_start = 0;
+  if (wl < b) {
+    nqt = w_len = seq_win_len[wl];
+    w_row = seq_row_start[wl];
+    w_start = seq_win_start[wl];
+  }
+  for (int i = wl + 64; i < b; i += 64) nqt = max(nqt, seq_win_len[i]);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) nqt = max(nqt, __shfl_xor(nqt, off));
+  nqt = __builtin_amdgcn_readfirstlane((G * nqt + AQ - 1) / AQ);
+  if (nqt == 0) return;
   const int items = b * Hkv * kv_splits * nqt;
   const int u = xcd_item(blockIdx.x, items);
   if (u >= items) return;
   const int qt = u % nqt, split = (u / nqt) % kv_splits;
   const int kv = (u / (nqt * kv_splits)) % Hkv, s = u / (nqt * kv_splits * Hkv);
-  const int W = seq_win_len[s];
+  const int W = s < 64 ? __builtin_amdgcn_readlane(w_len, s) : seq_win_len[s];
+  const int row_start = s < 64 ? __builtin_amdgcn_readlane(w_row, s) : seq_row_start[s];
+  const int win_start = s < 64 ? __builtin_amdgcn_readlane(w_start, s) : seq_win_start[s];
   const int QG = G * W;
   if (qt * AQ >= QG) return;
-  const int row_start = seq_row_start[s], win_start = seq_win_start[s];
   const int qlast = min(qt * AQ + AQ, QG) - 1;
   const int kend = ((win_start + qlast / G) / B + 1) * B;   // keys [0, kend): the last row's bound
-  // this split's key tiles: a contiguous, tile-aligned share of [0, kend)
-  const int ntiles_all = (kend + AK - 1) / AK;
-  const int per = (ntiles_all + kv_splits - 1) / kv_splits;
-  const int t_lo = split * per, t_hi = min(ntiles_all, t_lo + per);
+  // this split's stages: a contiguous share of [0, kend)
+  const int nst_all = (kend + SK - 1) / SK;
+  const int per = (nst_all + kv_splits - 1) / kv_splits;
+  const int t_lo = __builtin_amdgcn_readfirstlane(split * per);
+  const int t_hi = __builtin_amdgcn_readfirstlane(min(nst_all, t_lo + per));
   const bf16_t* Kp = Kc + ((size_t)s * Hkv + kv) * (size_t)maxpos * HD;
   const bf16_t* Vp = Vt + ((size_t)s * Hkv + kv) * (size_t)HD * vstride;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int g = lane >> 4, c = lane & 15;
-  const int qi = qt * AQ + wave * 16 + c;                    // this lane's query
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int qw = wave % QW, kw = wave / QW;
+  const int h = lane >> 5, c = lane & 31;
+  const int q0w = qt * AQ + qw * 32;                        // the wave's first query
+  const int qi = q0w + c;                                   // this lane's query
   const bool qvalid = qi < QG;
-  const bool wave_on = qt * AQ + wave * 16 < QG;             // the wave holds a query
-  const int qrow = row_start + (qvalid ? qi / G : 0);        // its row in the step
-  const int h = kv * G + (qvalid ? qi % G : 0);              // its q-head
+  const bool wave_on = q0w < QG;                            // the wave holds a query
+  const int qrow = row_start + (qvalid ? qi / G : 0);       // its row in the step
+  const int hq = kv * G + (qvalid ? qi % G : 0);            // its q-head
   const int qend = ((win_start + (qvalid ? qi / G : 0)) / B + 1) * B;   // its key bound
-  // the wave's smallest key bound (query index and bound rise together) and
-  // whether every lane holds a query: tiles below the bound skip the mask
-  const int q0w = qt * AQ + wave * 16;
-  const int qend_w = ((win_start + min(q0w, QG - 1) / G) / B + 1) * B;
-  const bool full_w = q0w + 16 <= QG;
+  // the wave's smallest and largest key bound (query index and bound rise
+  // together) and whether every lane holds a query: tiles below the smallest
+  // skip the mask, tiles from the largest on are skipped
+  const int qend_lo = ((win_start + min(q0w, QG - 1) / G) / B + 1) * B;
+  const int qend_hi = ((win_start + min(q0w + 31, QG - 1) / G) / B + 1) * B;
+  const bool full_w = q0w + 32 <= QG;
 
-  // Q^T fragments (B operand of S^T = K Q^T): dims [32 kc + 8 g, +8) of query c,
-  // hi and lo halves.
-  bf16x8 qh[HD / 32], ql[HD / 32];
+  floatx16 oacc[HD / 32];
 #pragma unroll
-  for (int kc = 0; kc < HD / 32; ++kc) {
-    if (qvalid) {
-      const bf16_t* qp = Q + ((size_t)qrow * H + h) * HD + kc * 32 + g * 8;
-      qh[kc] = __builtin_bit_cast(bf16x8, *(const u32x4*)qp);
-      ql[kc] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qp + q_plane));
-    } else {
-      qh[kc] = bf16x8{};
-      ql[kc] = bf16x8{};
-    }
-  }
-  floatx4 oacc[HD / 16];
-#pragma unroll
-  for (int t = 0; t < HD / 16; ++t) oacc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < HD / 32; ++t) oacc[t] = floatx16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
+                                                       0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY, l_part = 0.f;
 
-  // register prefetch of the next K/V tile (both planes) overlaps the loads
-  // with the MFMAs of the current tile.  K: chunk ci = (key, 8 dims), read
-  // through a buffer resource that starts at the tile's first key and ends
-  // at key kend, so keys >= kend (past the slice's written rows, possibly
-  // past the slice) read zeros, finite scores that every query masks.  V^T:
-  // chunk ci = (dim, 8 keys) of the tile's [HD][64] block; a tile never
-  // reaches past vstride and the keys past kend there are finite cache
-  // contents that meet zero probabilities.  The lanes' byte offsets inside a
-  // tile do not change from tile to tile.
-  u32x4 pkh[NCH], pkl[NCH], pvh[NCH], pvl[NCH];
-  uint32_t kof[NCH], vof[NCH];
+  // Stage loads: load n of an operand's plane fills its bytes [1024 n, +1024).
+  // K rows past the bound repeat row kend - 1 and V tiles past it the last one
+  // (finite values; every query masks those keys).
+  const __amdgpu_buffer_rsrc_t rkh = __builtin_amdgcn_make_buffer_rsrc((void*)Kp, 0, -1, ATT_BUF_DWORD3);
+  const __amdgpu_buffer_rsrc_t rkl = __builtin_amdgcn_make_buffer_rsrc((void*)(Kp + k_plane), 0, -1, ATT_BUF_DWORD3);
+  const __amdgpu_buffer_rsrc_t rvh = __builtin_amdgcn_make_buffer_rsrc((void*)Vp, 0, -1, ATT_BUF_DWORD3);
+  const __amdgpu_buffer_rsrc_t rvl = __builtin_amdgcn_make_buffer_rsrc((void*)(Vp + v_plane), 0, -1, ATT_BUF_DWORD3);
+  int krow[LP], vtile[LP];
+  uint32_t kchunk[LP], vin[LP];
 #pragma unroll
-  for (int it = 0; it < NCH; ++it) {
-    const int ci = tid + NT * it;
-    kof[it] = (uint32_t)((ci / (HD / 8)) * HD + (ci % (HD / 8)) * 8) * 2u;
-    vof[it] = (uint32_t)((ci / (AK / 8)) * AK + (ci % (AK / 8)) * 8) * 2u;
+  for (int i = 0; i < LP; ++i) {
+    const int n = i * NW + wave;
+    krow[i] = n * (64 / KCH) + lane / KCH;
+    kchunk[i] = (uint32_t)(((lane % KCH) ^ k_swz<HD>(krow[i])) * 16);
+    vtile[i] = n / (HD / 16);
+    const int dim = (n % (HD / 16)) * 16 + (lane >> 2);
+    vin[i] = (uint32_t)(dim * (AK * 2) + ((lane & 3) ^ v_swz(dim)) * 16);
   }
-#define BD_FETCH(K0)                                                                              \
-  do {                                                                                            \
-    const bf16_t* kb_ = Kp + (size_t)(K0) * HD;                                                   \
-    const bf16_t* vb_ = Vp + (size_t)(K0) * HD;                                                   \
-    const int nrec_ = max(kend - (K0), 0) * HD * 2;                                               \
-    const __amdgpu_buffer_rsrc_t rkh_ = __builtin_amdgcn_make_buffer_rsrc((void*)kb_, 0, nrec_, ATT_BUF_DWORD3); \
-    const __amdgpu_buffer_rsrc_t rkl_ =                                                           \
-        __builtin_amdgcn_make_buffer_rsrc((void*)(kb_ + k_plane), 0, nrec_, ATT_BUF_DWORD3);      \
-    const __amdgpu_buffer_rsrc_t rvh_ = __builtin_amdgcn_make_buffer_rsrc((void*)vb_, 0, AK * HD * 2, ATT_BUF_DWORD3); \
-    const __amdgpu_buffer_rsrc_t rvl_ =                                                           \
-        __builtin_amdgcn_make_buffer_rsrc((void*)(vb_ + v_plane), 0, AK * HD * 2, ATT_BUF_DWORD3); \
-    _Pragma("unroll") for (int it = 0; it < NCH; ++it) {                                          \
-      pkh[it] = __builtin_amdgcn_raw_buffer_load_b128(rkh_, kof[it], 0, 0);                       \
-      pkl[it] = __builtin_amdgcn_raw_buffer_load_b128(rkl_, kof[it], 0, 0);                       \
-      pvh[it] = __builtin_amdgcn_raw_buffer_load_b128(rvh_, vof[it], 0, 0);                       \
-      pvl[it] = __builtin_amdgcn_raw_buffer_load_b128(rvl_, vof[it], 0, 0);                       \
-    }                                                                                             \
-  } while (0)
-  if (t_lo < t_hi) BD_FETCH(t_lo * AK);
-  for (int kt = t_lo; kt < t_hi; ++kt) {
-    const int k0 = kt * AK;
-    // stage K (row-major) and V^T
+  auto issue = [&](Stage& sg, int t) {
+    const int left = kend - 1 - t * SK;                     // last key of the range, from the stage's start
+    const uint32_t so = (uint32_t)t * (SK * HD * 2);
 #pragma unroll
-    for (int it = 0; it < NCH; ++it) {
-      const int ci = tid + NT * it;
-      const int key = ci / (HD / 8), dc = (ci % (HD / 8)) * 8;
-      *(u32x4*)(sKh + key * KP + dc) = pkh[it];
-      *(u32x4*)(sKl + key * KP + dc) = pkl[it];
-      const int dim = ci / (AK / 8), kc8 = (ci % (AK / 8)) * 8;
-      *(u32x4*)(sVh + dim * VP + kc8) = pvh[it];
-      *(u32x4*)(sVl + dim * VP + kc8) = pvl[it];
+    for (int i = 0; i < LP; ++i) {
+      const int n = i * NW + wave;
+      const uint32_t ko = (uint32_t)min(krow[i], left) * (HD * 2) + kchunk[i];
+      const uint32_t vo = (uint32_t)min(vtile[i], left / AK) * (HD * AK * 2) + vin[i];
+      att_load_lds(rkh, sg.k[0] + n * 512, ko, so);
+      att_load_lds(rkl, sg.k[1] + n * 512, ko, so);
+      att_load_lds(rvh, sg.v[0] + n * 512, vo, so);
+      att_load_lds(rvl, sg.v[1] + n * 512, vo, so);
     }
-    __syncthreads();
-    if (kt + 1 < t_hi) BD_FETCH(k0 + AK);
-    if (wave_on) {
-
-    // S^T sub-tiles (keys st*16 + 4g + r, query c): Kh.Qh + Kh.Ql + Kl.Qh
-    float sv[4][4];
+  };
+  if (t_lo < t_hi) {
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    issue(st0, t_lo);
+  }
+  // Q^T fragments (B operand of S^T = K Q^T): dims [16 x + 8 h, +8) of query c,
+  // hi and lo halves (lanes without a query read the window's first and mask
+  // every key)
+  bf16x8 qh[NS], ql[NS];
+  const bf16_t* qp = Q + ((size_t)qrow * H + hq) * HD + h * 8;
 #pragma unroll
-    for (int st = 0; st < 4; ++st) {
-      floatx4 a = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int x = 0; x < NS; ++x) {
+    qh[x] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qp + x * 16));
+    ql[x] = __builtin_bit_cast(bf16x8, *(const u32x4*)(qp + q_plane + x * 16));
+  }
+  const int ksw = k_swz<HD>(c), vsw = v_swz(c);
+  auto compute = [&](const Stage& sg, int t) {
+    const int k0 = t * SK + kw * AK;                        // the wave's tile
+    if (!wave_on || k0 >= qend_hi) return;
+    // S^T (keys k0 + 8 (i >> 2) + 4 h + (i & 3), query c): Kh.Qh + Kh.Ql + Kl.Qh
+    const bf16_t* kh_ = sg.k[0] + (kw * AK + c) * HD;
+    const bf16_t* kl_ = sg.k[1] + (kw * AK + c) * HD;
+    floatx16 a = floatx16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int kc = 0; kc < HD / 32; ++kc) {
-        const int off = (st * 16 + c) * KP + kc * 32 + g * 8;
-        const bf16x8 kh = __builtin_bit_cast(bf16x8, *(const u32x4*)(sKh + off));
-        const bf16x8 kl = __builtin_bit_cast(bf16x8, *(const u32x4*)(sKl + off));
-        a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kh, qh[kc], a, 0, 0, 0);
-        a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kh, ql[kc], a, 0, 0, 0);
-        a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kl, qh[kc], a, 0, 0, 0);
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) sv[st][r] = a[r];
+    for (int x = 0; x < NS; ++x) {
+      const int off = ((2 * x + h) ^ ksw) * 8;
+      const bf16x8 kh = __builtin_bit_cast(bf16x8, *(const u32x4*)(kh_ + off));
+      const bf16x8 kl = __builtin_bit_cast(bf16x8, *(const u32x4*)(kl_ + off));
+      a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, qh[x], a, 0, 0, 0);
+      a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, ql[x], a, 0, 0, 0);
+      a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kl, qh[x], a, 0, 0, 0);
     }
-    // In this lane, score (st, r) belongs to key k0 + st*16 + 4g + r of query c.
     // Scores stay unscaled until the exponent: the max of the raw scores
     // times the (positive) scale is the max of the scaled ones.  The mask
     // branch is wave-uniform.
-    if (k0 + AK > qend_w || !full_w) {
+    if (k0 + AK > qend_lo || !full_w) {
 #pragma unroll
-      for (int st = 0; st < 4; ++st)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int key = k0 + st * 16 + 4 * g + r;
-          if (!qvalid || key >= qend) sv[st][r] = -INFINITY;
-        }
+      for (int i = 0; i < 16; ++i) {
+        const int key = k0 + 8 * (i >> 2) + 4 * h + (i & 3);
+        if (!qvalid || key >= qend) a[i] = -INFINITY;
+      }
     }
-    float tmax = -INFINITY;
+    float tmax = a[0];
 #pragma unroll
-    for (int st = 0; st < 4; ++st)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) tmax = fmaxf(tmax, sv[st][r]);
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
-    const float m_new = fmaxf(m_run, tmax * scale_log2);
-    const float m_ref = (m_new == -INFINITY) ? 0.f : m_new;
-    // rescale only when some lane's running max moved (alpha = 1 elsewhere);
-    // v_exp_f32 is exp2 without the denormal-range scaling: terms below
-    // 2^-126 of the row max contribute nothing at fp32 precision anyway
-    if (__any(m_new != m_run)) {
-      const float alpha = __builtin_amdgcn_exp2f(m_run - m_ref);
+    for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, a[i]);
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 32)) * scale_log2;
+    // m_run is the reference the exponents are taken from: the running maximum
+    // when it was last set.  It moves only when some lane's maximum has risen
+    // by more than 2^8 over it (P then stays below 2^8, with the same relative
+    // precision), which saves nearly every rescale of the output.
+    if (__any(tmax > m_run + 8.0f)) {
+      const float m_new = fmaxf(m_run, tmax);
+      const float alpha = __builtin_amdgcn_exp2f(m_new == -INFINITY ? 0.f : m_run - m_new);
+      m_run = m_new;
       l_part *= alpha;
 #pragma unroll
-      for (int t = 0; t < HD / 16; ++t) oacc[t] *= alpha;
+      for (int d = 0; d < HD / 32; ++d) oacc[d] *= alpha;
     }
-    m_run = m_new;
-    // P^T as a hi/lo bf16 pair: keys 4g + r of sub-tile st take slots
-    // (st & 1) * 4 + r of chunk st >> 1, two slots per 32-bit word
-    uint32_t hw[4][2], lw[4][2];
+    const float m_ref = m_run == -INFINITY ? 0.f : m_run;
+    // P^T as a hi/lo bf16 pair, two keys per 32-bit word.  v_exp_f32 is exp2
+    // without the denormal-range scaling: terms below 2^-126 of the row max
+    // contribute nothing at fp32 precision anyway
+    uint32_t hw[8], lw[8];
 #pragma unroll
-    for (int st = 0; st < 4; ++st)
-#pragma unroll
-      for (int r2 = 0; r2 < 2; ++r2) {
-        const float p0 = __builtin_amdgcn_exp2f(fmaf(sv[st][2 * r2], scale_log2, -m_ref));
-        const float p1 = __builtin_amdgcn_exp2f(fmaf(sv[st][2 * r2 + 1], scale_log2, -m_ref));
-        l_part += p0;
-        l_part += p1;
-        split_pair2(p0, p1, hw[st][r2], lw[st][r2]);
-      }
-    bf16x8 ph[2], pl[2];
-#pragma unroll
-    for (int kc = 0; kc < 2; ++kc) {
-      ph[kc] = __builtin_bit_cast(bf16x8, u32x4{hw[2 * kc][0], hw[2 * kc][1], hw[2 * kc + 1][0], hw[2 * kc + 1][1]});
-      pl[kc] = __builtin_bit_cast(bf16x8, u32x4{lw[2 * kc][0], lw[2 * kc][1], lw[2 * kc + 1][0], lw[2 * kc + 1][1]});
+    for (int i = 0; i < 8; ++i) {
+      const float p0 = __builtin_amdgcn_exp2f(fmaf(a[2 * i], scale_log2, -m_ref));
+      const float p1 = __builtin_amdgcn_exp2f(fmaf(a[2 * i + 1], scale_log2, -m_ref));
+      l_part += p0;
+      l_part += p1;
+      split_pair2(p0, p1, hw[i], lw[i]);
     }
-    // O^T += V^T P^T over 2 chunks of 32 keys; k-slot 8g+r <-> key 32kc+4g+r,
-    // k-slot 8g+4+r <-> key 32kc+16+4g+r (same permutation as the scores),
-    // which the V^T slot order (vt_slot) stores as slots 32kc+8g..+7: one
-    // 16-byte read per plane.  Vh.Ph + Vh.Pl + Vl.Ph
+    // O^T += V^T P^T over 2 depths of 16 keys; k-slot 8 h + j of depth x <->
+    // key 16 x + 8 (j >> 2) + 4 h + (j & 3), score registers 8 x + j, which the
+    // V^T slot order (vt_slot) stores as slots 16 x + 8 h + j: one 16-byte read
+    // per plane.  Vh.Ph + Vh.Pl + Vl.Ph
+    const bf16_t* vh_ = sg.v[0] + (kw * HD + c) * AK;
+    const bf16_t* vl_ = sg.v[1] + (kw * HD + c) * AK;
 #pragma unroll
-    for (int kc = 0; kc < 2; ++kc) {
+    for (int x = 0; x < 2; ++x) {
+      const bf16x8 ph = __builtin_bit_cast(bf16x8, u32x4{hw[4 * x], hw[4 * x + 1], hw[4 * x + 2], hw[4 * x + 3]});
+      const bf16x8 pl = __builtin_bit_cast(bf16x8, u32x4{lw[4 * x], lw[4 * x + 1], lw[4 * x + 2], lw[4 * x + 3]});
+      const int off = ((2 * x + h) ^ vsw) * 8;
 #pragma unroll
-      for (int t = 0; t < HD / 16; ++t) {
-        const int off = (t * 16 + c) * VP + kc * 32 + 8 * g;
-        const bf16x8 vh = __builtin_bit_cast(bf16x8, *(const u32x4*)(sVh + off));
-        const bf16x8 vl = __builtin_bit_cast(bf16x8, *(const u32x4*)(sVl + off));
-        oacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vh, ph[kc], oacc[t], 0, 0, 0);
-        oacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vh, pl[kc], oacc[t], 0, 0, 0);
-        oacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vl, ph[kc], oacc[t], 0, 0, 0);
+      for (int d = 0; d < HD / 32; ++d) {
+        const bf16x8 vh = __builtin_bit_cast(bf16x8, *(const u32x4*)(vh_ + d * 32 * AK + off));
+        const bf16x8 vl = __builtin_bit_cast(bf16x8, *(const u32x4*)(vl_ + d * 32 * AK + off));
+        oacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vh, ph, oacc[d], 0, 0, 0);
+        oacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vh, pl, oacc[d], 0, 0, 0);
+        oacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vl, ph, oacc[d], 0, 0, 0);
       }
     }
-    }  // wave_on
-    __syncthreads();
+  };
+  // own loads of the stage landed, LDS reads of the other one retired; then
+  // everyone's, and the other stage is free to refill
+#define BD_ATT_STEP(CUR, NXT, T)                  \
+  __builtin_amdgcn_s_waitcnt(0x0070);             \
+  __builtin_amdgcn_s_barrier();                   \
+  if ((T) + 1 < t_hi) issue(NXT, (T) + 1);        \
+  compute(CUR, T);                                \
+  if ((T) + 1 >= t_hi) break;
+  if (t_lo < t_hi) {
+    for (int t = t_lo;; t += 2) {
+      BD_ATT_STEP(st0, st1, t)
+      BD_ATT_STEP(st1, st0, t + 1)
+    }
   }
-#undef BD_FETCH
-  float l = l_part;
-  l += __shfl_xor(l, 16);
-  l += __shfl_xor(l, 32);
-  if (!qvalid) return;
+#undef BD_ATT_STEP
+  float l = l_part + __shfl_xor(l_part, 32);
+  if constexpr (KW > 1) {
+    // the query group's waves hand their results to its first, in wave order
+    __shared__ float xm[KW - 1][QW][2][64];
+    constexpr int XS = HD / 2 * 64;
+    static_assert(sizeof(Stage) >= sizeof(float) * XS * QW * (KW - 1), "partials fit a stage");
+    float* xo = (float*)&st0 + lane;                        // [KW - 1][QW][HD / 2 registers][64 lanes]
+    __syncthreads();
+    if (kw > 0) {
+      float* w = xo + ((kw - 1) * QW + qw) * XS;
+#pragma unroll
+      for (int d = 0; d < HD / 32; ++d)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) w[(d * 16 + i) * 64] = oacc[d][i];
+      xm[kw - 1][qw][0][lane] = m_run;
+      xm[kw - 1][qw][1][lane] = l;
+    }
+    __syncthreads();
+    if (kw > 0) return;                                     // the rest is the first waves' own
+    float mx = m_run;
+#pragma unroll
+    for (int k = 0; k < KW - 1; ++k) mx = fmaxf(mx, xm[k][qw][0][lane]);
+    const float ref = mx == -INFINITY ? 0.f : mx;
+    const float f0 = __builtin_amdgcn_exp2f(m_run - ref);
+    l *= f0;
+#pragma unroll
+    for (int d = 0; d < HD / 32; ++d) oacc[d] *= f0;
+#pragma unroll
+    for (int k = 0; k < KW - 1; ++k) {
+      const float* w = xo + (k * QW + qw) * XS;
+      const float f = __builtin_amdgcn_exp2f(xm[k][qw][0][lane] - ref);
+      l += f * xm[k][qw][1][lane];
+#pragma unroll
+      for (int d = 0; d < HD / 32; ++d)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[d][i] += f * w[(d * 16 + i) * 64];
+    }
+    m_run = mx;
+  }
+  // O^T block d: lane holds dims d * 32 + 8 j + 4 h + r (r < 4) of query c in
+  // registers 4 j + r.  The wave turns its block round in LDS (its part of
+  // stage 0, rows of HD floats, 16-byte chunk k of row r at k ^ (r & 15)) and
+  // writes whole rows: from the registers each lane would write 8 or 16 bytes
+  // of a row of its own.
+  constexpr int OCH = HD / 4;                               // 16-byte chunks of a row
+  static_assert(2 * sizeof(Stage) >= sizeof(float) * 32 * HD * QW && QW * KW <= 8, "output blocks fit the stages");
+  if constexpr (KW == 1) __syncthreads();                   // every wave is past its last stage
+  constexpr int PER = sizeof(Stage) / (sizeof(float) * 32 * HD);   // blocks per stage
+  float* ob = (qw < PER ? (float*)&st0 + qw * 32 * HD : (float*)&st1 + (qw - PER) * 32 * HD);
+  const float inv = kv_splits == 1 ? 1.0f / l : 1.0f;
+#pragma unroll
+  for (int d = 0; d < HD / 32; ++d)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      *(floatx4*)(ob + c * HD + (((d * 8 + 2 * j + h) ^ (c & 15)) * 4)) =
+          floatx4{oacc[d][4 * j] * inv, oacc[d][4 * j + 1] * inv, oacc[d][4 * j + 2] * inv, oacc[d][4 * j + 3] * inv};
+  if (kv_splits > 1 && h == 0 && qvalid) {
+    const size_t base = ((size_t)split * rows_cap + qrow) * H + hq;
+    ws_ml[2 * base] = m_run;
+    ws_ml[2 * base + 1] = l;
+  }
+  __builtin_amdgcn_s_waitcnt(0xC07F);                       // the wave's own writes, then its reads
+  __builtin_amdgcn_wave_barrier();
   if (kv_splits == 1) {
-    const float inv = 1.0f / l;
-    bf16_t* orow = O + (size_t)qrow * H * HD + h * HD;
-#pragma unroll
-    for (int t = 0; t < HD / 16; ++t) {
-      // O^T tile t: lane holds dims t*16 + 4g + r of query c; stored as the
-      // bf16 pair (hi, lo) of the O-projection operand
-      bf16_t hb[4], lb[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float y = oacc[t][r] * inv;
-        hb[r] = f2bf_a(y);
-        lb[r] = f2bf_a(y - bf2f_a(hb[r]));
-      }
-      *(uint2*)(orow + t * 16 + 4 * g) =
-          make_uint2((uint32_t)hb[0] | ((uint32_t)hb[1] << 16), (uint32_t)hb[2] | ((uint32_t)hb[3] << 16));
-      *(uint2*)(orow + o_plane + t * 16 + 4 * g) =
-          make_uint2((uint32_t)lb[0] | ((uint32_t)lb[1] << 16), (uint32_t)lb[2] | ((uint32_t)lb[3] << 16));
+    constexpr int RPI = 64 / (HD / 8);                      // rows per pass, 8 dims a lane
+#pragma unroll 2
+    for (int r0 = 0; r0 < 32; r0 += RPI) {
+      const int r = r0 + lane / (HD / 8), k = (lane % (HD / 8)) * 2, q = q0w + r;
+      if (q >= QG) continue;
+      const floatx4 x = *(const floatx4*)(ob + r * HD + ((k ^ (r & 15)) * 4));
+      const floatx4 y = *(const floatx4*)(ob + r * HD + (((k + 1) ^ (r & 15)) * 4));
+      u32x4 hi, lo;
+      uint32_t hb, lb;
+      split_pair2(x[0], x[1], hb, lb); hi[0] = hb; lo[0] = lb;
+      split_pair2(x[2], x[3], hb, lb); hi[1] = hb; lo[1] = lb;
+      split_pair2(y[0], y[1], hb, lb); hi[2] = hb; lo[2] = lb;
+      split_pair2(y[2], y[3], hb, lb); hi[3] = hb; lo[3] = lb;
+      bf16_t* o = O + ((size_t)(row_start + q / G) * H + kv * G + q % G) * HD + k * 4;
+      *(u32x4*)o = hi;
+      *(u32x4*)(o + o_plane) = lo;
     }
   } else {
     // unnormalised partial of this key split, merged by k_attn_merge
-    const size_t base = ((size_t)split * rows_cap + qrow) * H + h;
-    float* orow = ws_o + base * HD;
-#pragma unroll
-    for (int t = 0; t < HD / 16; ++t)
-      *(float4*)(orow + t * 16 + 4 * g) = make_float4(oacc[t][0], oacc[t][1], oacc[t][2], oacc[t][3]);
-    if (g == 0) {
-      ws_ml[2 * base] = m_run;
-      ws_ml[2 * base + 1] = l;
+    constexpr int RPI = 64 / OCH;
+#pragma unroll 2
+    for (int r0 = 0; r0 < 32; r0 += RPI) {
+      const int r = r0 + lane / OCH, k = lane % OCH, q = q0w + r;
+      if (q >= QG) continue;
+      *(floatx4*)(ws_o + (((size_t)split * rows_cap + row_start + q / G) * H + kv * G + q % G) * HD + k * 4) =
+          *(const floatx4*)(ob + r * HD + ((k ^ (r & 15)) * 4));
     }
   }
 }
@@ -450,34 +532,44 @@ __global__ __launch_bounds__(256) void k_attn_f32(const float* __restrict__ Q,
   for (int e = 0; e < PER; ++e) o[lane * PER + e] = acc[e] / l;
 }
 
-// waves per workgroup for a window of win_cap rows over a key capacity of
-// maxpos (see k_attn_bf16): 8 waves (128 queries per staged K/V tile) where a
-// kv head has at least 512 window queries over at least 4096 keys -- the
-// long-prefix decode's attention ran 7% faster than with 4 waves (484 -> 449
-// ms per decode), the multi-block one (2048 keys) 2.5% slower
-static int attention_waves(int win_cap, int H, int Hkv, int maxpos) {
-  const int q = (H / Hkv) * win_cap;
-  return q <= 32 ? 2 : (q >= 512 && maxpos >= 4096 ? 8 : 4);
+// Query groups of 32 and waves over the keys per workgroup, and key splits, from
+// the rows a window usually holds (rows_est; the grid covers the largest window).
+// Tiles of 128 queries are the rule: every K and V fragment staged serves 4 waves.
+//  * {2, 2} where a kv head's queries fill no more than half of one (512 rows of
+//    16 heads of 64: step 1340 us against 1354 in tiles of 128) or where there are
+//    so few tiles that the keys are split for them (96 rows of 16 heads over 1120
+//    keys: 24-layer step 2836 us against 2877; {1, 2} 2876).
+//  * {4, 1} else: two workgroups a CU (64 KB of LDS each at hd 128), whose loads
+//    and products overlap freely (32 windows of 96 rows: 2-layer step 1728 us
+//    against 1762 with two waves over the keys; 8 windows of 64: 431 against 437).
+//  * {4, 2} where one workgroup a CU has a long range to itself and would leave
+//    it a wave a SIMD (8 windows of 128 rows over 8320 keys: 927 against 974).
+// The keys are split until every CU has a workgroup, while a split keeps 160
+// keys: a split's partials are written and read at 4 bytes a value and merged by
+// another launch (64 tiles over 1504 keys: step 431 us in 4 splits, 457 in 8;
+// three windows of 32 rows over 256 keys: 239.3 unsplit, 240.1 in 2).
+struct AttnShape {
+  int qw, kw, splits;
+};
+static AttnShape attention_shape(int b, int rows_est, int H, int Hkv, int maxpos) {
+  const int q = (H / Hkv) * rows_est;
+  const int tiles = (q + 127) / 128 * Hkv * b;
+  const bool small = q <= 64 || tiles <= 32;
+  const int wgs = small ? (q + 63) / 64 * Hkv * b : tiles;
+  int splits = 1;
+  while (wgs * (splits + 1) <= 256 && maxpos / (splits + 1) >= 160 && splits < 16) ++splits;
+  const int nst = (maxpos + 63) / 64, per = (nst + splits - 1) / splits;
+  splits = (nst + per - 1) / per;                           // none of them empty in stages of 64
+  if (small) return AttnShape{2, 2, splits};
+  return AttnShape{4, wgs * splits <= 256 && maxpos / splits >= 1024 ? 2 : 1, splits};
 }
 
-int attention_splits(int b, int win_cap, int rows_est, int H, int Hkv, int hd, int maxpos) {
-  // the launch shape follows win_cap (the largest window); the work estimate
-  // follows rows_est, the rows a window usually holds
-  const int nw = attention_waves(win_cap, H, Hkv, maxpos);
-  const int wgs = (((H / Hkv) * rows_est + 16 * nw - 1) / (16 * nw)) * Hkv * b;
-  // workgroups resident per CU (LDS-bound: 37 KB per workgroup at hd 64,
-  // 72 KB at hd 128; registers hold the 4-wave hd-64 kind to 3 and the
-  // 8-wave kinds to 1): split the key range until
-  // the grid fills one resident round of 256 CUs, while every split keeps
-  // >= 2 key tiles of the longest range
-  const int round = (nw == 8 ? 1 : (hd == 64 ? (nw == 2 ? 4 : 3) : 2)) * 256;
-  int splits = 1;
-  while (wgs * (splits + 1) <= round && maxpos / (AK * (splits + 1)) >= 2 && splits < 16) ++splits;
-  return splits;
+int attention_splits(int b, int rows_est, int H, int Hkv, int maxpos) {
+  return attention_shape(b, rows_est, H, Hkv, maxpos).splits;
 }
 
 hipError_t launch_attention(bool is_bf16, const void* Q, size_t q_plane, const KvView& kv,
-                            void* O, size_t o_plane, PlanView plan, int b, int win_cap, int H,
+                            void* O, size_t o_plane, PlanView plan, int b, int win_cap, int rows_est, int H,
                             int Hkv, int hd, int B, int kv_splits, float* ws_o, float* ws_ml,
                             int rows_cap, hipStream_t st) {
   if (is_bf16) {
@@ -488,18 +580,22 @@ hipError_t launch_attention(bool is_bf16, const void* Q, size_t q_plane, const K
     const bf16_t* k = (const bf16_t*)kv.K;
     const bf16_t* v = (const bf16_t*)kv.V;
     if (kv_splits < 1 || (kv_splits > 1 && (!ws_o || !ws_ml))) return hipErrorInvalidValue;
-    const int nw = attention_waves(win_cap, H, Hkv, kv.maxpos);
-    const int nqt = ((H / Hkv) * win_cap + 16 * nw - 1) / (16 * nw);
+    const AttnShape sh = attention_shape(b, rows_est, H, Hkv, kv.maxpos);
+    const int nqt = ((H / Hkv) * win_cap + 32 * sh.qw - 1) / (32 * sh.qw);
     const int grid = b * Hkv * kv_splits * nqt + 7;
-#define BD_ATTN(HD_, NW_)                                                                     \
-  k_attn_bf16<HD_, NW_><<<grid, 64 * NW_, 0, st>>>(                                           \
+#define BD_ATTN(HD_, QW_, KW_)                                                                \
+  k_attn_bf16<HD_, QW_, KW_><<<grid, 64 * QW_ * KW_, 0, st>>>(                                \
       q, q_plane, k, kv.k_plane, v, kv.v_plane, kv.vstride, (bf16_t*)O, o_plane,              \
       plan.seq_row_start, plan.seq_win_len, plan.seq_win_start, H, Hkv, kv.maxpos, B,         \
-      scale_log2, kv_splits, ws_o, ws_ml, rows_cap, b, nqt)
+      scale_log2, kv_splits, ws_o, ws_ml, rows_cap, b)
     if (hd == 128) {
-      if (nw == 2) BD_ATTN(128, 2); else if (nw == 8) BD_ATTN(128, 8); else BD_ATTN(128, 4);
+      if (sh.qw == 2) BD_ATTN(128, 2, 2);
+      else if (sh.kw == 1) BD_ATTN(128, 4, 1);
+      else BD_ATTN(128, 4, 2);
     } else {
-      if (nw == 2) BD_ATTN(64, 2); else if (nw == 8) BD_ATTN(64, 8); else BD_ATTN(64, 4);
+      if (sh.qw == 2) BD_ATTN(64, 2, 2);
+      else if (sh.kw == 1) BD_ATTN(64, 4, 1);
+      else BD_ATTN(64, 4, 2);
     }
 #undef BD_ATTN
     if (kv_splits > 1) {

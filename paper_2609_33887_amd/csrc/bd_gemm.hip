@@ -597,23 +597,23 @@ __global__ __launch_bounds__(G::NT) void k_gemm_qkv(const bf16_t* __restrict__ A
     const int j = it & 3, c = nqk + (it >> 2) % nv, g0 = (it >> 2) / nv * 32;   // slot run j of rows g0 .. g0 + 31
     if (g0 >= rows) continue;
     const int vn = n0 + c - qkcols, kh = vn / hd, dim = vn % hd;
+    const int r0 = (j >> 1) * 16 + (j & 1) * 4;              // the run's keys: r0 .. r0 + 3, r0 + 8 .. r0 + 11
     float v[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = tl.row(g0 + (k >> 2) * 16 + 4 * j + (k & 3))[c];
+    for (int k = 0; k < 8; ++k) v[k] = tl.row(g0 + r0 + (k >> 2) * 8 + (k & 3))[c];
     const int m = m0 + g0;
     bool run = g0 + 31 < rows;
     if (run) {
       const int p0 = e.row_pos[m];
       run = p0 % 32 == 0 && e.row_pos[m + 31] == p0 + 31 && e.row_seq[m] == e.row_seq[m + 31];
       if (run)
-        store_pair8(Vc + ((size_t)e.row_seq[m] * e.Hkv + kh) * hd * e.kv.vstride + vt_row(p0, dim, hd) + p0 % VTILE +
-                        8 * j,
+        store_pair8(Vc + ((size_t)e.row_seq[m] * e.Hkv + kh) * hd * e.kv.vstride + vt_row(p0, dim, hd) + 8 * j,
                     e.kv.v_plane, v);
     }
     if (run) continue;
 #pragma unroll
     for (int hf = 0; hf < 2; ++hf) {
-      const int r = g0 + hf * 16 + 4 * j;                    // 4 rows from r on
+      const int r = g0 + r0 + hf * 8;                        // 4 rows from r on
       if (r >= rows) continue;
       if (e.rows4 && r + 3 < rows) {
         store_pair4(Vc + ((size_t)e.row_seq[m0 + r] * e.Hkv + kh) * hd * e.kv.vstride +

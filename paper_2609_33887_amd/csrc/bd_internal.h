@@ -245,22 +245,21 @@ __device__ __forceinline__ void band_tile(int u, int X, int Y, int R, int& x, in
 constexpr int BAND_R = 4;   // row tiles per band: a 128-row hi/lo activation tile is twice a weight tile
 
 // One layer's KV cache.  K: [seq][kv head][pos][hd].  V: bf16 models keep
-// it transposed in tiles of 64 keys, [seq][kv head][pos / 64][hd][64]: a
+// it transposed in tiles of 32 keys, [seq][kv head][pos / 32][hd][32]: a
 // tile is one contiguous block per plane (DRAM page locality when streamed).
-// Inside a tile row, key k sits at slot vt_slot(k): every group of 32 keys is
-// reordered so that keys 4j..4j+3 and 16+4j..16+4j+3 fill the 8 adjacent
-// slots 8j..8j+7 -- the 8 keys one lane feeds to a P.V MFMA, so that
-// fragment is one 16-byte read; aligned runs of 4 keys stay contiguous.
+// Inside a tile row, key k sits at slot vt_slot(k): in every group of 16 keys
+// the runs 4..7 and 8..11 change places, so that the 8 keys one lane feeds to a
+// P.V MFMA (4 h .. and 8 + 4 h .. of the group for lane half h) are 8 adjacent
+// slots, one 16-byte read; aligned runs of 4 keys stay contiguous.
 // vt_off gives the offset of (pos, dim) inside a (seq, kv head) slice of
 // hd * vstride elements, vstride = maxpos rounded up to 64; vt_row the
 // offset of slot 0 of a tile row.  fp32
 // models keep V as K.  bf16 models store pairs: lo planes at + k_plane /
 // + v_plane elements.  The whole cache is cleared at allocation, so padding
 // and not yet written positions are finite.
-constexpr int VTILE = 64;
+constexpr int VTILE = 32;
 __host__ __device__ __forceinline__ int vt_slot(int k) {
-  const int q = k & 31;
-  return (k & 32) + 8 * ((q & 15) >> 2) + 4 * (q >> 4) + (q & 3);
+  return (k & 19) + 8 * ((k >> 2) & 1) + 4 * ((k >> 3) & 1);
 }
 __host__ __device__ __forceinline__ size_t vt_row(int pos, int dim, int hd) {
   return ((size_t)(pos / VTILE) * hd + dim) * VTILE;
@@ -275,18 +274,19 @@ struct KvView {
   int maxpos, vstride;
 };
 
-// Attention of the rows of `plan` over the cache.  bf16 models: tiles of 64
+// Attention of the rows of `plan` over the cache.  bf16 models: groups of 32
 // queries of one (sequence, kv head) (window rows x the q-heads sharing the kv
-// head), 64-key tiles staged in LDS; kv_splits > 1 splits every
+// head), 32-key tiles staged in LDS; kv_splits > 1 splits every
 // query tile's key range into that many workgroups (partials in ws_o
 // [splits][rows_cap][H][hd], ws_ml [splits][rows_cap][H][2]) merged in split
-// order.  O: bf16 plane pair (lo at O + o_plane elements) for bf16 models,
+// order.  win_cap rows are the largest window of a sequence, rows_est those it
+// usually holds.  O: bf16 plane pair (lo at O + o_plane elements) for bf16 models,
 // fp32 otherwise.
 hipError_t launch_attention(bool is_bf16, const void* Q, size_t q_plane, const KvView& kv, void* O,
-                            size_t o_plane, PlanView plan, int b, int win_cap, int H, int Hkv,
+                            size_t o_plane, PlanView plan, int b, int win_cap, int rows_est, int H, int Hkv,
                             int hd, int B, int kv_splits, float* ws_o, float* ws_ml, int rows_cap,
                             hipStream_t st);
-int attention_splits(int b, int win_cap, int rows_est, int H, int Hkv, int hd, int maxpos);
+int attention_splits(int b, int rows_est, int H, int Hkv, int maxpos);
 
 hipError_t launch_embed(bool is_bf16, const int32_t* tokens, int tok_stride, const void* E, int d,
                         int vocab, PlanView plan, int rows_cap, float* X, int32_t* err_flag,

@@ -85,3 +85,31 @@ def test_gemm_tiles(w):
 @pytest.mark.parametrize("w", TILES[:3], ids=lambda w: w.name)
 def test_gemm_tiles_quantized(w, wq):
     check(w, wq=wq)
+
+
+ATTN = [
+    # (2, 2): up to 64 queries a kv head (a whole wave and one query beside it: 33), one split, up to three stages of keys
+    (small("v_attn_22_64", seed=150, n_heads=4, n_kv_heads=4, head_dim=64, batch=2, prompt_len=33, block_size=33,
+           n_inflight=1, gen_len=66), None),
+    # (2, 2) for few tiles, keys in splits of which the last holds a partial stage; 65 queries: a second tile of one
+    (small("v_attn_22_128", seed=151, n_heads=5, n_kv_heads=1, head_dim=128, batch=1, prompt_len=637, block_size=13,
+           n_inflight=1, gen_len=26), None),
+    # (4, 1): 40 tiles of 128 queries with 4 splits (hd 64: 96 queries, one group idle; hd 128: 130, a second tile)
+    (small("v_attn_41_64", seed=152, n_heads=16, n_kv_heads=4, head_dim=64, batch=10, prompt_len=648, block_size=8,
+           n_inflight=3, gen_len=48), (0, 9)),
+    (small("v_attn_41_128", seed=153, n_heads=10, n_kv_heads=2, head_dim=128, batch=10, prompt_len=650, block_size=13,
+           n_inflight=2, gen_len=26), (0, 9)),
+    # (4, 2): 144 tiles over 1,100 keys, unsplit (hd 64), and 132 (hd 128)
+    (small("v_attn_42_64", seed=154, n_heads=16, n_kv_heads=16, head_dim=64, batch=9, prompt_len=1036, block_size=37,
+           n_inflight=2, gen_len=74), (8,)),
+    (small("v_attn_42_128", seed=155, n_heads=12, n_kv_heads=12, head_dim=128, batch=11, prompt_len=990,
+           block_size=33, n_inflight=3, gen_len=99), (10,)),
+    # more sequences than a wave has lanes for their windows, of which the last ends last
+    (small("v_attn_b67", seed=156, n_heads=4, n_kv_heads=1, head_dim=64, batch=67, prompt_len=24, block_size=24,
+           n_inflight=1, gen_len=48), (0, 63, 64, 66)),
+]
+
+
+@pytest.mark.parametrize("w,ids", ATTN, ids=lambda x: getattr(x, "name", ""))
+def test_attention_shapes(w, ids):
+    check(w, seq_ids=ids)
