@@ -112,12 +112,12 @@ __device__ __forceinline__ bf16x8 fp4x8_to_bf16(uint32_t v, float scale) {
 }
 
 // Eight E4M3 codes (bytes 0..7 of v, k order) -> eight bf16 (exact).
-__device__ __forceinline__ bf16x8 fp8x8_to_bf16(uint2 v) {
+__device__ __forceinline__ bf16x8 fp8x8_to_bf16(u32x2 v) {
   typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-  const bf16x2_t a = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(v.x, 1.0f, false);
-  const bf16x2_t b = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(v.x, 1.0f, true);
-  const bf16x2_t c = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(v.y, 1.0f, false);
-  const bf16x2_t d = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(v.y, 1.0f, true);
+  const bf16x2_t a = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(v[0], 1.0f, false);
+  const bf16x2_t b = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(v[0], 1.0f, true);
+  const bf16x2_t c = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(v[1], 1.0f, false);
+  const bf16x2_t d = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(v[1], 1.0f, true);
   bf16x8 o;
   o[0] = a[0]; o[1] = a[1]; o[2] = b[0]; o[3] = b[1];
   o[4] = c[0]; o[5] = c[1]; o[6] = d[0]; o[7] = d[1];
@@ -136,12 +136,14 @@ __device__ __forceinline__ void wait_vmcnt() {
 
 // One stage.  W rows: bf16 (2 SK bytes, swizzled), fp8 codes (SK bytes,
 // swizzled), or E2M1 codes as [SK / 32][BN][16 bytes] with the blocks'
-// exponents [SK / 32][BN].
-template <int BM, int BN, int SK, int WQ>
+// exponents [SK / 32][BN], dealt to the NW waves that load them: each fills 256
+// bytes with copies of its share (a load of some lanes only is a branch, after
+// which the compiler no longer counts the loads in flight).
+template <int BM, int BN, int SK, int WQ, int NW>
 struct GemmStage {
   bf16_t a[2][BM * SK];
   uint8_t b[WQ == WQ_NONE ? BN * SK * 2 : (WQ == WQ_FP8 ? BN * SK : BN * SK / 2)];
-  uint8_t be[WQ == WQ_MXFP4 ? BN * SK / MX_BLOCK : 0];
+  uint8_t be[WQ == WQ_MXFP4 ? 256 * NW : 0];
 };
 
 // The ring's stages are separate LDS objects (declared by the kernel, see
@@ -181,7 +183,7 @@ struct Gemm {
   static_assert(LA >= 1 && LB >= 1 && LA * ARPI * NW == BM && LB * 64 * WLB * NW == WB, "whole loads per wave");
   static_assert(KS >= 1 && (WQ == WQ_NONE || (SK == 64 && KG == 2)), "quantized weights: two groups, 64 deep");
   static_assert(NS >= 2 && NS <= 4 && (KALIGN / SK) % 2 == 0, "ring");
-  typedef GemmStage<BM, BN, SK, WQ> Stage;
+  typedef GemmStage<BM, BN, SK, WQ, NW> Stage;
   typedef GemmRing<Stage> Ring;
   // output tile in LDS (see to_lds): half of the rows in each of two stages
   static constexpr int LD = BN + 4;
@@ -215,7 +217,7 @@ struct Gemm {
       else load_lds4(rw, d, wo[i], (uint32_t)kt * wstep);
     }
     if constexpr (WQ == WQ_MXFP4)
-      if (lane < EXPB / 4) load_lds4(re, s.be + wave * EXPB, eo, (uint32_t)kt * estep);
+      load_lds4(re, s.be + wave * 256, eo, (uint32_t)kt * estep);
   }
 
   __device__ __forceinline__ void mfma(const Stage& s) {
@@ -228,12 +230,16 @@ struct Gemm {
       for (int j = 0; j < FN; ++j) {
         const int row = wn * WCOLS + j * 16 + r16;
         if constexpr (WQ == WQ_FP8) {
-          const uint2 raw = *(const uint2*)(s.b + row * SK + ((g ^ swz(SK, r16)) * 16) + kg * 8);
+          const uint32_t off = sizeof(s.a) + row * SK + ((g ^ swz(SK, r16)) * 16) + kg * 8;
+          const u32x2 raw = *(const u32x2*)((const char*)&s + off);
           b[j] = __builtin_bit_cast(u32x4, fp8x8_to_bf16(raw));
         } else if constexpr (WQ == WQ_MXFP4) {
           // 2^(e - 127) (e >= 1; e = 0 only in all-zero blocks, whose codes are zero)
-          const uint32_t raw = *(const uint32_t*)(s.b + (kg * BN + row) * 16 + g * 4);
-          b[j] = __builtin_bit_cast(u32x4, fp4x8_to_bf16(raw, __uint_as_float((uint32_t)s.be[kg * BN + row] << 23)));
+          const uint32_t off = sizeof(s.a) + (kg * BN + row) * 16 + g * 4;
+          const uint32_t eoff = sizeof(s.a) + sizeof(s.b) + (kg * BN + row) / EXPB * 256 + (kg * BN + row) % EXPB;
+          const uint32_t raw = *(const uint32_t*)((const char*)&s + off);
+          const uint32_t ex = *((const uint8_t*)&s + eoff);
+          b[j] = __builtin_bit_cast(u32x4, fp4x8_to_bf16(raw, __uint_as_float(ex << 23)));
         } else {
           b[j] = *(const u32x4*)((const bf16_t*)s.b + row * SK + pos);
         }
@@ -317,7 +323,7 @@ struct Gemm {
         const int by = (i * NW + wave) * 256 + lane * 4;          // byte in [blocks][BN][16]
         wo[i] = (uint32_t)(by / (BN * 16)) * (uint32_t)ldw * 16u + by % (BN * 16);
       }
-      const int eb = wave * EXPB + (lane < EXPB / 4 ? lane : 0) * 4;
+      const int eb = wave * EXPB + (lane % (EXPB / 4)) * 4;
       eo = (uint32_t)(eb / BN) * (uint32_t)ldw + eb % BN;
     } else {
       constexpr int WRB = WQ == WQ_FP8 ? SK : SK * 2, ES = WQ == WQ_FP8 ? 1 : 2;
@@ -338,9 +344,12 @@ struct Gemm {
     // no scalar load left in flight: the loop's LDS waits can then count the
     // fragment reads down instead of draining them
     __builtin_amdgcn_s_waitcnt(0xC07F);
+    // The ring is filled unconditionally (stages past the last load another
+    // again): a fill under a branch leaves the compiler unsure of the loads in
+    // flight, and it waits for younger ones before a stage's first reads.
     issue(rg.template at<0>(), 0);
     if constexpr (NS > 2) issue(rg.template at<1>(), 1);
-    if constexpr (NS > 3) if (SK == 32 || nk > 2) issue(rg.template at<2>(), 2);
+    if constexpr (NS > 3) issue(rg.template at<2>(), SK == 32 || nk > 2 ? 2 : 1);
     int t = 0;
     for (; t + 2 * NS - 1 <= nk; t += NS) group<0>(rg, t);
     const int rem = nk - t;
@@ -887,17 +896,15 @@ struct GemmF32 {
   int lane, wave;
 
   // rows 2 q, 2 q + 1 of the stage by load q; BM is a multiple of 16, so a
-  // load is all A or all W.  Lanes past the depth are masked off: the chain
-  // does not read those chunks.
+  // load is all A or all W.  Chunks past the depth repeat the last one: the
+  // chain does not read them (masking the lanes off would be a branch, after
+  // which the compiler no longer counts the loads in flight).
   __device__ __forceinline__ void issue(Stage& s, int t, int K) {
-    const int src = (lane & 31);
 #pragma unroll
     for (int i = 0; i < LN; ++i) {
       const int q = i * NW + wave, r = 2 * q + (lane >> 5);
-      if (t * FKC + (src ^ (r & 7)) * 4 < K) {
-        if (q < BM / 2) load_lds16(ra, s.x + 2 * q * FKC, off[i], (uint32_t)t * (FKC * 4));
-        else load_lds16(rw, s.x + 2 * q * FKC, off[i], (uint32_t)t * (FKC * 4));
-      }
+      const int col = t * FKC + ((lane & 31) ^ (r & 7)) * 4;
+      load_lds16(q < BM / 2 ? ra : rw, s.x + 2 * q * FKC, off[i] + (uint32_t)min(col, K - 4) * 4u, 0);
     }
   }
   __device__ __forceinline__ void chain(const Stage& s, int steps) {
@@ -961,17 +968,16 @@ struct GemmF32 {
 #pragma unroll
     for (int i = 0; i < LN; ++i) {
       const int r = 2 * (i * NW + wave) + (lane >> 5);
-      const uint32_t c = ((lane & 31) ^ (r & 7)) * 4;
       const int n = r - BM;
-      off[i] = (r < BM ? (uint32_t)r * (uint32_t)lda + c
-                       : (uint32_t)((n >> 4) * wstep + (n & 15)) * (uint32_t)ldw + c) * 4u;
+      off[i] = (r < BM ? (uint32_t)r * (uint32_t)lda
+                       : (uint32_t)((n >> 4) * wstep + (n & 15)) * (uint32_t)ldw) * 4u;
     }
     acc = floatx4{0.f, 0.f, 0.f, 0.f};
     const int nk = (K + FKC - 1) / FKC;
     __builtin_amdgcn_s_waitcnt(0xC07F);
     issue(rg.template at<0>(), 0, K);
-    if (nk > 1) issue(rg.template at<1>(), 1, K);
-    if constexpr (NS > 3) if (nk > 2) issue(rg.template at<2>(), 2, K);
+    issue(rg.template at<1>(), nk > 1 ? 1 : 0, K);
+    if constexpr (NS > 3) issue(rg.template at<2>(), nk > 2 ? 2 : 0, K);
     int t = 0;
     for (; t + 2 * NS - 1 <= nk; t += NS) steps<0, NS, false>(rg, t, K);
     tails<1>(rg, t, nk - t, K);

@@ -14,6 +14,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 // native 16-byte vector (HIP's uint4 is a struct, which keeps register arrays
 // of it on the stack)
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 // Per-sequence decode descriptor, int32 fields of seq_state[b][SS_N].
 enum {
