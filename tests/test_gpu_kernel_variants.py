@@ -113,3 +113,20 @@ ATTN = [
 @pytest.mark.parametrize("w,ids", ATTN, ids=lambda x: getattr(x, "name", ""))
 def test_attention_shapes(w, ids):
     check(w, seq_ids=ids)
+
+
+MOE = [
+    # router and dispatch: every expert chosen, two chunks a wave, one row; 20 experts of 64 lanes, 6 chunks (a multiple
+    # of the ring), one row past a row tile; 64 experts, 10 chunks, assignments that end within a wave's share
+    small("v_moe_e5", seed=160, ffn_dim=0, n_experts=5, top_k=5, expert_ffn=128, batch=1, prompt_len=3, block_size=1,
+          n_inflight=1, gen_len=6),
+    small("v_moe_e20", seed=161, d_model=768, ffn_dim=0, n_experts=20, top_k=3, expert_ffn=128, n_shared=1, batch=1,
+          prompt_len=17, block_size=17, n_inflight=1, gen_len=34),
+    small("v_moe_e64", seed=162, d_model=1280, ffn_dim=0, n_experts=64, top_k=8, expert_ffn=128, batch=5,
+          prompt_len=105, block_size=15, n_inflight=2, gen_len=30),
+]
+
+
+@pytest.mark.parametrize("w", MOE, ids=lambda w: w.name)
+def test_moe_router_and_dispatch(w):
+    check(w)
