@@ -130,3 +130,16 @@ MOE = [
 @pytest.mark.parametrize("w", MOE, ids=lambda w: w.name)
 def test_moe_router_and_dispatch(w):
     check(w)
+
+
+COMMIT = [
+    # the commit kernel: more masked positions than it keeps in LDS (70 x 4 x 32 = 8,960), sequences beyond a wave's
+    # lanes and off the four a lane sums
+    (small("v_commit_8960", seed=170, n_layers=1, d_model=128, n_heads=2, n_kv_heads=2, ffn_dim=128, vocab=256,
+           batch=70, prompt_len=32, block_size=32, n_inflight=4, gen_len=256), (0, 1, 63, 64, 69)),
+]
+
+
+@pytest.mark.parametrize("w,ids", COMMIT, ids=lambda x: getattr(x, "name", ""))
+def test_commit_many_positions(w, ids):
+    check(w, seq_ids=ids)
