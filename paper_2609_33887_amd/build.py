@@ -23,6 +23,10 @@ HIP_FLAGS = [
     # MFMA accumulators in VGPRs: with AGPR accumulators the pipelined GEMM
     # loops carried accumulator copies (v_accvgpr_*) in every stage
     "-mllvm", "-amdgpu-mfma-vgpr-form",
+    # Leading kernel arguments arrive in scalar registers instead of being
+    # loaded by every wave (up to 14 dwords, until the first struct): the
+    # kernels put the row counts and addresses that they read first in front
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wno-unused-result",
 ]
 CXX_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall"]

@@ -78,11 +78,12 @@ struct AttStage {
 
 template <int HD, int QW, int KW>
 __global__ __launch_bounds__(64 * QW * KW) __attribute__((amdgpu_waves_per_eu(KW == 1 ? 2 : 1, 2)))
-void k_attn_bf16(const bf16_t* __restrict__ Q, size_t q_plane, const bf16_t* __restrict__ Kc, size_t k_plane,
-                 const bf16_t* __restrict__ Vt, size_t v_plane, int vstride, bf16_t* __restrict__ O, size_t o_plane,
-                 const int32_t* __restrict__ seq_row_start, const int32_t* __restrict__ seq_win_len,
-                 const int32_t* __restrict__ seq_win_start, int H, int Hkv, int maxpos, int B, float scale_log2,
-                 int kv_splits, float* __restrict__ ws_o, float* __restrict__ ws_ml, int rows_cap, int b) {
+void k_attn_bf16(const int32_t* __restrict__ seq_win_len, const int32_t* __restrict__ seq_row_start,
+                 const int32_t* __restrict__ seq_win_start, int b, int H, int Hkv, int kv_splits, int B, int maxpos,
+                 const bf16_t* __restrict__ Kc, const bf16_t* __restrict__ Vt, const bf16_t* __restrict__ Q,
+                 size_t k_plane, size_t v_plane, size_t q_plane, int vstride, float scale_log2,
+                 bf16_t* __restrict__ O, size_t o_plane, float* __restrict__ ws_o, float* __restrict__ ws_ml,
+                 int rows_cap) {
   constexpr int NW = QW * KW;
   constexpr int AQ = 32 * QW;             // queries per workgroup
   constexpr int SK = AK * KW;             // keys per stage
@@ -585,9 +586,9 @@ hipError_t launch_attention(bool is_bf16, const void* Q, size_t q_plane, const K
     const int grid = b * Hkv * kv_splits * nqt + 7;
 #define BD_ATTN(HD_, QW_, KW_)                                                                \
   k_attn_bf16<HD_, QW_, KW_><<<grid, 64 * QW_ * KW_, 0, st>>>(                                \
-      q, q_plane, k, kv.k_plane, v, kv.v_plane, kv.vstride, (bf16_t*)O, o_plane,              \
-      plan.seq_row_start, plan.seq_win_len, plan.seq_win_start, H, Hkv, kv.maxpos, B,         \
-      scale_log2, kv_splits, ws_o, ws_ml, rows_cap, b)
+      plan.seq_win_len, plan.seq_row_start, plan.seq_win_start, b, H, Hkv, kv_splits, B,      \
+      kv.maxpos, k, v, q, kv.k_plane, kv.v_plane, q_plane, kv.vstride, scale_log2,            \
+      (bf16_t*)O, o_plane, ws_o, ws_ml, rows_cap)
     if (hd == 128) {
       if (sh.qw == 2) BD_ATTN(128, 2, 2);
       else if (sh.kw == 1) BD_ATTN(128, 4, 1);

@@ -469,10 +469,10 @@ __device__ __forceinline__ void swiglu_tile(const typename G::Tile& tl, int rows
 // (rows padded to whole tiles) and the next RMSNorm of the residual stream adds
 // the partials in split order.
 template <class G, int EPI>
-__global__ __launch_bounds__(G::NT) void k_gemm_bf16(const bf16_t* __restrict__ A, int lda,
-                                                     size_t a_plane, const void* __restrict__ W,
-                                                     int ldw, int N, int K,
-                                                     const int32_t* __restrict__ Mp,
+__global__ __launch_bounds__(G::NT) void k_gemm_bf16(const int32_t* __restrict__ Mp,
+                                                     const bf16_t* __restrict__ A,
+                                                     const void* __restrict__ W, size_t a_plane,
+                                                     int lda, int ldw, int N, int K,
                                                      void* __restrict__ out, int ldo, size_t out_plane,
                                                      float* __restrict__ ws, int zmax,
                                                      const void* __restrict__ waux) {
@@ -555,10 +555,11 @@ __global__ __launch_bounds__(G::NT) void k_gemm_bf16(const bf16_t* __restrict__ 
 // a multiple of 32 on, they are one 16-byte store per plane, else 4-position
 // runs or single values.
 template <class G>
-__global__ __launch_bounds__(G::NT) void k_gemm_qkv(const bf16_t* __restrict__ A, int lda,
-                                                    size_t a_plane, const void* __restrict__ W,
-                                                    int K, const int32_t* __restrict__ Mp, QkvEpi e,
-                                                    const void* __restrict__ waux) {
+__global__ __launch_bounds__(G::NT) void k_gemm_qkv(const int32_t* __restrict__ Mp,
+                                                    const bf16_t* __restrict__ A,
+                                                    const void* __restrict__ W, size_t a_plane,
+                                                    int lda, int K, const void* __restrict__ waux,
+                                                    QkvEpi e) {
   constexpr int BM = G::BM, BN = G::BN, WQ = G::WQ;
   const int M = *Mp;
   const int X = (e.H + 2 * e.Hkv) * e.hd / BN, Y = (M + BM - 1) / BM;
@@ -1162,9 +1163,9 @@ static void launch_tile(int epi, dim3 grid, const bf16_t* a, int lda, size_t ap,
                         int ldw, int N, int K, const int32_t* M_dev, void* o, int ldo, size_t op,
                         float* ws, int zmax, const void* waux, hipStream_t st) {
   if (epi == EPI_ADD_F32)
-    k_gemm_bf16<G, EPI_ADD_F32><<<grid, G::NT, 0, st>>>(a, lda, ap, w, ldw, N, K, M_dev, o, ldo, op, ws, zmax, waux);
+    k_gemm_bf16<G, EPI_ADD_F32><<<grid, G::NT, 0, st>>>(M_dev, a, w, ap, lda, ldw, N, K, o, ldo, op, ws, zmax, waux);
   else   // EPI_SWIGLU
-    k_gemm_bf16<G, EPI_SWIGLU><<<grid, G::NT, 0, st>>>(a, lda, ap, w, ldw, N, K, M_dev, o, ldo, op, nullptr, 1, waux);
+    k_gemm_bf16<G, EPI_SWIGLU><<<grid, G::NT, 0, st>>>(M_dev, a, w, ap, lda, ldw, N, K, o, ldo, op, nullptr, 1, waux);
 }
 
 // Tile choice: 128x256 (8 waves of 64 x 64, two per SIMD; 128 KB of LDS) over
@@ -1301,7 +1302,7 @@ hipError_t launch_gemm_qkv(const void* A, int lda, size_t a_plane, const void* W
   if (N % bn) return hipErrorInvalidValue;
   dim3 grid((N / bn) * cdiv(rows_cap, bm) + 7);
   const bf16_t* a = (const bf16_t*)A;
-#define BD_QKV(G_) k_gemm_qkv<G_><<<grid, G_::NT, 0, st>>>(a, lda, a_plane, W, K, M_dev, e, wq.aux)
+#define BD_QKV(G_) k_gemm_qkv<G_><<<grid, G_::NT, 0, st>>>(M_dev, a, W, a_plane, lda, K, wq.aux, e)
   if (wq.fmt == WQ_FP8) {
     if (bm == 128) BD_QKV(Tile128<WQ_FP8>); else BD_QKV(Tile64<WQ_FP8>);
   } else if (wq.fmt == WQ_MXFP4) {
