@@ -515,11 +515,16 @@ static bd_status run_forward(bd_model* m, bd_state* s, const PlanView& plan, int
     e.Hkv = Hkv;
     e.hd = hd;
     e.rows4 = s->B % 4 == 0;
+    // The prompt's rows leave nothing but their K and V: in the last layer the
+    // rest of the forward has no reader.
+    const bool kv_only = !lm && l == c.n_layers - 1;
+    e.first = kv_only ? H * hd : 0;
     if (bf)
       LAUNCH(BD_PROF_GEMM_QKV, launch_gemm_qkv(s->A, d, s->pl_A, L.w_qkv_p, d, plan.hdr, rows_cap, e, st,
                                                L.q_qkv));
     else
       LAUNCH(BD_PROF_GEMM_QKV, launch_gemm_qkv_f32(s->A, d, L.w_qkv, d, plan.hdr, rows_cap, e, m->inv_freq, st));
+    if (kv_only) break;
     LAUNCH(BD_PROF_ATTN, launch_attention(bf, s->Qb, q_plane, kv,
                                           s->Ob, s->pl_O, plan, s->b, win_cap, lm ? s->nb * s->B : win_cap, H, Hkv, hd, s->B,
                                           kv_splits, s->attn_ws_o, s->attn_ws_ml, rows_cap, st));

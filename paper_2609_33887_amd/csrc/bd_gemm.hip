@@ -562,15 +562,16 @@ __global__ __launch_bounds__(G::NT) void k_gemm_qkv(const int32_t* __restrict__ 
                                                     QkvEpi e) {
   constexpr int BM = G::BM, BN = G::BN, WQ = G::WQ;
   const int M = *Mp;
-  const int X = (e.H + 2 * e.Hkv) * e.hd / BN, Y = (M + BM - 1) / BM;
+  const int N = (e.H + 2 * e.Hkv) * e.hd;
+  const int X = (N - e.first) / BN, Y = (M + BM - 1) / BM;
   const int u = xcd_item(blockIdx.x, X * Y);
   if (u >= X * Y) return;
   int tx, ty;
   band_tile(u, X, Y, BAND_R, tx, ty);
-  const int m0 = ty * BM, n0 = tx * BN;
+  const int m0 = ty * BM, n0 = e.first + tx * BN;
   BD_GEMM_SMEM(G);
   G t;
-  t.run(ring, A, lda, a_plane, W, WQ == WQ_MXFP4 ? X * BN : K, (const uint8_t*)waux, 0, K, m0, n0);
+  t.run(ring, A, lda, a_plane, W, WQ == WQ_MXFP4 ? N : K, (const uint8_t*)waux, 0, K, m0, n0);
   if constexpr (WQ == WQ_FP8) t.scale_columns((const float*)waux, n0);
   const typename G::Tile tl = t.to_lds(ring);
   const int hd = e.hd, half = hd >> 1;
@@ -1299,8 +1300,8 @@ hipError_t launch_gemm_qkv(const void* A, int lda, size_t a_plane, const void* W
   const int half_cap = cdiv(rows_cap, 2);
   const int bm = N % 128 == 0 && (N / 128) * cdiv(half_cap, 128) >= 192 ? 128 : 64;
   const int bn = bm == 128 || (wq.fmt == WQ_NONE && N % 128 == 0 && (N / 128) * cdiv(half_cap, 64) >= 192) ? 128 : 64;
-  if (N % bn) return hipErrorInvalidValue;
-  dim3 grid((N / bn) * cdiv(rows_cap, bm) + 7);
+  if (N % bn || e.first % bn) return hipErrorInvalidValue;
+  dim3 grid(((N - e.first) / bn) * cdiv(rows_cap, bm) + 7);
   const bf16_t* a = (const bf16_t*)A;
 #define BD_QKV(G_) k_gemm_qkv<G_><<<grid, G_::NT, 0, st>>>(M_dev, a, W, a_plane, lda, K, wq.aux, e)
   if (wq.fmt == WQ_FP8) {

@@ -366,6 +366,10 @@ struct QkvEpi {
   size_t q_plane;
   KvView kv;
   int H, Hkv, hd;
+  int first;                // the first column wanted: 0, or H * hd for K and V
+                            // alone (a multiple of the column tile: tiles are
+                            // 128 wide only where H + 2 Hkv heads of 64 are even;
+                            // the fp32 kernel computes all columns)
   int rows4;                // 1: every aligned group of 4 rows is 4 consecutive
                             // positions of one sequence (block size % 4 == 0)
 };
