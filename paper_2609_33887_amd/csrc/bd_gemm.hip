@@ -435,6 +435,8 @@ struct Gemm {
 template <int WQ> using Tile128 = Gemm<128, 128, 2, 2, 2, 64, 3, WQ>;
 template <int WQ> using Tile64x128 = Gemm<64, 128, 2, 2, 2, 64, 4, WQ>;
 template <int WQ> using Tile64 = Gemm<64, 64, 2, 2, 2, 64, 3, WQ>;
+typedef Gemm<64, 128, 2, 2, 1, 64, 2, WQ_NONE> Tile64x128x2;   // 4 waves, two workgroups a CU
+typedef Gemm<32, 64, 1, 2, 2, 64, 4, WQ_NONE> Tile32;          // 4 waves
 using TileW = Gemm<128, 256, 2, 4, 1, 32, 4, WQ_NONE>;
 using TileW2 = Gemm<128, 256, 2, 2, 1, 32, 2, WQ_NONE>;
 
@@ -1209,8 +1211,12 @@ static void launch_tile(int epi, dim3 grid, const bf16_t* a, int lda, size_t ap,
 // instead of 64x64 (bf16 weights): half the re-reads of the activation per
 // column tile, two workgroups per CU; the dense decode's gate/up product
 // went from 27.3 to 24.0 us per launch, while the MoE window's (4096 rows)
-// shared-expert products ran 1.5-3% slower in it.  zmax: the largest
-// residual split (1 = none).
+// shared-expert products ran 1.5-3% slower in it.  Where half the row capacity
+// (what a step window usually holds) gives more of those tiles than CUs, four
+// waves take one (launch_gemm_planned), so that a CU runs two side by side and one
+// multiplies while the other waits for its stage: 512 x 8192 x 1024, 512 tiles,
+// 22.3 us against 26.4 with eight waves; one tile a CU (96 x 16384 x 2048) takes
+// 34.7 so and 23.8 with eight.  zmax: the largest residual split (1 = none).
 GemmPlan plan_gemm(bool is_bf16, int N, int K, int rows_cap, bool resid, bool wide_ok) {
   if (!is_bf16) return GemmPlan{64, 64, 1};
   if (wide_ok && N % 256 == 0 && rows_cap >= 2048 && (N >= 8192 || (resid && K >= 2048)))
@@ -1248,6 +1254,7 @@ hipError_t launch_gemm_planned(const GemmPlan& p, int epi, const void* A, int ld
     if (wide && epi == EPI_SWIGLU) BD_TILE(TileW2);
     else if (wide) BD_TILE(TileW);
     else if (big) BD_TILE(Tile128<WQ_NONE>);
+    else if (mid && (N / 128) * cdiv(cdiv(rows_cap, 2), 64) > 256) BD_TILE(Tile64x128x2);
     else if (mid) BD_TILE(Tile64x128<WQ_NONE>);
     else BD_TILE(Tile64<WQ_NONE>);
   }
@@ -1316,9 +1323,12 @@ hipError_t launch_gemm_qkv(const void* A, int lda, size_t a_plane, const void* W
   // 64 x 128, where there are at least 192 of them, else 64 x 64.  Measured for
   // N 3072, K 2048 (us, 128 x 128 / 64 x 128 / 64 x 64): 96 rows - / 14.3 /
   // 11.8, 512 rows 24.9 / 17.2 / 19.1, 1024 rows 28.8 / 32.3 / 30.4, 3072 rows
-  // 77 / - / -.
+  // 77 / - / -.  At most half a 64 x 64 tile a CU: 32 x 64, which brings a third
+  // less through each CU's L1 (96 rows in the 24-layer step: 12.7 against 17.1;
+  // quantized weights keep 64 x 64).
   const int half_cap = cdiv(rows_cap, 2);
-  const int bm = N % 128 == 0 && (N / 128) * cdiv(half_cap, 128) >= 192 ? 128 : 64;
+  const int bm = N % 128 == 0 && (N / 128) * cdiv(half_cap, 128) >= 192 ? 128
+                 : wq.fmt == WQ_NONE && (N / 64) * cdiv(half_cap, 64) <= 128 ? 32 : 64;
   const int bn = bm == 128 || (wq.fmt == WQ_NONE && N % 128 == 0 && (N / 128) * cdiv(half_cap, 64) >= 192) ? 128 : 64;
   if (N % bn || e.first % bn) return hipErrorInvalidValue;
   dim3 grid(((N - e.first) / bn) * cdiv(rows_cap, bm) + 7);
@@ -1331,6 +1341,7 @@ hipError_t launch_gemm_qkv(const void* A, int lda, size_t a_plane, const void* W
   } else {
     if (bm == 128) BD_QKV(Tile128<WQ_NONE>);
     else if (bn == 128) BD_QKV(Tile64x128<WQ_NONE>);
+    else if (bm == 32) BD_QKV(Tile32);
     else BD_QKV(Tile64<WQ_NONE>);
   }
 #undef BD_QKV

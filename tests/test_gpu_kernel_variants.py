@@ -71,6 +71,14 @@ TILES = [
     # shorter runs), hd 64 and 128
     small("v_tile_rows", seed=142, n_heads=4, n_kv_heads=2, head_dim=128, batch=3, prompt_len=43, block_size=43,
           n_inflight=1, gen_len=86),
+    # four waves a 64 x 128 tile: gate/up of 64 column tiles over a capacity of 768 rows and 360 live ones (a part tile);
+    # QKV in 32 x 64 tiles over 33 and 63 live rows; K of two stages in both
+    small("v_tile_4waves", seed=144, d_model=128, n_heads=2, n_kv_heads=1, head_dim=64, ffn_dim=4096, batch=9,
+          prompt_len=40, block_size=40, n_inflight=1, gen_len=80, n_layers=1),
+    small("v_tile_33", seed=145, n_heads=4, n_kv_heads=2, head_dim=128, batch=1, prompt_len=33, block_size=33,
+          n_inflight=1, gen_len=66),
+    small("v_tile_63", seed=146, d_model=128, n_heads=2, n_kv_heads=1, head_dim=64, batch=3, prompt_len=21,
+          block_size=21, n_inflight=1, gen_len=42),
     small("v_tile_rows64", seed=143, n_heads=8, n_kv_heads=4, head_dim=64, batch=13, prompt_len=15, block_size=5,
           n_inflight=2, gen_len=20),
 ]
