@@ -436,6 +436,7 @@ template <int WQ> using Tile128 = Gemm<128, 128, 2, 2, 2, 64, 3, WQ>;
 template <int WQ> using Tile64x128 = Gemm<64, 128, 2, 2, 2, 64, 4, WQ>;
 template <int WQ> using Tile64 = Gemm<64, 64, 2, 2, 2, 64, 3, WQ>;
 typedef Gemm<64, 128, 2, 2, 1, 64, 2, WQ_NONE> Tile64x128x2;   // 4 waves, two workgroups a CU
+typedef Gemm<64, 64, 2, 2, 1, 64, 2, WQ_NONE> Tile64x3;         // 4 waves, three workgroups a CU
 typedef Gemm<32, 64, 1, 2, 2, 64, 4, WQ_NONE> Tile32;          // 4 waves
 using TileW = Gemm<128, 256, 2, 4, 1, 32, 4, WQ_NONE>;
 using TileW2 = Gemm<128, 256, 2, 2, 1, 32, 2, WQ_NONE>;
@@ -1256,6 +1257,7 @@ hipError_t launch_gemm_planned(const GemmPlan& p, int epi, const void* A, int ld
     else if (big) BD_TILE(Tile128<WQ_NONE>);
     else if (mid && (N / 128) * cdiv(cdiv(rows_cap, 2), 64) > 256) BD_TILE(Tile64x128x2);
     else if (mid) BD_TILE(Tile64x128<WQ_NONE>);
+    else if (epi == EPI_ADD_F32 && (N / 64) * cdiv(cdiv(rows_cap, 2), 64) <= 512) BD_TILE(Tile64x3);
     else BD_TILE(Tile64<WQ_NONE>);
   }
 #undef BD_TILE
