@@ -94,6 +94,13 @@ __device__ __forceinline__ float4 scaled(float4 v, float inv, float4 g) {
   return make_float4(v.x * inv * g.x, v.y * inv * g.y, v.z * inv * g.z, v.w * inv * g.w);
 }
 
+// The sum of a float4's squares, in one order wherever it is compiled: left to
+// the compiler, the product that the others are fused onto varies with the code
+// around it, and with it the last bits of fp32 models.
+__device__ __forceinline__ float squares(float4 v) {
+  return fmaf(v.w, v.w, fmaf(v.z, v.z, fmaf(v.x, v.x, v.y * v.y)));
+}
+
 template <bool PAIR, int NV>
 __global__ __launch_bounds__(256) void k_rmsnorm_rows(float* __restrict__ X,
                                                       const float* __restrict__ g, int d, float eps,
@@ -156,7 +163,7 @@ __global__ __launch_bounds__(256) void k_rmsnorm_rows(float* __restrict__ X,
     }
 #pragma unroll
     for (int i = 0; i < NV; ++i)
-      if (t + i * tpr < nf) ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
+      if (t + i * tpr < nf) ss += squares(v[i]);
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
@@ -215,7 +222,7 @@ void k_rmsnorm_wave(float* __restrict__ X, const float* __restrict__ g, int d, f
   float ss = 0.f;
 #pragma unroll
   for (int i = 0; i < NV; ++i)
-    if (i < nv) ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
+    if (i < nv) ss += squares(v[i]);
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
   const float inv = 1.0f / sqrtf(ss / (float)d + eps);
@@ -273,7 +280,7 @@ static void launch_rmsnorm_as(float* X, const float* g, int d, float eps, const 
   const int b4 = (rows_cap + 3) / 4;
   if (d % 256 || d > 4096) {
     k_rmsnorm_any<PAIR><<<b4, 256, 0, st>>>(X, g, d, eps, M_dev, gather, out, plane, fold);
-  } else if (d >= 2048 && rows_cap > 256) {
+  } else if (d >= 2048 && (rows_cap > 256 || !PAIR)) {   // fp32 models: one order of the sum for any rows
     if (d == 2048) k_rmsnorm_wave<PAIR, 8><<<b4, 256, 0, st>>>(X, g, d, eps, M_dev, gather, out, plane, fold);
     else k_rmsnorm_wave<PAIR, 16><<<b4, 256, 0, st>>>(X, g, d, eps, M_dev, gather, out, plane, fold);
   } else {
