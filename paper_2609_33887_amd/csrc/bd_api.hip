@@ -475,7 +475,7 @@ static bd_status run_forward(bd_model* m, bd_state* s, const PlanView& plan, int
   const hipStream_t st = m->stream;
   const int d = c.d_model, H = c.n_heads, Hkv = c.n_kv_heads, hd = c.head_dim, F = c.ffn_dim;
   // cache layout: K [layer][seq][kv head][pos][hd], V [layer][seq][kv head]
-  // [vstride / 64][hd][64] (bf16) or as K (fp32); bf16 models keep the lo
+  // [vstride / 32][hd][32] (bf16) or as K (fp32); bf16 models keep the lo
   // planes of Q and of each whole cache after the hi planes
   const size_t layer_k = (size_t)s->b * Hkv * s->maxpos * hd;
   const size_t layer_v = (size_t)s->b * Hkv * hd * s->vstride;

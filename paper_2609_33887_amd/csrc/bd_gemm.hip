@@ -4,26 +4,24 @@
 // W [N][K] (weights stored [out][in]), so both operands are K-contiguous.
 //
 // bf16 path (bf16 weights, activations as bf16 hi/lo plane pairs): workgroup
-// tiles of 128x256 (8 wave64s of 64x64), 128x128 (4 waves of 64x64, or 8 of
-// 64x32), 64x128 (4 waves of 32x64) or 64x64 (4 waves of 32x32), the waves
-// in a 2 x (waves / 2)
-// arrangement, MFMA 16x16x32 bf16 with fp32 accumulate (plan_gemm and the
-// launchers choose).  Operands reach LDS through direct global-to-LDS loads
-// into a four-stage ring (K-stages of 32, swizzled rows); one barrier per
-// stage; the residual projections may split K (the partial sums are folded
-// in by the next RMSNorm).
+// tiles of 128 x 256 down to 32 x 64 over 4 or 8 waves (see Gemm and the tiles
+// below it), MFMA 16x16x32 bf16 with fp32 accumulate (plan_gemm and the
+// launchers choose).  Operands reach LDS through direct buffer-to-LDS loads
+// into a ring of two to four stages of 32 or 64 depth (swizzled rows); one
+// barrier per stage; the residual projections may split K (the partial sums
+// are folded in by the next RMSNorm).
 // fp8 weights (WQ = WQ_FP8): W holds OCP fp8 E4M3 codes, one byte per
 // element, with a power-of-two scale per output row; the W stage holds
-// 32-byte rows, each lane converts its 8 codes of a fragment to bf16 (exact)
+// 64-byte rows, each lane converts its 8 codes of a fragment to bf16 (exact)
 // before the MFMA, and the epilogue multiplies each output column by its row
 // scale (exact, so the result equals the bf16 product with the dequantized
 // weights).
-// MXFP4 weights (WQ = WQ_MXFP4): a 32-deep stage is one MX block, so the
-// stage holds each W row's 16 bytes of E2M1 codes and its block exponent; the
-// lane converts its 8 codes with the block scale (v_cvt_scalef32_pk_bf16_fp4:
-// E2M1 value x 2^X, exact in bf16), again the bf16 product with the
-// dequantized weights.  The codes are stored stage-major (WQuant), so a
-// stage's W rows are one contiguous run of 16-byte rows.
+// MXFP4 weights (WQ = WQ_MXFP4): a 64-deep stage is two MX blocks, so the
+// stage holds 16 bytes of E2M1 codes and an exponent for each block of each W
+// row; the lane converts its 8 codes with the block scale
+// (v_cvt_scalef32_pk_bf16_fp4: E2M1 value x 2^X, exact in bf16), again the bf16
+// product with the dequantized weights.  The codes are stored block-major
+// (WQuant), so a block's W rows are one contiguous run of 16-byte rows.
 // f32 path (small fp32 models): fp32 MFMA tiles, the sums in order of depth.
 //
 // The row count M is read from device memory so that a launch sized for the
