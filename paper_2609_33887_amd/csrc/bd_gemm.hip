@@ -190,7 +190,9 @@ struct Gemm {
   floatx4 acc[FM][FN];
   __amdgpu_buffer_rsrc_t rah, ral, rw, re;
   uint32_t ao[LA], wo[LB], eo;
-  uint32_t wstep, estep;         // W (and exponent) bytes per stage
+  // MXFP4: the codes (and exponents) of the stage to be loaded next, their bytes per stage
+  const uint8_t *wnext, *enext;
+  size_t wstep, estep;
   int lane, wave, wm, wn, kg;
 
   // 16-byte chunk of an A row for group g of the lanes at MFMA depth q: the
@@ -208,14 +210,25 @@ struct Gemm {
       load_lds16(rah, s.a[0] + r * SK, ao[i], ka);
       load_lds16(ral, s.a[1] + r * SK, ao[i], ka);
     }
+    // bf16 and fp8: a stage is the next bytes of every W row.  MXFP4: the next
+    // blocks of all N rows, 16 bytes a row; past 2^33 weights their offsets
+    // leave 32 bits, so the resources move from stage to stage (an addition:
+    // with at most three ring stages run() issues every stage once, in order).
+    constexpr uint32_t WRB = WQ == WQ_FP8 ? SK : SK * 2;
+    if constexpr (WQ == WQ_MXFP4) {
+      static_assert(NS <= 3, "stages issued in order");
+      rw = buf_rsrc(wnext);
+      re = buf_rsrc(enext);
+      wnext += wstep;
+      enext += estep;
+    }
 #pragma unroll
     for (int i = 0; i < LB; ++i) {
       uint8_t* d = s.b + (i * NW + wave) * (64 * WLB);
-      if constexpr (WLB == 16) load_lds16(rw, d, wo[i], (uint32_t)kt * wstep);
-      else load_lds4(rw, d, wo[i], (uint32_t)kt * wstep);
+      if constexpr (WLB == 16) load_lds16(rw, d, wo[i], (uint32_t)kt * WRB);
+      else load_lds4(rw, d, wo[i], WQ == WQ_MXFP4 ? 0u : (uint32_t)kt * WRB);
     }
-    if constexpr (WQ == WQ_MXFP4)
-      load_lds4(re, s.be + wave * 256, eo, (uint32_t)kt * estep);
+    if constexpr (WQ == WQ_MXFP4) load_lds4(re, s.be + wave * 256, eo, 0u);
   }
 
   __device__ __forceinline__ void mfma(const Stage& s) {
@@ -332,10 +345,10 @@ struct Gemm {
     }
     if constexpr (WQ == WQ_MXFP4) {
       const size_t kb0 = (size_t)(k0 / MX_BLOCK);
-      rw = buf_rsrc((const uint8_t*)Wv + (kb0 * ldw + n0) * 16);
-      re = buf_rsrc(wexp + kb0 * ldw + n0);
-      wstep = (uint32_t)ldw * (16 * SK / MX_BLOCK);
-      estep = (uint32_t)ldw * (SK / MX_BLOCK);
+      wnext = (const uint8_t*)Wv + (kb0 * ldw + n0) * 16;
+      enext = wexp + kb0 * ldw + n0;
+      wstep = (size_t)ldw * (16 * SK / MX_BLOCK);
+      estep = (size_t)ldw * (SK / MX_BLOCK);
 #pragma unroll
       for (int i = 0; i < LB; ++i) {
         const int by = (i * NW + wave) * 256 + lane * 4;          // byte in [blocks][BN][16]
@@ -346,7 +359,6 @@ struct Gemm {
     } else {
       constexpr int WRB = WQ == WQ_FP8 ? SK : SK * 2, ES = WQ == WQ_FP8 ? 1 : 2;
       rw = buf_rsrc((const uint8_t*)Wv + ((size_t)n0 * ldw + k0) * ES);
-      wstep = WRB;
 #pragma unroll
       for (int i = 0; i < LB; ++i) {
         const int by = (i * NW + wave) * (64 * WLB) + lane * WLB, r = by / WRB, in = by % WRB;

@@ -151,3 +151,67 @@ COMMIT = [
 @pytest.mark.parametrize("w,ids", COMMIT, ids=lambda x: getattr(x, "name", ""))
 def test_commit_many_positions(w, ids):
     check(w, seq_ids=ids)
+
+
+def test_mxfp4_weight_of_more_than_4_gib_of_codes():
+    """Gate/up of 135,168 x 65,536 weights, 4.1 GiB of MXFP4 codes, non-zero in
+    the last 1,024 columns alone, which lie past 4 GiB: blocks read from
+    anywhere else are zero or another block's.  O is zero, so that every row of
+    the window is the mask token's; the weights are E2M1 values times a power of
+    two (exact in the format), and float64 takes the non-zero parts.  Tolerance
+    as for every bf16 model; without the product the logits are off by several
+    units."""
+    from paper_2609_33887_amd import bd
+    from tests.test_gpu_parity import _need_gpu
+    _need_gpu()
+    dev = torch.device("cuda", 0)
+    if torch.cuda.get_device_properties(dev).total_memory < 100 << 30:
+        pytest.skip("needs 60 GiB of device memory")
+    d, F, V, S, D = 65536, 67584, 128, 1024, 256
+    g = torch.Generator(device=dev).manual_seed(180)
+    vals = torch.tensor([0.5, 1.0, 1.5, 2.0, 3.0, 4.0, 6.0], device=dev)
+
+    def e2m1(rows, cols):
+        mag = vals[torch.randint(0, 7, (rows, cols), generator=g, device=dev)]
+        sign = 1 - 2 * torch.randint(0, 2, (rows, cols), generator=g, device=dev)
+        return (mag * sign * 2.0 ** -8).bfloat16()
+
+    def normal(*shape, std=0.02):
+        return torch.randn(shape, generator=g, device=dev).mul_(std).bfloat16()
+
+    def zeros(*shape):
+        return torch.zeros(shape, dtype=torch.bfloat16, device=dev)
+
+    ones = torch.ones(d, device=dev)
+    embed, head = normal(V, d), normal(V, d, std=0.001)
+    gate, up, down = zeros(F, d), zeros(F, d), zeros(d, F)
+    gate[:, -S:], up[:, -S:], down[:D] = e2m1(F, S), e2m1(F, S), e2m1(D, F)
+    tensors = [embed, ones, normal(256, d), zeros(d, 128), ones, gate, up, down, ones, head]
+    cfg = bd.bd_model_cfg(n_layers=1, d_model=d, n_heads=2, n_kv_heads=1, head_dim=64, ffn_dim=F, vocab=V, n_experts=0,
+                          top_k=0, expert_ffn=0, n_shared=0, rms_eps=1e-6, rope_theta=1e4, logit_scale=20.0,
+                          mask_id=V - 1, dtype=bd.BD_BF16, wq=bd.BD_WQ_MXFP4)
+    stream = torch.cuda.current_stream(dev).cuda_stream
+    model = bd.bd_init_model(cfg, [t.data_ptr() for t in tensors], stream)
+    try:
+        prompt = torch.randint(0, V - 1, (1, 16), generator=g, device=dev, dtype=torch.int32)
+        state = bd.bd_prefill(model, prompt.data_ptr(), 1, 16, 16, bd.decode_cfg(0.9, 1, 16))
+        try:
+            logits = torch.zeros(16, V, device=dev)
+            bd.bd_denoise_step(model, state, 0, 0, logits.data_ptr())
+            torch.cuda.synchronize(dev)
+        finally:
+            bd.bd_state_free(state)
+    finally:
+        bd.bd_model_free(model)
+
+    def norm(v):
+        return v / torch.sqrt(v.square().mean() + 1e-6)
+
+    x = embed[V - 1].double()
+    f = norm(x)[-S:]
+    act = torch.nn.functional.silu(gate[:, -S:].double() @ f) * (up[:, -S:].double() @ f)
+    x[:D] += down[:D].double() @ act
+    want = 20.0 * (head.double() @ norm(x))
+    assert want.std() > 1.0
+    assert torch.isneginf(logits[:, V - 1]).all()
+    assert (logits[:, :-1].double() - want[:-1]).abs().max() <= TOL["bf16"][1]
