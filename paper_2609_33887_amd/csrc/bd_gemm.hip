@@ -1127,8 +1127,10 @@ __global__ __launch_bounds__(256) void k_lm_head_f32(const float* __restrict__ A
     if (m >= M) continue;                                   // wave-uniform
     const float v = n == mask_id ? -INFINITY : scale * x[r * G::LD + lane];
     if (so.logits) so.logits[so.at(m) * V + n] = v;
-    float mx = v;
-    int arg = n;
+    // a NaN takes no part in the maximum (a lane that started from one would
+    // keep the columns reduced through it out), only in the sum
+    float mx = v == v ? v : -INFINITY;
+    int arg = v == v ? n : 0x7fffffff;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
       const float om = __shfl_xor(mx, off);

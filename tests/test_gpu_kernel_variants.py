@@ -215,3 +215,31 @@ def test_mxfp4_weight_of_more_than_4_gib_of_codes():
     assert want.std() > 1.0
     assert torch.isneginf(logits[:, V - 1]).all()
     assert (logits[:, :-1].double() - want[:-1]).abs().max() <= TOL["bf16"][1]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_lm_head_argmax_beside_nan_logits(dtype):
+    """Columns of NaN (head rows of NaN; the first of every 64 among them, which a
+    row's reduction starts from) leave the argmax to the other columns; the
+    confidence, a sum over all of them, is NaN.  Both against the logits that the
+    same step returns."""
+    import numpy as np
+    from bd_synth import make_prompts, make_weights
+    from paper_2609_33887_amd import bd
+    from tests.test_gpu_parity import _need_gpu
+    _need_gpu()
+    w = small("v_head_nan", seed=181, dtype=dtype, n_layers=1, batch=2, prompt_len=16, gen_len=32)
+    nan = np.nonzero(np.isin(np.arange(w.vocab) % 64, [0, 2, 5, 32]))[0]
+    ws = make_weights(w)
+    ws[-1][nan] = 0x7FC0 if dtype == "bf16" else np.nan
+    model = bd.Model(w, ws)
+    st = bd.State(model, make_prompts(w), w.gen_len, 0.9, w.n_inflight, w.block_size)
+    conf = torch.zeros((w.batch, w.gen_len), device=model.device)
+    tok = torch.full((w.batch, w.gen_len), -1, dtype=torch.int32, device=model.device)
+    logits = torch.zeros((w.batch, w.gen_len, w.vocab), device=model.device)
+    st.step(conf, tok, logits)
+    torch.cuda.synchronize()
+    assert torch.isnan(logits[..., torch.as_tensor(nan, device=model.device)]).all() and torch.isnan(conf).all()
+    assert torch.equal(tok.long(), logits.nan_to_num(nan=-float("inf"), neginf=-float("inf")).argmax(-1))
+    st.close()
+    model.close()
