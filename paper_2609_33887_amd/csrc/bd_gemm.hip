@@ -1114,7 +1114,7 @@ __global__ __launch_bounds__(256) void k_lm_head_f32(const float* __restrict__ A
                                                      int32_t* __restrict__ parg, int V, StepOut so) {
   typedef F32Head G;
   const int M = *Mp;
-  const int m0 = blockIdx.y * G::BM, n0 = blockIdx.x * FHN;
+  const int m0 = (blockIdx.z * gridDim.y + blockIdx.y) * G::BM, n0 = blockIdx.x * FHN;
   if (m0 >= M) return;
   BD_GEMM_SMEM(G);
   G t;
@@ -1428,7 +1428,9 @@ hipError_t launch_lm_head(bool is_bf16, const void* A, int d, size_t a_plane, co
   } else {
     if (V % FHN || d % 16) return hipErrorInvalidValue;
     ntiles = V / FHN;
-    dim3 grid(ntiles, cdiv(rows_cap, F32Head::BM));
+    // row tiles over y and, past 32,768 of them, z (y and z hold 65,535)
+    const int tiles = cdiv(rows_cap, F32Head::BM), nz = cdiv(tiles, 32768);
+    dim3 grid(ntiles, cdiv(tiles, nz), nz);
     k_lm_head_f32<<<grid, F32Head::NT, 0, st>>>((const float*)A, d, (const float*)W, mask_id, scale, M_dev,
                                        rows_cap, part_max, part_sum, part_arg, V, so);
   }

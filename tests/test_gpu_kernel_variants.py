@@ -243,3 +243,27 @@ def test_lm_head_argmax_beside_nan_logits(dtype):
     assert torch.equal(tok.long(), logits.nan_to_num(nan=-float("inf"), neginf=-float("inf")).argmax(-1))
     st.close()
     model.close()
+
+
+def test_f32_head_over_a_million_rows():
+    """1,064,960 masked positions (256 sequences x 8 blocks of 520), 66,560 row
+    tiles of the fp32 head, more than a grid's second dimension holds.  Without a
+    prompt every sequence is the same, and one row's arithmetic does not depend on
+    the rows beside it: each sequence's confidences are those of a state of one,
+    to the last bit."""
+    from bd_synth import make_weights
+    from paper_2609_33887_amd import bd
+    from tests.test_gpu_parity import _need_gpu
+    _need_gpu()
+    w = small("v_f32_rows", seed=182, dtype="f32", n_layers=1, d_model=64, n_heads=1, n_kv_heads=1, ffn_dim=64, vocab=64,
+              batch=256, prompt_len=0, block_size=520, n_inflight=8, gen_len=4160)
+    model = bd.Model(w, make_weights(w))
+    conf = {}
+    for b in (1, w.batch):
+        st = bd.State(model, torch.zeros((b, 0), dtype=torch.int32), w.gen_len, 0.9, w.n_inflight, w.block_size)
+        conf[b] = torch.zeros((b, w.gen_len), device=model.device)
+        st.step(conf[b])
+        torch.cuda.synchronize()
+        st.close()
+    model.close()
+    assert (conf[1] > 0).all() and (conf[w.batch] == conf[1]).all()
