@@ -267,3 +267,32 @@ def test_f32_head_over_a_million_rows():
         st.close()
     model.close()
     assert (conf[1] > 0).all() and (conf[w.batch] == conf[1]).all()
+
+
+def test_f32_weights_at_any_float():
+    """fp32 weights that start at any float of a buffer (a tensor of a flat
+    checkpoint, say) give what the same weights at a 256-byte boundary give."""
+    from bd_synth import make_prompts, make_weights
+    from paper_2609_33887_amd import bd
+    from tests.test_gpu_parity import _need_gpu
+    _need_gpu()
+    w = small("v_f32_offset", seed=183, dtype="f32", n_layers=1, batch=2, prompt_len=16, gen_len=32)
+    ws = make_weights(w)
+    got = []
+    for shift in (0, 1, 2, 3):
+        model = bd.Model(w, ws)
+        bufs = []
+        for t in model.tensors:
+            b = torch.zeros(t.numel() + 64, device=model.device)
+            b[shift:shift + t.numel()] = t.flatten()
+            bufs.append(b)
+        bd.bd_model_free(model.handle)
+        model.handle = bd.bd_init_model(model.cfg, [b.data_ptr() + 4 * shift for b in bufs], model.stream.cuda_stream)
+        st = bd.State(model, make_prompts(w), w.gen_len, 0.9, w.n_inflight, w.block_size)
+        logits = torch.zeros((w.batch, w.gen_len, w.vocab), device=model.device)
+        st.step(None, None, logits)
+        torch.cuda.synchronize()
+        got.append(logits)
+        st.close()
+        model.close()
+    assert all(torch.equal(got[0], g) for g in got[1:])
