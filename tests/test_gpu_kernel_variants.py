@@ -20,18 +20,31 @@ def check(w, **kw):
 
 
 F32 = [
-    # one live row, 16 K per wave (d 128: one chunk for each of 8 waves), widths of a single tile pair
+    # The products walk the depth in 128-deep stages through a ring of three (the 64-row tile, the head) or four (the
+    # 16-row tile): one stage, one live row, widths of a single tile pair
     small("v_f32_one", seed=120, dtype="f32", d_model=128, n_heads=2, n_kv_heads=2, ffn_dim=32, vocab=64, batch=1,
           prompt_len=3, block_size=1, n_inflight=1, gen_len=6),
-    # depths that leave some waves without a chunk (80 = 5 chunks) or with uneven ones (336 = 21), 19 rows
+    # three stages of which the last is partial (320 = 2 x 128 + 64, 352), 19 rows
     small("v_f32_uneven", seed=121, dtype="f32", d_model=320, n_heads=5, n_kv_heads=1, ffn_dim=352, vocab=192, batch=1,
           prompt_len=19, block_size=19, n_inflight=1, gen_len=38),
-    # head_dim 128, more than 256 keys (every wave of the attention walks several key tiles, the last one partial)
+    # head_dim 128, more than 512 keys (nine and more key tiles of 64, the last one partial)
     small("v_f32_keys", seed=122, dtype="f32", n_heads=4, n_kv_heads=2, head_dim=128, batch=1, prompt_len=602,
           block_size=7, n_inflight=2, gen_len=28),
-    # a prefill of 1,030 rows in 64-row tiles (32 columns x 17 tiles and up), steps in 16-row tiles
+    # a prefill of 1,030 rows in 64-row tiles (32 columns x 17 tiles and up), steps in 16-row tiles; eight stages
     small("v_f32_large", seed=123, dtype="f32", n_heads=8, n_kv_heads=4, ffn_dim=1024, batch=5, prompt_len=206,
           block_size=2, n_inflight=3, gen_len=12),
+    # Deeper rings.  Prefills of 1,024 and 1,280 rows whose QKV and gate/up take the 64-row tile (1,344 / 32 = 42
+    # column tiles x 16 row tiles and the like, from 512 on), head and steps over the same depths, and down products
+    # of the 16-row tile: 4 stages (448: the three-stage ring's longest end) and 5 (608)
+    small("v_f32_d448", seed=124, dtype="f32", d_model=448, n_heads=7, n_kv_heads=7, ffn_dim=608, vocab=192, batch=4,
+          prompt_len=256, block_size=8, n_inflight=1, gen_len=16),
+    # 5 stages (640: one steady round and an end of two), down 6 (704)
+    small("v_f32_d640", seed=125, dtype="f32", d_model=640, n_heads=10, n_kv_heads=5, ffn_dim=704, vocab=192, batch=4,
+          prompt_len=256, block_size=8, n_inflight=1, gen_len=16),
+    # 7 stages (832 = 6.5 x 128: a steady round and an end of four, the last partial), down 7 (864: the four-stage
+    # ring's first steady round)
+    small("v_f32_d832", seed=126, dtype="f32", d_model=832, n_heads=13, n_kv_heads=1, ffn_dim=864, vocab=192, batch=5,
+          prompt_len=256, block_size=8, n_inflight=1, gen_len=16),
 ]
 
 
@@ -112,6 +125,11 @@ ATTN = [
            n_inflight=2, gen_len=74), (8,)),
     (small("v_attn_42_128", seed=155, n_heads=12, n_kv_heads=12, head_dim=128, batch=11, prompt_len=990,
            block_size=33, n_inflight=3, gen_len=99), (10,)),
+    # (4, 2) with the keys in two splits: 100 tiles over 2,120 keys, 80 queries each (one group of 32 idle, one half full)
+    (small("v_attn_42_split64", seed=157, n_layers=1, n_heads=20, n_kv_heads=10, head_dim=64, batch=10, prompt_len=2080,
+           block_size=20, n_inflight=2, gen_len=40), (7,)),
+    (small("v_attn_42_split128", seed=158, n_layers=1, n_heads=20, n_kv_heads=10, head_dim=128, batch=10,
+           prompt_len=2080, block_size=20, n_inflight=2, gen_len=40), (9,)),
     # more sequences than a wave has lanes for their windows, of which the last ends last
     (small("v_attn_b67", seed=156, n_heads=4, n_kv_heads=1, head_dim=64, batch=67, prompt_len=24, block_size=24,
            n_inflight=1, gen_len=48), (0, 63, 64, 66)),
