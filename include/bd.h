@@ -145,8 +145,7 @@ typedef struct bd_state bd_state;
  *  BD_EUNSUPPORTED (MoE, BD_WQ_FP8 or BD_WQ_MXFP4 with the f32 dtype; shapes off the GEMM tiles: with
  *  bf16 every projection's output and input widths -- (H + 2 Hkv) hd, d,
  *  H hd, vocab, 2 ffn or 2 Fe, ffn or Fe -- must be multiples of 128; an
- *  MoE model's d_model a multiple of 256, for its router's four depth
- *  quarters of 64-deep blocks),
+ *  MoE model's d_model a multiple of 256),
  *  BD_ENOMEM, BD_EHIP.
  */
 bd_status bd_init_model(const bd_model_cfg* cfg, const void* const* weights_dev, int32_t n_weights,
@@ -304,7 +303,9 @@ bd_status bd_state_steps(const bd_state* st, int32_t* steps_out);
  */
 bd_status bd_state_stats(bd_model* model, bd_state* st, int64_t* out, int32_t n);
 
-/* Kernel classes timed by bd_profile / bd_profile_read. */
+/* Kernel classes timed by bd_profile / bd_profile_read.  BD_PROF_ROPE keeps its
+ * number and stays zero: RoPE and the K/V cache write are part of the QKV product
+ * (BD_PROF_GEMM_QKV). */
 enum {
     BD_PROF_EMBED = 0, BD_PROF_NORM = 1, BD_PROF_GEMM_QKV = 2, BD_PROF_ROPE = 3, BD_PROF_ATTN = 4,
     BD_PROF_GEMM_O = 5, BD_PROF_GEMM_GU = 6, BD_PROF_GEMM_DOWN = 7, BD_PROF_LM_HEAD = 8,
@@ -330,7 +331,8 @@ bd_status bd_profile_read(bd_model* model, double* ms_out, int32_t* count_out);
  *  take ws_floats floats of the state's workspace at most (the largest extent
  *  over every live row count in [1, rows_cap]; 0 when K is never split).
  *  bd_prefill sizes the workspace with this extent, and the step refuses a
- *  projection whose extent exceeds it.  Outputs may be NULL.
+ *  projection whose extent exceeds it.  How many waves share a tile is chosen at
+ *  the launch and not part of the plan.  Outputs may be NULL.
  *  Errors: BD_EINVAL when N, K or rows_cap < 1; BD_EUNSUPPORTED when N or K
  *  is not a multiple of 128.
  */

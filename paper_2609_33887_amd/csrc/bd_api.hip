@@ -2,8 +2,9 @@
 // allocation, and the launch sequence of one denoising step.
 //
 // One step = embedding gather of the window rows -> per layer {RMSNorm, QKV
-// GEMM, RoPE + K/V cache write, block-causal attention, O GEMM + residual,
-// RMSNorm, gate/up GEMM with SwiGLU epilogue, down GEMM + residual} -> final
+// GEMM with RoPE and the K/V cache write in its epilogue, block-causal attention,
+// O GEMM + residual, RMSNorm, gate/up GEMM with SwiGLU epilogue, down GEMM +
+// residual} -> final
 // RMSNorm of the masked rows -> fused LM-head statistics.  Then the commit
 // kernel applies the threshold rule, sweeps, admits and writes the next plan.
 // Every launch is sized for the largest window and reads the live row counts
@@ -736,7 +737,7 @@ static bd_status state_layout(const bd_model* m, int32_t b, int32_t P, int32_t G
   }
   if (c.n_experts > 0) {
     const int E = c.n_experts, k = c.top_k, Fe = c.expert_ffn;
-    const size_t assign_cap = (size_t)s->rows_cap * k + GROUP_BM;   // + one tile of padding rows
+    const size_t assign_cap = (size_t)s->rows_cap * k + GROUP_BM;   // a tile's slack, which no kernel reaches
     s->moe_tiles = (int)((size_t)s->rows_cap * k / GROUP_BM) + E + 1;
     ALLOC(s->top_e, (size_t)s->rows_cap * k * 4);
     ALLOC(s->top_w, (size_t)s->rows_cap * k * 4);
@@ -768,9 +769,11 @@ static bd_status state_init(bd_model* m, const int32_t* prompt, bd_state* s) {
   const hipStream_t st = m->stream;
   const int d = c.d_model, H = c.n_heads, hd = c.head_dim;
   if (m->bf16) HIPCHK(launch_rope_table(m->inv_freq, hd, s->maxpos, s->rope, st));
-  // Row buffers are read in whole GEMM tiles: clear them once so that rows
-  // past the live count never hold NaN patterns.  The caches are cleared too:
-  // attention tiles read (and weigh by zero) positions past the live keys.
+  // The V cache of bf16 models has to be finite: attention reads it in tiles of 32
+  // keys and weighs those past the last live one by zero.  The others have no such
+  // reader (bf16 products load live rows only, a dead row of an fp32 tile stays in
+  // its own output row, K rows past the last key repeat it); they are cleared so
+  // that a state never carries what the memory held before.
   HIPCHK(launch_zero(s->A, (size_t)s->rows_cap * d * 4, st));
   HIPCHK(launch_zero(s->Kc, s->k_bytes, st));
   HIPCHK(launch_zero(s->Vc, s->v_bytes, st));

@@ -755,7 +755,7 @@ hipError_t launch_gemm_grouped(int epi, const void* A, int lda, size_t a_plane, 
 // They used to come from a second product of the same size, a scaling pass and
 // a scatter pass over [rows][V]: 199 us for 3072 rows x 4096 columns (d 2048)
 // on top of the head's 118, and 246 on top of 242 for 96 x 152064.
-// Tiles that fit the ring go through LDS, four threads a row; the wide ones
+// Tiles that fit the ring go through LDS, four (128 x 128) or eight (64 x 128) threads a row; the wide ones
 // (LM rows from 2048 on) reduce in the accumulators, 16 lanes a row.
 template <class G, bool LOGITS>
 __global__ __launch_bounds__(G::NT) void k_lm_head_bf16(const bf16_t* __restrict__ A, int d,
@@ -1204,32 +1204,38 @@ static void launch_tile(int epi, dim3 grid, const bf16_t* a, int lda, size_t ap,
     k_gemm_bf16<G, EPI_SWIGLU><<<grid, G::NT, 0, st>>>(M_dev, a, w, ap, lda, ldw, N, K, o, ldo, op, nullptr, 1, waux);
 }
 
-// Tile choice: 128x256 (8 waves of 64 x 64, two per SIMD; 128 KB of LDS) over
-// windows of at least 2048 rows for wide plain products (N >= 8192) and
-// residual ones with K >= 2048, when the caller allows it (bf16 weights and a
-// kernel instantiated for it): on
-// 3328-row products it ran gate/up (N 16384) in 494 us against 550 and down
-// (N 2048, K 8192) in 259 against 291.  With 8 waves per tile the shallower
-// O projection (N 2048, K 2048) gains too, even where few rows are live: per
-// decode 256 -> 193 ms on the multi-block window, 90 -> 71 on the MoE window
-// (about 2300 live rows of 4096), 56 -> 39 on the long-prefix window.
-// Otherwise 128x128 when that tiling gives enough workgroups over the row
-// capacity (the 64x64 tile runs out of LDS bandwidth on large products),
-// else 64x64.  Enough: 1024 for plain products (below that the 128x128 grid
-// leaves part of the chip idle for a round: the gate/up product of the dense
-// decode, 512 workgroups over its 1024-row capacity, runs 6% faster in
-// 64x64 tiles), 512 for residual projections, whose split-K partials grow
-// with the tile count (the multi-block O projection ran 18% slower in 64x64
-// tiles).  Plain products over windows of at most 1024 rows take 64x128
-// instead of 64x64 (bf16 weights): half the re-reads of the activation per
-// column tile, two workgroups per CU; the dense decode's gate/up product
-// went from 27.3 to 24.0 us per launch, while the MoE window's (4096 rows)
-// shared-expert products ran 1.5-3% slower in it.  Where half the row capacity
-// (what a step window usually holds) gives more of those tiles than CUs, four
-// waves take one (launch_gemm_planned), so that a CU runs two side by side and one
-// multiplies while the other waits for its stage: 512 x 8192 x 1024, 512 tiles,
-// 22.3 us against 26.4 with eight waves; one tile a CU (96 x 16384 x 2048) takes
-// 34.7 so and 23.8 with eight.  zmax: the largest residual split (1 = none).
+// Tile choice.  Figures: us a launch, from kernel traces of one layer's steps
+// (weights warm in the caches), over half the row capacity as live rows, which
+// is what a step window usually holds.
+// Plain products (gate/up), N x K:
+//  * 128 x 256 (launched in four waves, two workgroups a CU) over capacities of at
+//    least 2048 rows from N 8192 on, bf16 weights.  16384 x 2048: 1024 rows 108-117
+//    (128 x 128 124, 64 x 128 143), 3072 rows 305-315 (365, 385; 64 x 64 476);
+//    8192 x 1024: 2048 rows 59 (71, 69), but 1024 rows 40 (37, 36).
+//  * 128 x 128 where the capacity holds 1024 of them.  4096 x 2048, 2048 rows: 60
+//    (64 x 128 64-69, 64 x 64 75); 16384 x 2048, 512 rows: 62 (62-69, 78).
+//  * 64 x 128 over capacities of at most 1024 rows, bf16 weights.  Where half the
+//    capacity gives more of them than CUs, four waves take one
+//    (launch_gemm_planned), so that a CU runs two side by side and one multiplies
+//    while the other waits for its stage: 8192 x 1024, 512 rows, 512 tiles, 19.5
+//    (eight waves, one a CU: 22.5; 64 x 64 24); one tile a CU (16384 x 2048, 96
+//    rows) takes 26.7 so and 18.8 with eight (64 x 64 21, 128 x 128 26).
+//  * 64 x 64 else.  2816 x 2048, 2048 rows: 57, where 64 x 128 in eight waves
+//    takes 51 and 128 x 128 54.
+// Residual products (O and down), whose split partials the next norm reads:
+//  * 128 x 256 (eight waves) over capacities of at least 2048 rows from K 2048 on,
+//    bf16 weights.  2048 x 8192: 1024 rows 61-65 (128 x 128 65, 64 x 64 80), 3072
+//    rows 204-212 (192, 234); 2048 x 2048: 1024 rows 23-26 (27, 28), 3072 rows 69
+//    (62, 73).
+//  * 128 x 128 where the capacity holds 512 of them (1024 x 1024, 4096 rows: 28
+//    against 33-37 in 64 x 64) and, by plan_resid, from K 4096 on.
+//  * 64 x 64 else; with up to 512 tiles over half the capacity four waves take one,
+//    three workgroups a CU (launch_gemm_planned).  1024 x 1024: 512 rows 7.6 (eight
+//    waves 10.2), 2048 rows, 512 tiles, 15.8 (18.7), 1024 tiles 33 (37); 2048 x 2048:
+//    96 rows 7.5 (8.8), 1024 tiles 50.5 (48.8).
+// Three of these lines lie off where the loops of today put them: 8192 x 1024 at
+// 1024 rows, 2816 x 2048 at 2048, and 128 x 256 for the residual products past 2048
+// live rows.  zmax: the largest residual split (1 = none).
 GemmPlan plan_gemm(bool is_bf16, int N, int K, int rows_cap, bool resid, bool wide_ok) {
   if (!is_bf16) return GemmPlan{64, 64, 1};
   if (wide_ok && N % 256 == 0 && rows_cap >= 2048 && (N >= 8192 || (resid && K >= 2048)))
@@ -1293,8 +1299,11 @@ size_t resid_extent_max(int rows_cap, int N, const ResidSplit& r) {
 }
 
 GemmPlan plan_resid(int N, int K, int rows_cap, bool wide_ok) {
-  // deep products (K >= 4096) take 128-row tiles: with K split, their A and
-  // W re-reads halve against 64x64 at the same parallelism
+  // Deep products (K >= 4096) take 128 x 128: with K split, their A and W re-reads
+  // halve against 64 x 64 at the same parallelism.  2048 x 8192: 512 rows 33-35 us
+  // against 39; 96 rows, where 8 splits make 128 workgroups, 16.1 against 14.0;
+  // 1024 x 4096: 512 rows 15.5 against 14.5 (three workgroups a CU), 2048 rows 35
+  // against 41.
   GemmPlan p = plan_gemm(true, N, K, rows_cap, true, wide_ok);
   if (K >= 4096 && N % 128 == 0 && p.bm != 128) p = GemmPlan{128, 128, 1};
   p.zmax = 8;

@@ -79,8 +79,12 @@ struct ResidSplit {
   const int32_t* Mp;    // row count of the producing GEMM
   int nx, bm, K, zmax;  // its column tiles, row tile, depth and largest split
 };
-constexpr int RESID_TARGET_128 = 256;   // workgroups aimed at with 128-row tiles
-constexpr int RESID_TARGET_64 = 512;    // ... with 64-row tiles
+// Workgroups aimed at with 128-row tiles (one a CU) and with 64-row tiles.  128 x 128
+// at a target of 128 / 256 / 512 (us): 2048 x 8192 over 512 rows 50 / 33 / 40, over 1024
+// rows 91 / 65 / 67, 1024 x 4096 over 2048 rows 48 / 35 / 41.  64 x 64 at 256 / 512 / 1024:
+// 2048 x 2048 over 512 rows 23.4 / 14.5 / 17.8, over 96 rows 8.0 / 7.6 / 8.9.
+constexpr int RESID_TARGET_128 = 256;
+constexpr int RESID_TARGET_64 = 512;
 __host__ __device__ __forceinline__ int resid_splits(int M, const ResidSplit& r) {
   const int tiles = r.nx * ((M + r.bm - 1) / r.bm);
   const int target = r.bm == 128 ? RESID_TARGET_128 : RESID_TARGET_64;
