@@ -1106,6 +1106,7 @@ __global__ __launch_bounds__(G::NT) void k_gemm_qkv_f32(const float* __restrict_
 // fp32 LM head: 16 rows x 64 vocabulary columns; a wave then takes four rows,
 // a lane a column.  The exponentials are summed over columns c, c + 16, c + 32,
 // c + 48 and then over a tree of c.
+constexpr int F32_HEAD_Y = 32768;   // row tiles over a grid's y, further ones over z (y and z hold 65,535)
 __global__ __launch_bounds__(256) void k_lm_head_f32(const float* __restrict__ A, int d,
                                                      const float* __restrict__ W, int mask_id,
                                                      float scale, const int32_t* __restrict__ Mp,
@@ -1114,7 +1115,7 @@ __global__ __launch_bounds__(256) void k_lm_head_f32(const float* __restrict__ A
                                                      int32_t* __restrict__ parg, int V, StepOut so) {
   typedef F32Head G;
   const int M = *Mp;
-  const int m0 = (blockIdx.z * gridDim.y + blockIdx.y) * G::BM, n0 = blockIdx.x * FHN;
+  const int m0 = (blockIdx.z * F32_HEAD_Y + blockIdx.y) * G::BM, n0 = blockIdx.x * FHN;
   if (m0 >= M) return;
   BD_GEMM_SMEM(G);
   G t;
@@ -1437,9 +1438,8 @@ hipError_t launch_lm_head(bool is_bf16, const void* A, int d, size_t a_plane, co
   } else {
     if (V % FHN || d % 16) return hipErrorInvalidValue;
     ntiles = V / FHN;
-    // row tiles over y and, past 32,768 of them, z (y and z hold 65,535)
-    const int tiles = cdiv(rows_cap, F32Head::BM), nz = cdiv(tiles, 32768);
-    dim3 grid(ntiles, cdiv(tiles, nz), nz);
+    const int tiles = cdiv(rows_cap, F32Head::BM);
+    dim3 grid(ntiles, tiles < F32_HEAD_Y ? tiles : F32_HEAD_Y, cdiv(tiles, F32_HEAD_Y));
     k_lm_head_f32<<<grid, F32Head::NT, 0, st>>>((const float*)A, d, (const float*)W, mask_id, scale, M_dev,
                                        rows_cap, part_max, part_sum, part_arg, V, so);
   }
