@@ -23,6 +23,7 @@ EXPORTED = ["bd_init_model", "bd_quantize_fp8", "bd_quantize_mxfp4", "bd_prefill
             "bd_profile_read", "bd_plan_projection", "bd_state_free", "bd_model_free", "bd_last_error", "rl_risk_select",
             "rl_select", "rl_alpha_sweep", "rl_split_exceedance", "rl_monte_carlo"]
 RL_METHODS = {"holm": 0, "bonferroni": 1, "fixed_sequence": 2, "uncorrected": 3, "plugin": 4}
+# "rope" stays zero: RoPE and the cache write are part of gemm_qkv
 PROF_KINDS = ["embed", "norm", "gemm_qkv", "rope", "attn", "gemm_o", "gemm_gu", "gemm_down", "lm_head",
               "commit", "moe_route"]
 
